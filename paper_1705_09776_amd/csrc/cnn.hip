@@ -21,6 +21,8 @@ namespace {
 
 typedef short s4 __attribute__((ext_vector_type(4)));
 typedef short s8 __attribute__((ext_vector_type(8)));
+// (the caller's activation and work buffers are only 8-byte aligned)
+typedef short s8u __attribute__((ext_vector_type(8), aligned(8)));
 typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f2v __attribute__((ext_vector_type(2)));
@@ -378,76 +380,131 @@ __global__ __launch_bounds__(FTHREADS, 2) void k_cnn_infer(const uint8_t* __rest
 
 __device__ __forceinline__ float softplus(float z) { return fmaxf(z, 0.f) + log1pf(expf(-fabsf(z))); }
 
+// Sums, over the 64 lanes of the wave, of N values per lane (N a power of
+// two, at most 64): at each distance a lane hands over the half of its values
+// that its partner keeps, so the values halve as the lanes they cover double
+// (N - 1 exchanges in all, against 6 N for a butterfly of each value); lane l
+// returns the sum of value l % N.
+template <int N>
+__device__ __forceinline__ float wave_sums(float (&v)[N], int lane) {
+    if constexpr (N > 1) {
+        float h[N / 2];
+        const bool up = (lane & (N / 2)) != 0;
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i) {
+            const float keep = up ? v[i + N / 2] : v[i], send = up ? v[i] : v[i + N / 2];
+            h[i] = keep + __uint_as_float(lane_xor<N / 2>(__float_as_uint(send)));
+        }
+        return wave_sums<N / 2>(h, lane);
+    } else {
+        return v[0];
+    }
+}
+
+// The first `n` words of out[] (the last in out_last when that is not null)
+// as the sums of `parts` rows of `stride` floats: 32 columns per workgroup,
+// whose 32 lane rows take every 32nd row each.
+constexpr int kSumCols = 32, kSumRows = 32;
+__global__ __launch_bounds__(kSumCols * kSumRows) void k_sum_parts(const float* __restrict__ part, int parts, int stride,
+                                                                   int n, float* __restrict__ out,
+                                                                   float* __restrict__ out_last) {
+    __shared__ float red[kSumRows][kSumCols + 1];
+    const int c = threadIdx.x % kSumCols, r = threadIdx.x / kSumCols, col = blockIdx.x * kSumCols + c;
+    float s = 0.f;
+    if (col < n) {
+#pragma unroll 4
+        for (int p = r; p < parts; p += kSumRows) s += part[(int64_t)p * stride + col];
+    }
+    red[r][c] = s;
+    __syncthreads();
+    if (r == 0 && col < n) {
+#pragma unroll
+        for (int i = 1; i < kSumRows; ++i) s += red[i][c];
+        if (out_last && col == n - 1) *out_last = s;
+        else out[col] = s;
+    }
+}
+
 // Head backward + loss: per cell dZ, the masked gradient dP4 = (dZ Wh^T) *
-// (X4 > 0) as bf16, and grid-stride partial sums of dWh, dbh and the loss
-// reduced per wave and added to the global gradient with atomics.  The loss
-// is the mean over images of each image's mean over cells and its octaves.
+// (X4 > 0) as bf16, and the sums of dWh, dbh and the loss over this
+// workgroup's cells as one row of `part` (k_sum_parts adds the rows).  The
+// loss is the mean over images of each image's mean over cells and its
+// octaves.
+//
+// Bound by memory (64 B read and 32 B written per cell).  Each lane sums its
+// own cells' 103 products in registers; adding them up used to take 6
+// exchanges per value and one global atomic per value and wave, all on the
+// same 7 cache lines, which was nearly all of the kernel's time (931 us for
+// 614,400 cells); with the halving exchange, one row of sums per workgroup
+// and no atomics it takes 31 us, and the rows' sum 5.
+constexpr int kHeadSums = CC * NHD + NHD + 1;   // dWh, dbh, loss: 103
+constexpr int kHeadRow = 104;                   // floats per row of sums
 __global__ __launch_bounds__(256) void k_head_bwd(const short* __restrict__ X4, const float* __restrict__ P,
                                                   const float* __restrict__ logits, const uint32_t* __restrict__ labels,
                                                   const float* __restrict__ pos_w, const CnnImage* __restrict__ imgs,
-                                                  int nimg, int64_t ncells, short* __restrict__ dP4,
-                                                  float* __restrict__ grad, float* __restrict__ loss) {
+                                                  int nimg, int64_t ncells, int per_block, short* __restrict__ dP4,
+                                                  float* __restrict__ part) {
+    __shared__ float red[4][128];
     const float* Wh = P + kCnnLayers * LAYER_P;
-    float gW[CC * NHD], gb[NHD], lsum = 0.f;
+    // values 0..95: dWh[channel][head]; 96..101: dbh; 102: loss; the rest 0
+    float g0[64], g1[64];
 #pragma unroll
-    for (int i = 0; i < CC * NHD; ++i) gW[i] = 0.f;
-#pragma unroll
-    for (int o = 0; o < NHD; ++o) gb[o] = 0.f;
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < ncells; c += (int64_t)gridDim.x * blockDim.x) {
-        const CnnImage& g = imgs[find_cell_image(imgs, nimg, c)];
-        const float scale = 1.f / ((float)g.H4 * (float)g.W4 * (float)g.n_oct * (float)nimg);
+    for (int i = 0; i < 64; ++i) g0[i] = g1[i] = 0.f;
+    auto add = [&](int i, float v) {
+        if (i < 64) g0[i] += v;
+        else g1[i - 64] += v;
+    };
+    // a contiguous range of cells per workgroup: the image is searched for
+    // once and then only stepped forward
+    const int64_t beg = (int64_t)blockIdx.x * per_block, end = min(beg + per_block, ncells);
+    int64_t c = beg + threadIdx.x;
+    int im = c < end ? find_cell_image(imgs, nimg, c) : 0;
+    for (; c < end; c += blockDim.x) {
+        while (im + 1 < nimg && imgs[im + 1].cell0 <= c) ++im;
+        const CnnImage& g = imgs[im];
+        const int n_oct = g.n_oct;
+        const float scale = 1.f / ((float)g.H4 * (float)g.W4 * (float)n_oct * (float)nimg);
         const uint32_t y = labels[c];
-        float x[CC];
-#pragma unroll
-        for (int ch = 0; ch < CC; ++ch) x[ch] = bf2f(X4[c * CC + ch]);
+        const s8u *xp = reinterpret_cast<const s8u*>(X4 + c * CC);
+        const s8 xa = xp[0], xb = xp[1];
+        const float* zc = logits + c * NHD;
         float dz[NHD];
 #pragma unroll
         for (int o = 0; o < NHD; ++o) {
-            dz[o] = 0.f;
-            if (o < g.n_oct) {
-                const float z = logits[c * NHD + o];
-                const float yo = (float)((y >> o) & 1u), w = pos_w[o];
-                const float s = 1.f / (1.f + expf(-z));
-                dz[o] = (s * (w * yo + 1.f - yo) - w * yo) * scale;
-                lsum += (w * yo * softplus(-z) + (1.f - yo) * softplus(z)) * scale;
-            }
-            gb[o] += dz[o];
+            const float z = zc[o];
+            const float yo = (float)((y >> o) & 1u), w = pos_w[o];
+            const float s = 1.f / (1.f + expf(-z));
+            const bool on = o < n_oct;
+            dz[o] = on ? (s * (w * yo + 1.f - yo) - w * yo) * scale : 0.f;
+            add(102, on ? (w * yo * softplus(-z) + (1.f - yo) * softplus(z)) * scale : 0.f);
+            add(96 + o, dz[o]);
         }
-        short out[CC];
+        s8 oa, ob;
 #pragma unroll
         for (int ch = 0; ch < CC; ++ch) {
+            const float x = bf2f(ch < 8 ? xa[ch] : xb[ch - 8]);
             float d = 0.f;
 #pragma unroll
             for (int o = 0; o < NHD; ++o) {
                 d = fmaf(Wh[ch * NHD + o], dz[o], d);
-                gW[ch * NHD + o] = fmaf(x[ch], dz[o], gW[ch * NHD + o]);
+                const int i = ch * NHD + o;
+                if (i < 64) g0[i] = fmaf(x, dz[o], g0[i]);
+                else g1[i - 64] = fmaf(x, dz[o], g1[i - 64]);
             }
-            out[ch] = f2bf(x[ch] > 0.f ? d : 0.f);
+            const short v = f2bf(x > 0.f ? d : 0.f);
+            if (ch < 8) oa[ch] = v;
+            else ob[ch - 8] = v;
         }
-        s4* dst = reinterpret_cast<s4*>(dP4 + c * CC);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) dst[q] = s4{out[4 * q], out[4 * q + 1], out[4 * q + 2], out[4 * q + 3]};
+        s8u* dst = reinterpret_cast<s8u*>(dP4 + c * CC);
+        dst[0] = oa;
+        dst[1] = ob;
     }
-    const int lane = threadIdx.x & 63;
-    float* gWh = grad + kCnnLayers * LAYER_P;
-    float* gbh = gWh + CC * NHD;
-#pragma unroll
-    for (int i = 0; i < CC * NHD; ++i) {
-        float v = gW[i];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-        if (lane == 0) atomicAdd(&gWh[i], v);
-    }
-#pragma unroll
-    for (int o = 0; o < NHD; ++o) {
-        float v = gb[o];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-        if (lane == 0) atomicAdd(&gbh[o], v);
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off);
-    if (lane == 0) atomicAdd(loss, lsum);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    red[wave][lane] = wave_sums(g0, lane);
+    red[wave][64 + lane] = wave_sums(g1, lane);
+    __syncthreads();
+    const int t = threadIdx.x;
+    if (t < kHeadSums) part[(int64_t)blockIdx.x * kHeadRow + t] = (red[0][t] + red[1][t]) + (red[2][t] + red[3][t]);
 }
 
 // Input gradient of layer l: dX_{l-1}[p][ci] = sum_t sum_co W[t][ci][co]
@@ -665,13 +722,21 @@ hipError_t launch_cnn_backward(const uint8_t* images, const float* params, const
                                const CnnImage* imgs, int nimg, int ntiles, int nchunks, const float* logits,
                                const uint32_t* labels, const float* pos_w, short* dbuf, float* grad, float* loss,
                                int wgrid, hipStream_t s) {
-    hipLaunchKernelGGL(k_fill, dim3((kCnnParams + 255) / 256), dim3(256), 0, s, grad, kCnnParams, 0.f);
-    hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, s, loss, 1, 0.f);
+    hipLaunchKernelGGL(k_fill, dim3((kCnnLayers * LAYER_P + 255) / 256), dim3(256), 0, s, grad, kCnnLayers * LAYER_P, 0.f);
     short* dA = dbuf;
     short* dB = dbuf + ncells * CC;
-    const int hgrid = std::max(1, std::min((int)((ncells + 255) / 256), wgrid));
+    // one workgroup per 256 cells, or wgrid of them with a longer range each;
+    // their sums go to dB, which nothing else uses until the first
+    // k_conv_bwd_data (416 B per workgroup of the 32 B per cell it has; an
+    // image has at least 16 cells)
+    const int64_t groups = (ncells + 255) / 256;
+    const int hgrid = (int)std::max<int64_t>(1, std::min<int64_t>(groups, wgrid));
+    const int per_block = (int)((groups + hgrid - 1) / hgrid) * 256;
+    float* part = reinterpret_cast<float*>(dB);
     hipLaunchKernelGGL(k_head_bwd, dim3(hgrid), dim3(256), 0, s, acts + (int64_t)(kCnnLayers - 1) * ncells * CC,
-                       params, logits, labels, pos_w, imgs, nimg, ncells, dA, grad, loss);
+                       params, logits, labels, pos_w, imgs, nimg, ncells, per_block, dA, part);
+    hipLaunchKernelGGL(k_sum_parts, dim3((kHeadSums + kSumCols - 1) / kSumCols), dim3(kSumCols * kSumRows), 0, s, part,
+                       hgrid, kHeadRow, kHeadSums, grad + kCnnLayers * LAYER_P, loss);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     for (int l = kCnnLayers - 1; l >= 0; --l) {
