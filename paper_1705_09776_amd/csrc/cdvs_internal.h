@@ -177,7 +177,6 @@ struct CnnImage {
     int32_t n_oct;     // octaves of the image (valid head channels)
     int32_t tiles_x;   // 16-cell segments per row
     int32_t tile0;     // first conv tile (16 x 4 cells) of the image
-    int32_t chunk0;    // first 16-cell row chunk of the image
     int32_t ftiles_x;  // fused-inference tiles (kCnnFusedW x kCnnFusedH cells) per row
     int32_t ftile0;    // first fused-inference tile of the image
 };
@@ -241,9 +240,9 @@ hipError_t launch_cnn_forward(const uint8_t* images, const float* params, short*
                               const CnnImage* imgs, int nimg, int ntiles, float* logits, uint8_t* mask, float zthr,
                               hipStream_t s);
 hipError_t launch_cnn_backward(const uint8_t* images, const float* params, const short* acts, int64_t ncells,
-                               const CnnImage* imgs, int nimg, int ntiles, int nchunks, const float* logits,
-                               const uint32_t* labels, const float* pos_w, short* dbuf, float* grad, float* loss,
-                               int wgrid, hipStream_t s);
+                               const CnnImage* imgs, int nimg, int ntiles, const int32_t* owner, int nftiles,
+                               const float* logits, const uint32_t* labels, const float* pos_w, short* dbuf,
+                               float* grad, float* loss, int wgrid, hipStream_t s);
 hipError_t launch_cnn_adam(float* p, const float* g, float* m, float* v, int step, float lr, float b1, float b2,
                            float eps, hipStream_t s);
 hipError_t launch_cnn_labels(const cdvs_keypoint* kp, const int32_t* count, int kp_cap, const CnnImage* imgs, int nimg,

@@ -90,13 +90,6 @@ __device__ __forceinline__ s4 s2d_frag(const uint8_t* __restrict__ images, const
     return b;
 }
 
-// One s2d channel ci of cell (cy, cx).
-__device__ __forceinline__ short s2d_chan(const uint8_t* __restrict__ images, const CnnImage& g, int cy, int cx,
-                                          int ci) {
-    const int y = min(4 * cy + (ci >> 2), g.H - 1), x = min(4 * cx + (ci & 3), g.W - 1);
-    return f2bf((float)images[g.src + (int64_t)y * g.src_pitch + x] / 255.f);
-}
-
 // Forward 3x3 conv + bias + relu for a 16-cell x 4-row tile (one wave per row).
 template <bool FIRST>
 __global__ __launch_bounds__(256) void k_conv_fwd(const uint8_t* __restrict__ images, const short* __restrict__ X,
@@ -545,69 +538,177 @@ __global__ __launch_bounds__(256) void k_conv_bwd_data(const short* __restrict__
 }
 
 // Weight and bias gradients of layer l: dW[t][ci][co] = sum_p X_{l-1}[p + d_t][ci]
-// dP_l[p][co] as MFMAs with K = 16 pixels of one row; grid-stride over
-// 16-cell row chunks, per-lane partial sums added with global atomics.
+// dP_l[p][co], db[co] = sum_p dP_l[p][co], as v_mfma_f32_16x16x32_bf16 with
+// K = 32 cells of one row.
+//
+// One 256-lane workgroup per tile of 32 x 16 cells at a time, the grid
+// striding over the tiles with the sums kept in registers.  Both operands
+// need their cells along K, while a cell's 16 channels are contiguous in
+// memory: the tile of dP and the tile of X with a one-cell rim are staged
+// through LDS transposed ([row][channel][cell], two cells packed per 4-byte
+// write; row strides of 40 and 56 shorts put the 16 channels of an operand
+// read on different banks).  A wave takes four rows: a row of X is read once
+// and, shifted by a cell either way in registers, serves the nine taps of up
+// to three rows of dP.  The workgroup's four waves are added up in LDS and
+// written as one row of sums for k_sum_parts (a single workgroup writes the
+// gradient itself).
+//
+// Bound by memory: 64 B per cell.  Gathering operands two bytes at a time and
+// adding every wave's sums with global atomics took 272 us for 614,400 cells
+// (303 us for the first layer, which also divided per pixel); this takes
+// 13 us (18 us), the rows' sum 5.
+constexpr int WTW = kCnnFusedW, WTH = kCnnFusedH;   // 32 x 16 cells
+constexpr int WXS = 56, WPS = 40;                   // LDS strides of a channel's row of X and dP (shorts)
+constexpr int WX0 = 8;                              // position of the tile's first cell in a row of X
+constexpr int kConvSums = LAYER_P;                  // dW (9 x 16 x 16), db (16)
+static_assert(WTW == 32 && WTH == 16, "a wave takes four rows of 32 cells");
+
+// The 16 bytes (8 channels, 8 half ..) of cell (cy, cx) of the layer input,
+// or of the space-to-depth image when FIRST; zero outside the image.
+template <bool FIRST>
+__device__ __forceinline__ s8 load_cell8(const uint8_t* __restrict__ images, const short* __restrict__ X,
+                                         const CnnImage& g, int cy, int cx, int half) {
+    s8 v = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (cy < 0 || cy >= g.H4 || cx < 0 || cx >= g.W4) return v;
+    if constexpr (!FIRST) {
+        v = *reinterpret_cast<const s8u*>(X + (g.cell0 + (int64_t)cy * g.W4 + cx) * CC + 8 * half);
+    } else {
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const uint8_t* row = images + g.src + (int64_t)min(4 * cy + 2 * half + r, g.H - 1) * g.src_pitch;
+            const int x0 = 4 * cx;
+            uint32_t px = 0;
+            if (x0 + 3 < g.W && ((uintptr_t)(row + x0) & 3) == 0) {
+                px = *reinterpret_cast<const uint32_t*>(row + x0);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) px |= (uint32_t)row[min(x0 + j, g.W - 1)] << (8 * j);
+            }
+            // u * (1 / 255) and u / 255 round to the same bf16 for every u8
+            const float k = 1.f / 255.f;
+            const uint32_t lo = f2bf2((float)(px & 255u) * k, (float)((px >> 8) & 255u) * k);
+            const uint32_t hi = f2bf2((float)((px >> 16) & 255u) * k, (float)(px >> 24) * k);
+            v[4 * r] = (short)lo;
+            v[4 * r + 1] = (short)(lo >> 16);
+            v[4 * r + 2] = (short)hi;
+            v[4 * r + 3] = (short)(hi >> 16);
+        }
+    }
+    return v;
+}
+
 template <bool FIRST>
 __global__ __launch_bounds__(256) void k_conv_bwd_weight(const uint8_t* __restrict__ images,
                                                          const short* __restrict__ Xprev, const short* __restrict__ dP,
-                                                         const CnnImage* __restrict__ imgs, int nimg, int nchunks,
-                                                         float* __restrict__ gW, float* __restrict__ gb) {
-    const int lane = threadIdx.x & 63, kb = lane >> 4, li = lane & 15;
-    const int wave_g = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int nwaves = (gridDim.x * blockDim.x) >> 6;
-    f4 acc[9];
+                                                         const CnnImage* __restrict__ imgs,
+                                                         const int32_t* __restrict__ owner, int ntiles,
+                                                         float* __restrict__ part) {
+    constexpr int XP = WTW / 2 + 2;                      // cell pairs per staged row of X: cells -2 .. 33
+    constexpr int NX = (WTH + 2) * XP * 2, NP = WTH * (WTW / 2) * 2;
+    constexpr int JX = (NX + 255) / 256, JP = NP / 256;
+    static_assert(NP % 256 == 0, "whole rounds");
+    __shared__ __align__(16) short Xt[(WTH + 2) * CC * WXS];
+    __shared__ __align__(16) short Pt[WTH * CC * WPS];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, kb = lane >> 4, li = lane & 15;
+    f4 acc[9], accb = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < 9; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
-    float bsum = 0.f;
-    for (int ch = wave_g; ch < nchunks; ch += nwaves) {
-        // chunk -> (image, row, 16-cell segment): chunks of an image are
-        // numbered row-major with tiles_x segments per row
-        int lo = 0, hi = nimg - 1;
-        while (lo < hi) {
-            int mid = (lo + hi + 1) >> 1;
-            if (imgs[mid].chunk0 <= ch) lo = mid;
-            else hi = mid - 1;
-        }
-        const CnnImage& g = imgs[lo];
-        const int lc = ch - g.chunk0;
-        const int cy = lc / g.tiles_x, cx0 = (lc % g.tiles_x) * kCnnTileW;
-        s4 b;
+    const short one = 0x3F80;   // 1.0: a row of ones sums dP itself
+    const s8 ones = {one, one, one, one, one, one, one, one};
+    uint32_t* X32 = reinterpret_cast<uint32_t*>(Xt);
+    uint32_t* P32 = reinterpret_cast<uint32_t*>(Pt);
+    for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        const CnnImage g = imgs[owner[tile]];
+        const int lt = tile - g.ftile0;
+        const int ty0 = (lt / g.ftiles_x) * WTH, tx0 = (lt % g.ftiles_x) * WTW;
+        // every load of the tile goes out before the first LDS write; an item
+        // is half of the channels of two neighbouring cells
+        s8 xv[JX][2], pv[JP][2];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int xx = cx0 + 4 * kb + j;
-            b[j] = xx < g.W4 ? dP[(g.cell0 + (int64_t)cy * g.W4 + xx) * CC + li] : (short)0;
-            bsum += bf2f(b[j]);
+        for (int j = 0; j < JX; ++j) {
+            const int it = tid + 256 * j, half = it & 1, k = (it >> 1) % XP, r = (it >> 1) / XP;
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+                xv[j][c] = load_cell8<FIRST>(images, Xprev, g, it < NX ? ty0 - 1 + r : -1, tx0 - 2 + 2 * k + c, half);
         }
 #pragma unroll
-        for (int t = 0; t < 9; ++t) {
-            const int yy = cy + t / 3 - 1;
-            s4 a;
+        for (int j = 0; j < JP; ++j) {
+            const int it = tid + 256 * j, half = it & 1, k = (it >> 1) % (WTW / 2), r = (it >> 1) / (WTW / 2);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int xx = cx0 + 4 * kb + j + t % 3 - 1;
-                short v = 0;
-                if (yy >= 0 && yy < g.H4 && xx >= 0 && xx < g.W4) {
-                    if constexpr (FIRST) v = s2d_chan(images, g, yy, xx, li);
-                    else v = Xprev[(g.cell0 + (int64_t)yy * g.W4 + xx) * CC + li];
-                }
-                a[j] = v;
+            for (int c = 0; c < 2; ++c) pv[j][c] = load_cell8<false>(nullptr, dP, g, ty0 + r, tx0 + 2 * k + c, half);
+        }
+        __syncthreads();   // the previous tile's readers are done
+#pragma unroll
+        for (int j = 0; j < JX; ++j) {
+            const int it = tid + 256 * j, half = it & 1, k = (it >> 1) % XP, r = (it >> 1) / XP;
+            if (it < NX) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c)
+                    X32[((r * CC + 8 * half + c) * WXS + WX0 - 2) / 2 + k] =
+                        (uint32_t)(uint16_t)xv[j][0][c] | ((uint32_t)(uint16_t)xv[j][1][c] << 16);
             }
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[t], 0, 0, 0);
+        }
+#pragma unroll
+        for (int j = 0; j < JP; ++j) {
+            const int it = tid + 256 * j, half = it & 1, k = (it >> 1) % (WTW / 2), r = (it >> 1) / (WTW / 2);
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                P32[(r * CC + 8 * half + c) * WPS / 2 + k] =
+                    (uint32_t)(uint16_t)pv[j][0][c] | ((uint32_t)(uint16_t)pv[j][1][c] << 16);
+        }
+        __syncthreads();
+        // this wave's rows of dP: 4 wave .. 4 wave + 3; B[k = cell 8 kb + j][co = li]
+        s8 b[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            b[q] = *reinterpret_cast<const s8*>(&Pt[((4 * wave + q) * CC + li) * WPS + 8 * kb]);
+            accb = mfma32(ones, b[q], accb);
+        }
+        // rows of X: row r of the staged tile is image row ty0 - 1 + r, and
+        // with dP row q it is tap row dy + 1 = r - (4 wave + q)
+#pragma unroll
+        for (int x = 0; x < 6; ++x) {
+            const short* row = &Xt[((4 * wave + x) * CC + li) * WXS + WX0 + 8 * kb];
+            const uint4 d = *reinterpret_cast<const uint4*>(row);
+            const uint32_t dl = *reinterpret_cast<const uint32_t*>(row - 2), dr = *reinterpret_cast<const uint32_t*>(row + 8);
+            const uint32_t m1 = __builtin_amdgcn_alignbyte(d.y, d.x, 2), m2 = __builtin_amdgcn_alignbyte(d.z, d.y, 2),
+                           m3 = __builtin_amdgcn_alignbyte(d.w, d.z, 2);
+            const uint4 al = make_uint4(__builtin_amdgcn_alignbyte(d.x, dl, 2), m1, m2, m3);   // cells x - 1
+            const uint4 ar = make_uint4(m1, m2, m3, __builtin_amdgcn_alignbyte(dr, d.w, 2));   // cells x + 1
+            const s8 a[3] = {__builtin_bit_cast(s8, al), __builtin_bit_cast(s8, d), __builtin_bit_cast(s8, ar)};
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (x - q >= 0 && x - q <= 2) {
+#pragma unroll
+                    for (int dx = 0; dx < 3; ++dx) acc[3 * (x - q) + dx] = mfma32(a[dx], b[q], acc[3 * (x - q) + dx]);
+                }
         }
     }
-    // acc[t][r] = dW[t][ci = 4 kb + r][co = li]
+    // acc[t][r] = dW[t][ci = 4 kb + r][co = li]; every row of accb is db[li]
+    __syncthreads();
+    static_assert(sizeof(Xt) >= 3 * kConvSums * sizeof(float), "three waves' sums");
+    float* red = reinterpret_cast<float*>(Xt);
+    if (wave > 0) {
+        float* w = red + (wave - 1) * kConvSums;
 #pragma unroll
-    for (int t = 0; t < 9; ++t)
+        for (int t = 0; t < 9; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) atomicAdd(&gW[(t * CC + 4 * kb + r) * CC + li], acc[t][r]);
-    bsum += __shfl_xor(bsum, 16);
-    bsum += __shfl_xor(bsum, 32);
-    if (lane < 16) atomicAdd(&gb[li], bsum);
-}
-
-__global__ void k_fill(float* p, int n, float v) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
+            for (int r = 0; r < 4; ++r) w[(t * CC + 4 * kb + r) * CC + li] = acc[t][r];
+        if (kb == 0) w[CONV_W + li] = accb[0];
+    }
+    __syncthreads();
+    if (wave == 0) {
+        float* out = part + (int64_t)blockIdx.x * kConvSums;
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = (t * CC + 4 * kb + r) * CC + li;
+                out[i] = (acc[t][r] + red[i]) + (red[kConvSums + i] + red[2 * kConvSums + i]);
+            }
+        const int i = CONV_W + li;
+        if (kb == 0) out[i] = (accb[0] + red[i]) + (red[kConvSums + i] + red[2 * kConvSums + i]);
+    }
 }
 
 __global__ void k_fill_u32(uint32_t* p, int64_t n) {
@@ -719,10 +820,9 @@ hipError_t launch_cnn_forward(const uint8_t* images, const float* params, short*
 }
 
 hipError_t launch_cnn_backward(const uint8_t* images, const float* params, const short* acts, int64_t ncells,
-                               const CnnImage* imgs, int nimg, int ntiles, int nchunks, const float* logits,
-                               const uint32_t* labels, const float* pos_w, short* dbuf, float* grad, float* loss,
-                               int wgrid, hipStream_t s) {
-    hipLaunchKernelGGL(k_fill, dim3((kCnnLayers * LAYER_P + 255) / 256), dim3(256), 0, s, grad, kCnnLayers * LAYER_P, 0.f);
+                               const CnnImage* imgs, int nimg, int ntiles, const int32_t* owner, int nftiles,
+                               const float* logits, const uint32_t* labels, const float* pos_w, short* dbuf,
+                               float* grad, float* loss, int wgrid, hipStream_t s) {
     short* dA = dbuf;
     short* dB = dbuf + ncells * CC;
     // one workgroup per 256 cells, or wgrid of them with a longer range each;
@@ -739,17 +839,24 @@ hipError_t launch_cnn_backward(const uint8_t* images, const float* params, const
                        hgrid, kHeadRow, kHeadSums, grad + kCnnLayers * LAYER_P, loss);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    // weight gradients: as many workgroups as rows of sums fit in the free
+    // half of the work buffer (32 B per cell), at most two per compute unit;
+    // one alone writes the gradient itself
+    const int parts = (int)std::min<int64_t>(std::min(nftiles, wgrid),
+                                             ncells * CC * (int64_t)sizeof(short) / (kConvSums * (int64_t)sizeof(float)));
     for (int l = kCnnLayers - 1; l >= 0; --l) {
         const float* W = params + l * LAYER_P;
-        float* gW = grad + l * LAYER_P;
-        float* gb = gW + CONV_W;
+        float* gl = grad + l * LAYER_P;
         const short* Xprev = l > 0 ? acts + (int64_t)(l - 1) * ncells * CC : nullptr;
+        float* out = parts > 1 ? reinterpret_cast<float*>(dB) : gl;
+        const dim3 wg(std::max(parts, 1));
         if (l == 0)
-            hipLaunchKernelGGL(k_conv_bwd_weight<true>, dim3(wgrid), dim3(256), 0, s, images, nullptr, dA, imgs, nimg,
-                               nchunks, gW, gb);
+            hipLaunchKernelGGL(k_conv_bwd_weight<true>, wg, dim3(256), 0, s, images, nullptr, dA, imgs, owner, nftiles, out);
         else
-            hipLaunchKernelGGL(k_conv_bwd_weight<false>, dim3(wgrid), dim3(256), 0, s, images, Xprev, dA, imgs, nimg,
-                               nchunks, gW, gb);
+            hipLaunchKernelGGL(k_conv_bwd_weight<false>, wg, dim3(256), 0, s, images, Xprev, dA, imgs, owner, nftiles, out);
+        if (parts > 1)
+            hipLaunchKernelGGL(k_sum_parts, dim3((kConvSums + kSumCols - 1) / kSumCols), dim3(kSumCols * kSumRows), 0, s,
+                               out, parts, kConvSums, kConvSums, gl, nullptr);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (l > 0) {
             hipLaunchKernelGGL(k_conv_bwd_data, dim3(ntiles), dim3(256), 0, s, dA, W, Xprev, dB, imgs, nimg);
