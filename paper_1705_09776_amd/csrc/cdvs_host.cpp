@@ -907,14 +907,9 @@ cdvs_status cdvs_cnn_forward(cdvs_ctx* ctx, const uint8_t* d_images, const float
     const float zthr = d_mask ? logf(tau / (1.f - tau)) : 0.f;
     hipStream_t s = (hipStream_t)stream;
     Bracket b(ctx, CDVS_KERNEL_CNN_FORWARD, s);
-    if (!d_acts) {
-        if (!d_logits && !d_mask) return CDVS_OK;
-        HIP_OR_FAIL(ctx, launch_cnn_infer(d_images, d_params, ctx->d_cnn_frag, ctx->d_cnn, ctx->d_cnn_owner,
-                                          ctx->cnn_ftiles, d_logits, d_mask, zthr, s));
-        return CDVS_OK;
-    }
-    HIP_OR_FAIL(ctx, launch_cnn_forward(d_images, d_params, (short*)d_acts, ctx->ncells, ctx->d_cnn, ctx->n,
-                                        ctx->cnn_tiles, d_logits, d_mask, zthr, s));
+    if (!d_acts && !d_logits && !d_mask) return CDVS_OK;
+    HIP_OR_FAIL(ctx, launch_cnn_forward(d_images, d_params, ctx->d_cnn_frag, ctx->d_cnn, ctx->d_cnn_owner,
+                                        ctx->cnn_ftiles, (short*)d_acts, ctx->ncells, d_logits, d_mask, zthr, s));
     return CDVS_OK;
 }
 

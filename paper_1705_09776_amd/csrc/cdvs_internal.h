@@ -234,11 +234,10 @@ hipError_t launch_describe(const float* pyr, const OctGeom* geom, const cdvs_key
                            int n_images, const DescParams& dp, float* desc, hipStream_t stream);
 
 constexpr int kCnnFragShorts = kCnnLayers * 5 * 64 * 8;   // packed MFMA weight fragments (5 tap pairs)
-hipError_t launch_cnn_infer(const uint8_t* images, const float* params, short* frag, const CnnImage* imgs,
-                            const int32_t* owner, int ntiles, float* logits, uint8_t* mask, float zthr, hipStream_t s);
-hipError_t launch_cnn_forward(const uint8_t* images, const float* params, short* acts, int64_t ncells,
-                              const CnnImage* imgs, int nimg, int ntiles, float* logits, uint8_t* mask, float zthr,
-                              hipStream_t s);
+// acts may be null (inference): then only logits and mask are written.
+hipError_t launch_cnn_forward(const uint8_t* images, const float* params, short* frag, const CnnImage* imgs,
+                              const int32_t* owner, int ntiles, short* acts, int64_t ncells, float* logits,
+                              uint8_t* mask, float zthr, hipStream_t s);
 hipError_t launch_cnn_backward(const uint8_t* images, const float* params, const short* acts, int64_t ncells,
                                const CnnImage* imgs, int nimg, int ntiles, const int32_t* owner, int nftiles,
                                const float* logits, const uint32_t* labels, const float* pos_w, short* dbuf,

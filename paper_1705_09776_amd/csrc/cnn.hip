@@ -78,123 +78,26 @@ __device__ __forceinline__ int find_cell_image(const CnnImage* im, int n, int64_
     return lo;
 }
 
-// Four consecutive s2d channels ci = 4 kb + j (row kb of the 4x4 block,
-// columns j = 0..3) of cell (cy, cx), as bf16: u8/255 with edge clamping.
-__device__ __forceinline__ s4 s2d_frag(const uint8_t* __restrict__ images, const CnnImage& g, int cy, int cx,
-                                       int kb) {
-    const int y = min(4 * cy + kb, g.H - 1);
-    const uint8_t* row = images + g.src + (int64_t)y * g.src_pitch;
-    s4 b;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) b[j] = f2bf((float)row[min(4 * cx + j, g.W - 1)] / 255.f);
-    return b;
-}
-
-// Forward 3x3 conv + bias + relu for a 16-cell x 4-row tile (one wave per row).
-template <bool FIRST>
-__global__ __launch_bounds__(256) void k_conv_fwd(const uint8_t* __restrict__ images, const short* __restrict__ X,
-                                                  const float* __restrict__ Wl, const float* __restrict__ bl,
-                                                  short* __restrict__ Y, const CnnImage* __restrict__ imgs, int nimg) {
-    const int tile = xcd_remap(blockIdx.x, gridDim.x);
-    const CnnImage& g = imgs[find_cnn_image(imgs, nimg, tile)];
-    const int lt = tile - g.tile0;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int cy = (lt / g.tiles_x) * kCnnTileH + wave;
-    const int px = (lt % g.tiles_x) * kCnnTileW + (lane & 15);
-    const int kb = lane >> 4, half = kb >> 1, c8 = (kb & 1) * 8;
-    if (cy >= g.H4) return;
-    s8 a[kTapPairs];
-#pragma unroll
-    for (int m = 0; m < kTapPairs; ++m) {
-        const int t = 2 * m + half;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) a[m][j] = t < 9 ? f2bf(Wl[(t * CC + c8 + j) * CC + (lane & 15)]) : (short)0;
-    }
-    f4 acc;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) acc[r] = bl[4 * kb + r];
-#pragma unroll
-    for (int m = 0; m < kTapPairs; ++m) {
-        const int t = 2 * m + half;
-        const int yy = cy + t / 3 - 1, xx = px + t % 3 - 1;
-        s8 b = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (t < 9 && yy >= 0 && yy < g.H4 && xx >= 0 && xx < g.W4) {
-            if constexpr (FIRST) {
-                const s4 lo = s2d_frag(images, g, yy, xx, 2 * (kb & 1)), hi = s2d_frag(images, g, yy, xx, 2 * (kb & 1) + 1);
-                b = s8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-            } else {
-                b = *reinterpret_cast<const s8*>(X + (g.cell0 + (int64_t)yy * g.W4 + xx) * CC + c8);
-            }
-        }
-        acc = mfma32(a[m], b, acc);
-    }
-    if (px < g.W4) {
-        s4 o;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) o[r] = f2bf(fmaxf(acc[r], 0.f));
-        *reinterpret_cast<s4*>(Y + (g.cell0 + (int64_t)cy * g.W4 + px) * CC + 4 * kb) = o;
-    }
-}
-
-// 1x1 head: logits and/or mask bits, one thread per cell.
-__global__ __launch_bounds__(256) void k_head(const short* __restrict__ X4, const float* __restrict__ P,
-                                              const CnnImage* __restrict__ imgs, int nimg, int64_t ncells,
-                                              float* __restrict__ logits, uint8_t* __restrict__ mask, float zthr) {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= ncells) return;
-    const float* Wh = P + kCnnLayers * LAYER_P;
-    const float* bh = Wh + CC * NHD;
-    float x[CC];
-    const uint4* src = reinterpret_cast<const uint4*>(X4 + c * CC);
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const uint4 v = src[q];
-        const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-            x[8 * q + 2 * h] = __uint_as_float(w4[h] << 16);
-            x[8 * q + 2 * h + 1] = __uint_as_float(w4[h] & 0xFFFF0000u);
-        }
-    }
-    float z[NHD];
-#pragma unroll
-    for (int o = 0; o < NHD; ++o) {
-        float s = bh[o];
-#pragma unroll
-        for (int ch = 0; ch < CC; ++ch) s = fmaf(x[ch], Wh[ch * NHD + o], s);
-        z[o] = s;
-    }
-    if (logits) {
-#pragma unroll
-        for (int o = 0; o < NHD; ++o) logits[c * NHD + o] = z[o];
-    }
-    if (mask) {
-        const int n_oct = imgs[find_cell_image(imgs, nimg, c)].n_oct;
-        uint32_t bits = 0;
-#pragma unroll
-        for (int o = 0; o < NHD; ++o)
-            if (o < n_oct && z[o] > zthr) bits |= 1u << o;
-        mask[c] = (uint8_t)bits;
-    }
-}
-
-// Fused inference: the four convolutions and the head for a 32 x 16 block of
-// output cells in one workgroup, with every activation kept in LDS (no
-// activation goes to HBM).  The workgroup stages the s2d input over the block
+// Fused forward pass: the four convolutions and the head for a 32 x 16 block
+// of output cells in one workgroup, with every activation kept in LDS.  For
+// inference no activation goes to HBM; for training (ACTS) each layer's
+// output over the block is written out as well, the same values.  (Training
+// had a kernel per layer, whose waves loaded and converted all the layer's
+// weights for 16 cells each, and for the first layer divided every pixel by
+// 255 nine times over: 182 us for the forward pass of 614,400 cells, now
+// 53 us.)  The workgroup stages the s2d input over the block
 // plus a 4-cell halo (one cell per layer) and each layer writes its output
 // over a region one cell smaller on every side, so the last layer covers
 // exactly the block.  Cells outside the image are written as zeros at every
-// layer, which is the zero padding of each convolution.  The arithmetic is
-// the unfused kernels' (same fragments, same MFMA order, same bf16
-// roundings), so logits and mask bits are identical to theirs.
+// layer, which is the zero padding of each convolution.
 constexpr int FTW = kCnnFusedW, FTH = kCnnFusedH, FHALO = kCnnLayers;
 constexpr int FFW = FTW + 2 * FHALO, FFH = FTH + 2 * FHALO;   // 40 x 24 frame
 constexpr int FSTR = CC;                                       // shorts per cell (32 B, 16-byte aligned reads)
 
 
 // MFMA weight fragments of all layers, packed once per forward call:
-// frag[((l * kTapPairs + m) * 64 + lane) * 8 + j] is exactly the A operand
-// element j that lane `lane` of k_conv_fwd builds for tap pair m of layer l.
+// frag[((l * kTapPairs + m) * 64 + lane) * 8 + j] is element j of lane
+// `lane`'s A operand for tap pair m of layer l.
 __global__ void k_cnn_pack(const float* __restrict__ P, short* __restrict__ frag) {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kCnnLayers * kTapPairs * 64; i += gridDim.x * blockDim.x) {
         const int lane = i % 64, m = (i / 64) % kTapPairs, l = i / (64 * kTapPairs);
@@ -208,12 +111,13 @@ __global__ void k_cnn_pack(const float* __restrict__ P, short* __restrict__ frag
 constexpr int FTHREADS = 512;                       // 8 waves: twice the latency hiding of 4 at the same LDS
 constexpr int FSTAGE = (FFH * FFW * 4 + FTHREADS - 1) / FTHREADS;   // 4-pixel cell rows staged per lane
 
+template <bool ACTS>
 __global__ __launch_bounds__(FTHREADS, 2) void k_cnn_infer(const uint8_t* __restrict__ images, const float* __restrict__ P,
                                                       const short* __restrict__ frag,
                                                       const CnnImage* __restrict__ imgs,
-                                                      const int32_t* __restrict__ owner,
-                                                      float* __restrict__ logits, uint8_t* __restrict__ mask,
-                                                      float zthr) {
+                                                      const int32_t* __restrict__ owner, short* __restrict__ acts,
+                                                      int64_t ncells, float* __restrict__ logits,
+                                                      uint8_t* __restrict__ mask, float zthr) {
     __shared__ __align__(16) short buf[2][FFH * FFW * FSTR];
     __shared__ short lut[256];
     __shared__ float head[CC * NHD + NHD];
@@ -225,7 +129,7 @@ __global__ __launch_bounds__(FTHREADS, 2) void k_cnn_infer(const uint8_t* __rest
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, kb = lane >> 4;
     const int H4 = g.H4, W4 = g.W4;   // read once (the layer loops test every cell against them)
 
-    // u8 -> bf16(u / 255) table (the same expression as s2d_frag)
+    // u8 -> bf16(u / 255) table
     if (threadIdx.x < 256) lut[threadIdx.x] = f2bf((float)threadIdx.x / 255.f);
     for (int i = threadIdx.x; i < CC * NHD + NHD; i += blockDim.x) head[i] = P[kCnnLayers * LAYER_P + i];
     // layer 0 input: s2d of the frame, zero outside the image.  Lanes take
@@ -339,8 +243,13 @@ __global__ __launch_bounds__(FTHREADS, 2) void k_cnn_infer(const uint8_t* __rest
                 o.y = f2bf2(relu(acc[h][2]), relu(acc[h][3]));
                 o.x = in ? o.x : 0u;
                 o.y = in ? o.y : 0u;
-                if (q0 + 16 * h + (lane & 15) < n)
+                if (q0 + 16 * h + (lane & 15) < n) {
                     *reinterpret_cast<uint2*>(&Y[(fy[h] * FFW + fx[h]) * FSTR + 4 * kb]) = o;
+                    // the block's own cells also go out for the backward pass
+                    if (ACTS && in && (unsigned)(fy[h] - FHALO) < (unsigned)FTH && (unsigned)(fx[h] - FHALO) < (unsigned)FTW)
+                        *reinterpret_cast<uint2*>(acts + ((int64_t)l * ncells + g.cell0 + (int64_t)cy * W4 + cx) * CC +
+                                                  4 * kb) = o;
+                }
             }
         }
 #pragma unroll
@@ -788,34 +697,17 @@ __global__ __launch_bounds__(kCountThreads) void k_mask_count(const uint8_t* __r
 
 }  // namespace
 
-hipError_t launch_cnn_infer(const uint8_t* images, const float* params, short* frag, const CnnImage* imgs,
-                            const int32_t* owner, int ntiles, float* logits, uint8_t* mask, float zthr, hipStream_t s) {
+hipError_t launch_cnn_forward(const uint8_t* images, const float* params, short* frag, const CnnImage* imgs,
+                              const int32_t* owner, int ntiles, short* acts, int64_t ncells, float* logits,
+                              uint8_t* mask, float zthr, hipStream_t s) {
     if (ntiles <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_cnn_pack, dim3(9), dim3(256), 0, s, params, frag);
-    hipLaunchKernelGGL(k_cnn_infer, dim3(ntiles), dim3(FTHREADS), 0, s, images, params, frag, imgs, owner, logits,
-                       mask, zthr);
-    return hipGetLastError();
-}
-
-hipError_t launch_cnn_forward(const uint8_t* images, const float* params, short* acts, int64_t ncells,
-                              const CnnImage* imgs, int nimg, int ntiles, float* logits, uint8_t* mask, float zthr,
-                              hipStream_t s) {
-    if (ntiles <= 0) return hipSuccess;
-    for (int l = 0; l < kCnnLayers; ++l) {
-        const float* W = params + l * LAYER_P;
-        const float* b = W + CONV_W;
-        short* Y = acts + (int64_t)l * ncells * CC;
-        if (l == 0)
-            hipLaunchKernelGGL(k_conv_fwd<true>, dim3(ntiles), dim3(256), 0, s, images, nullptr, W, b, Y, imgs, nimg);
-        else
-            hipLaunchKernelGGL(k_conv_fwd<false>, dim3(ntiles), dim3(256), 0, s, images,
-                               acts + (int64_t)(l - 1) * ncells * CC, W, b, Y, imgs, nimg);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    const int blocks = (int)((ncells + 255) / 256);
-    hipLaunchKernelGGL(k_head, dim3(blocks), dim3(256), 0, s, acts + (int64_t)(kCnnLayers - 1) * ncells * CC, params,
-                       imgs, nimg, ncells, logits, mask, zthr);
+    if (acts)
+        hipLaunchKernelGGL(k_cnn_infer<true>, dim3(ntiles), dim3(FTHREADS), 0, s, images, params, frag, imgs, owner, acts,
+                           ncells, logits, mask, zthr);
+    else
+        hipLaunchKernelGGL(k_cnn_infer<false>, dim3(ntiles), dim3(FTHREADS), 0, s, images, params, frag, imgs, owner,
+                           nullptr, ncells, logits, mask, zthr);
     return hipGetLastError();
 }
 
