@@ -45,7 +45,7 @@ struct cdvs_ctx {
     // surrogate CNN cell grid
     std::vector<CnnImage> cnn;
     int64_t ncells = 0;
-    int cnn_tiles = 0, cnn_ftiles = 0;
+    int cnn_ftiles = 0;
     CnnImage* d_cnn = nullptr;
     int32_t* d_active = nullptr;  // [n][kMaxOctaves] active mask cells
     short* d_cnn_frag = nullptr;  // packed weight fragments of the fused inference kernel
@@ -432,7 +432,7 @@ static cdvs_status build_layout(cdvs_ctx* c) {
     // surrogate CNN cells: 4x4-pixel cells of each base image
     c->cnn.assign(c->n, CnnImage{});
     int64_t cell = 0;
-    int tiles = 0, ftiles = 0;
+    int ftiles = 0;
     for (int i = 0; i < c->n; ++i) {
         const cdvs_image_desc& d = c->images[i];
         CnnImage& g = c->cnn[i];
@@ -444,17 +444,13 @@ static cdvs_status build_layout(cdvs_ctx* c) {
         g.H4 = (d.height + 3) / 4;
         g.W4 = (d.width + 3) / 4;
         g.n_oct = std::min(c->octaves[i], kCnnHeads);
-        g.tiles_x = (g.W4 + kCnnTileW - 1) / kCnnTileW;
-        g.tile0 = tiles;
         g.ftiles_x = (g.W4 + kCnnFusedW - 1) / kCnnFusedW;
         g.ftile0 = ftiles;
         ftiles += g.ftiles_x * ((g.H4 + kCnnFusedH - 1) / kCnnFusedH);
         c->cnn_owner.resize(ftiles, i);
-        tiles += g.tiles_x * ((g.H4 + kCnnTileH - 1) / kCnnTileH);
         cell += (int64_t)g.H4 * g.W4;
     }
     c->ncells = cell;
-    c->cnn_tiles = tiles;
     c->cnn_ftiles = ftiles;
     return CDVS_OK;
 }
@@ -931,7 +927,7 @@ cdvs_status cdvs_cnn_backward(cdvs_ctx* ctx, const uint8_t* d_images, const floa
     if ((((uintptr_t)d_acts | (uintptr_t)d_work) & 7) != 0)
         return fail(ctx, CDVS_ERR_ARG, "cdvs_cnn_backward: d_acts and d_work must be 8-byte aligned");
     HIP_OR_FAIL(ctx, launch_cnn_backward(d_images, d_params, (const short*)d_acts, ctx->ncells, ctx->d_cnn, ctx->n,
-                                         ctx->cnn_tiles, ctx->d_cnn_owner, ctx->cnn_ftiles, d_logits, d_labels,
+                                         ctx->d_cnn_owner, ctx->cnn_ftiles, d_logits, d_labels,
                                          d_pos_weight, (short*)d_work, d_grad, d_loss, ctx->wgrad_grid,
                                          (hipStream_t)stream));
     return CDVS_OK;

@@ -167,18 +167,15 @@ constexpr int kFlagFrontShape = 4;      // a front-end source image does not map
 // Surrogate CNN geometry: one entry per image.
 constexpr int kCnnChannels = 16, kCnnHeads = 6, kCnnLayers = 4;
 constexpr int kCnnParams = kCnnLayers * (9 * 16 * 16 + 16) + 16 * 6 + 6;  // 9382
-constexpr int kCnnTileW = 16, kCnnTileH = 4;  // cells per conv workgroup
-constexpr int kCnnFusedW = 32, kCnnFusedH = 16;  // output cells per fused-inference workgroup
+constexpr int kCnnFusedW = 32, kCnnFusedH = 16;  // output cells per workgroup
 struct CnnImage {
     int64_t cell0;     // first cell of the image in the batch's cell arrays
     int64_t src;       // byte offset of the u8 image
     int32_t src_pitch, H, W;
     int32_t H4, W4;    // grid of 4x4 cells
     int32_t n_oct;     // octaves of the image (valid head channels)
-    int32_t tiles_x;   // 16-cell segments per row
-    int32_t tile0;     // first conv tile (16 x 4 cells) of the image
-    int32_t ftiles_x;  // fused-inference tiles (kCnnFusedW x kCnnFusedH cells) per row
-    int32_t ftile0;    // first fused-inference tile of the image
+    int32_t ftiles_x;  // tiles of kCnnFusedW x kCnnFusedH cells per row
+    int32_t ftile0;    // first tile of the image
 };
 
 // Gating of detection by a cell mask.
@@ -239,7 +236,7 @@ hipError_t launch_cnn_forward(const uint8_t* images, const float* params, short*
                               const int32_t* owner, int ntiles, short* acts, int64_t ncells, float* logits,
                               uint8_t* mask, float zthr, hipStream_t s);
 hipError_t launch_cnn_backward(const uint8_t* images, const float* params, const short* acts, int64_t ncells,
-                               const CnnImage* imgs, int nimg, int ntiles, const int32_t* owner, int nftiles,
+                               const CnnImage* imgs, int nimg, const int32_t* owner, int ntiles,
                                const float* logits, const uint32_t* labels, const float* pos_w, short* dbuf,
                                float* grad, float* loss, int wgrid, hipStream_t s);
 hipError_t launch_cnn_adam(float* p, const float* g, float* m, float* v, int step, float lr, float b1, float b2,

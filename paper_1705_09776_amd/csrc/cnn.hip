@@ -5,11 +5,7 @@
 //   Z = X4 . Wh + bh (16 -> 6, one logit per octave), mask bit o = Z_o > logit(tau).
 // Activations are bf16 in HWC order (16 channels = 32 bytes per cell); the
 // 3x3 convolutions of the forward pass and of both backward passes are
-// v_mfma_f32_16x16x16_bf16 with fp32 accumulation; the head is fp32 VALU.
-//
-// MFMA 16x16x16 bf16 operand layout (wave64, checked on the device): lane l
-// holds A[l%16][4(l/16)+j] and B[4(l/16)+j][l%16] for j = 0..3, and
-// D[4(l/16)+r][l%16] for r = 0..3.
+// v_mfma_f32_16x16x32_bf16 with fp32 accumulation; the head is fp32 VALU.
 //
 // Parameter vector (fp32, 9382): for l = 1..4: W_l[9][16][16] ([tap][ci][co],
 // tap = 3(dy+1)+(dx+1)) then b_l[16]; then Wh[16][6] ([c][o]) then bh[6].
@@ -28,9 +24,9 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f2v __attribute__((ext_vector_type(2)));
 typedef __bf16 bf2v __attribute__((ext_vector_type(2)));
 
-// Forward 3x3 convolutions use v_mfma_f32_16x16x32_bf16, two taps per
+// 3x3 convolutions use v_mfma_f32_16x16x32_bf16, two taps per
 // instruction: lane l holds A[l%16][8(l/16)+j] and B[8(l/16)+j][l%16] for
-// j = 0..7 (checked on the device), so with k = 16 (tap - 2m) + ci the lanes
+// j = 0..7, and D[4(l/16)+r][l%16] for r = 0..3 (checked on the device), so with k = 16 (tap - 2m) + ci the lanes
 // with l/16 = 2h + c carry tap 2m + h, input channels 8c..8c+7; the tenth tap
 // of the last pair is zero.
 constexpr int kTapPairs = 5;
@@ -56,16 +52,6 @@ __device__ __forceinline__ float relu(float x) { return __builtin_amdgcn_fmed3f(
 // conversion, which rounds to nearest even as f2bf does (finite inputs).
 __device__ __forceinline__ uint32_t f2bf2(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){a, b}, bf2v));
-}
-
-__device__ __forceinline__ int find_cnn_image(const CnnImage* im, int n, int tile) {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (im[mid].tile0 <= tile) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
 }
 
 __device__ __forceinline__ int find_cell_image(const CnnImage* im, int n, int64_t cell) {
@@ -409,43 +395,6 @@ __global__ __launch_bounds__(256) void k_head_bwd(const short* __restrict__ X4, 
     if (t < kHeadSums) part[(int64_t)blockIdx.x * kHeadRow + t] = (red[0][t] + red[1][t]) + (red[2][t] + red[3][t]);
 }
 
-// Input gradient of layer l: dX_{l-1}[p][ci] = sum_t sum_co W[t][ci][co]
-// dP_l[p - d_t][co], then times (X_{l-1} > 0) to give dP_{l-1} (bf16).
-__global__ __launch_bounds__(256) void k_conv_bwd_data(const short* __restrict__ dP, const float* __restrict__ Wl,
-                                                       const short* __restrict__ Xprev, short* __restrict__ dPprev,
-                                                       const CnnImage* __restrict__ imgs, int nimg) {
-    const int tile = xcd_remap(blockIdx.x, gridDim.x);
-    const CnnImage& g = imgs[find_cnn_image(imgs, nimg, tile)];
-    const int lt = tile - g.tile0;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int cy = (lt / g.tiles_x) * kCnnTileH + wave;
-    const int px = (lt % g.tiles_x) * kCnnTileW + (lane & 15);
-    const int kb = lane >> 4;
-    if (cy >= g.H4) return;
-    s4 a[9];
-#pragma unroll
-    for (int t = 0; t < 9; ++t)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) a[t][j] = f2bf(Wl[(t * CC + (lane & 15)) * CC + 4 * kb + j]);
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int t = 0; t < 9; ++t) {
-        const int yy = cy - (t / 3 - 1), xx = px - (t % 3 - 1);
-        s4 b = {0, 0, 0, 0};
-        if (yy >= 0 && yy < g.H4 && xx >= 0 && xx < g.W4)
-            b = *reinterpret_cast<const s4*>(dP + (g.cell0 + (int64_t)yy * g.W4 + xx) * CC + 4 * kb);
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[t], b, acc, 0, 0, 0);
-    }
-    if (px < g.W4) {
-        const int64_t off = (g.cell0 + (int64_t)cy * g.W4 + px) * CC + 4 * kb;
-        const s4 xp = *reinterpret_cast<const s4*>(Xprev + off);
-        s4 o;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) o[r] = f2bf(bf2f(xp[r]) > 0.f ? acc[r] : 0.f);
-        *reinterpret_cast<s4*>(dPprev + off) = o;
-    }
-}
-
 // Weight and bias gradients of layer l: dW[t][ci][co] = sum_p X_{l-1}[p + d_t][ci]
 // dP_l[p][co], db[co] = sum_p dP_l[p][co], as v_mfma_f32_16x16x32_bf16 with
 // K = 32 cells of one row.
@@ -620,6 +569,99 @@ __global__ __launch_bounds__(256) void k_conv_bwd_weight(const uint8_t* __restri
     }
 }
 
+// Input gradient of layer l: dX_{l-1}[p][ci] = sum_t sum_co W[t][ci][co]
+// dP_l[p - d_t][co], then times (X_{l-1} > 0) to give dP_{l-1} (bf16): the
+// forward convolution with the taps reversed and the weights transposed, and
+// the same MFMA operands (two taps per instruction, the tenth zero).
+//
+// One 256-lane workgroup per 32 x 16 cells; the tile of dP with its rim is
+// staged in LDS and each wave takes four rows.  Bound by memory: 96 B per
+// cell.  A wave per 16 cells loading and converting all the weights for
+// itself took 41 us for 614,400 cells; this takes 13 us.
+__global__ __launch_bounds__(256) void k_conv_bwd_data(const short* __restrict__ dP, const float* __restrict__ Wl,
+                                                       const short* __restrict__ Xprev, short* __restrict__ dPprev,
+                                                       const CnnImage* __restrict__ imgs,
+                                                       const int32_t* __restrict__ owner) {
+    constexpr int PW = WTW + 2, PH = WTH + 2, N = PW * PH * 2, J = (N + 255) / 256;
+    __shared__ __align__(16) short buf[PH * PW * CC];
+    const int tile = xcd_remap(blockIdx.x, gridDim.x);
+    const CnnImage g = imgs[owner[tile]];
+    const int lt = tile - g.ftile0;
+    const int ty0 = (lt / g.ftiles_x) * WTH, tx0 = (lt % g.ftiles_x) * WTW;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, kb = lane >> 4, li = lane & 15;
+    const int half = kb >> 1, c8 = (kb & 1) * 8;
+    s8 v[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int it = threadIdx.x + 256 * j, cell = it >> 1, r = cell / PW, c = cell % PW;
+        v[j] = load_cell8<false>(nullptr, dP, g, it < N ? ty0 - 1 + r : -1, tx0 - 1 + c, it & 1);
+    }
+    // A[ci = lane % 16][8 half-tap channels]: reversed tap t reads the cell at
+    // (t / 3 - 1, t % 3 - 1), so its weight is W[8 - t][ci][co]
+    s8 a[kTapPairs];
+#pragma unroll
+    for (int m = 0; m < kTapPairs; ++m) {
+        const int t = 2 * m + half;
+        const float* w = Wl + ((t < 9 ? 8 - t : 0) * CC + li) * CC + c8;
+        uint32_t p[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) p[j] = t < 9 ? f2bf2(w[2 * j], w[2 * j + 1]) : 0u;
+        a[m] = __builtin_bit_cast(s8, make_uint4(p[0], p[1], p[2], p[3]));
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int it = threadIdx.x + 256 * j;
+        if (it < N) reinterpret_cast<s8*>(buf)[it] = v[j];
+    }
+    // the rows' own activations, needed only after the MFMAs
+    s4 xp[4][2];
+    int64_t off[4][2];
+    bool in[4][2];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int cy = ty0 + 4 * wave + q, cx = tx0 + 16 * h + li;
+            in[q][h] = cy < g.H4 && cx < g.W4;
+            off[q][h] = (g.cell0 + (int64_t)cy * g.W4 + cx) * CC + 4 * kb;
+            xp[q][h] = in[q][h] ? *reinterpret_cast<const s4*>(Xprev + off[q][h]) : s4{0, 0, 0, 0};
+        }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        s8 b[kTapPairs][2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            // tap 0 of this lane's cell; lanes of a pair's second tap are one
+            // cell further (pair 1: the next row's first); the tenth tap is
+            // zero on both sides (a gradient may not be finite)
+            const short* base = &buf[((4 * wave + q) * PW + 16 * h + li) * CC + c8];
+            const short* pa = base + half * CC;
+            b[0][h] = *reinterpret_cast<const s8*>(pa);
+            b[1][h] = *reinterpret_cast<const s8*>(base + half * (PW - 2) * CC + 2 * CC);
+            b[2][h] = *reinterpret_cast<const s8*>(pa + (PW + 1) * CC);
+            b[3][h] = *reinterpret_cast<const s8*>(pa + 2 * PW * CC);
+            b[4][h] = *reinterpret_cast<const s8*>(base + (2 * PW + 2) * CC);
+            if (half) b[4][h] = s8{0, 0, 0, 0, 0, 0, 0, 0};
+        }
+        f4 acc[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int m = 0; m < kTapPairs; ++m)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) acc[h] = mfma32(a[m], b[m][h], acc[h]);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            float r[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) r[i] = bf2f(xp[q][h][i]) > 0.f ? acc[h][i] : 0.f;
+            uint2 o;
+            o.x = f2bf2(r[0], r[1]);
+            o.y = f2bf2(r[2], r[3]);
+            if (in[q][h]) *reinterpret_cast<uint2*>(dPprev + off[q][h]) = o;
+        }
+    }
+}
+
 __global__ void k_fill_u32(uint32_t* p, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0u;
@@ -712,7 +754,7 @@ hipError_t launch_cnn_forward(const uint8_t* images, const float* params, short*
 }
 
 hipError_t launch_cnn_backward(const uint8_t* images, const float* params, const short* acts, int64_t ncells,
-                               const CnnImage* imgs, int nimg, int ntiles, const int32_t* owner, int nftiles,
+                               const CnnImage* imgs, int nimg, const int32_t* owner, int ntiles,
                                const float* logits, const uint32_t* labels, const float* pos_w, short* dbuf,
                                float* grad, float* loss, int wgrid, hipStream_t s) {
     short* dA = dbuf;
@@ -734,7 +776,7 @@ hipError_t launch_cnn_backward(const uint8_t* images, const float* params, const
     // weight gradients: as many workgroups as rows of sums fit in the free
     // half of the work buffer (32 B per cell), at most two per compute unit;
     // one alone writes the gradient itself
-    const int parts = (int)std::min<int64_t>(std::min(nftiles, wgrid),
+    const int parts = (int)std::min<int64_t>(std::min(ntiles, wgrid),
                                              ncells * CC * (int64_t)sizeof(short) / (kConvSums * (int64_t)sizeof(float)));
     for (int l = kCnnLayers - 1; l >= 0; --l) {
         const float* W = params + l * LAYER_P;
@@ -743,15 +785,15 @@ hipError_t launch_cnn_backward(const uint8_t* images, const float* params, const
         float* out = parts > 1 ? reinterpret_cast<float*>(dB) : gl;
         const dim3 wg(std::max(parts, 1));
         if (l == 0)
-            hipLaunchKernelGGL(k_conv_bwd_weight<true>, wg, dim3(256), 0, s, images, nullptr, dA, imgs, owner, nftiles, out);
+            hipLaunchKernelGGL(k_conv_bwd_weight<true>, wg, dim3(256), 0, s, images, nullptr, dA, imgs, owner, ntiles, out);
         else
-            hipLaunchKernelGGL(k_conv_bwd_weight<false>, wg, dim3(256), 0, s, images, Xprev, dA, imgs, owner, nftiles, out);
+            hipLaunchKernelGGL(k_conv_bwd_weight<false>, wg, dim3(256), 0, s, images, Xprev, dA, imgs, owner, ntiles, out);
         if (parts > 1)
             hipLaunchKernelGGL(k_sum_parts, dim3((kConvSums + kSumCols - 1) / kSumCols), dim3(kSumCols * kSumRows), 0, s,
                                out, parts, kConvSums, kConvSums, gl, nullptr);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (l > 0) {
-            hipLaunchKernelGGL(k_conv_bwd_data, dim3(ntiles), dim3(256), 0, s, dA, W, Xprev, dB, imgs, nimg);
+            hipLaunchKernelGGL(k_conv_bwd_data, dim3(ntiles), dim3(256), 0, s, dA, W, Xprev, dB, imgs, owner);
             if ((e = hipGetLastError()) != hipSuccess) return e;
             short* t = dA;
             dA = dB;
