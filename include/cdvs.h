@@ -114,7 +114,8 @@ cdvs_status cdvs_validate(const cdvs_params* params, const cdvs_image_desc* imag
  * host array `images` (copied).  kp_capacity is the per-image record count
  * of every keypoint buffer passed to the calls below (topk <= kp_capacity).
  * Allocates the context's device tables and scratch on the current device
- * (scratch is about 0.4 MB per image).  On failure *out is NULL. */
+ * (scratch is about 0.4 MB per image, and up to 33 MB more for the
+ * aggregation of small batches, see cdvs_scfv).  On failure *out is NULL. */
 cdvs_status cdvs_ctx_create(const cdvs_params* params, const cdvs_image_desc* images, int32_t n_images,
                             int32_t kp_capacity, cdvs_ctx** out);
 void cdvs_ctx_destroy(cdvs_ctx* ctx);
@@ -417,7 +418,9 @@ typedef struct {
  *     d_gv[image][i][.], bit k set when entry k is positive.
  * Shapes: d_gm, d_gv n_images x 512 x 32 floats; d_delta n_images x 512;
  * d_order n_images x 512 int32; d_bits n_images x 512 x 2 uint32.  Uses
- * 196 KB of context scratch (so calls on one context must not overlap). */
+ * 196 KB of context scratch and, in a context of at most 80 images, 75 KB
+ * for each 32 descriptors of kp_capacity x n_images, at most 33 MB or one
+ * image's (so calls on one context must not overlap). */
 cdvs_status cdvs_scfv(cdvs_ctx* ctx, const cdvs_scfv_model* model, const float* d_desc, const int32_t* d_count,
                       float* d_gm, float* d_gv, float* d_delta, int32_t* d_order, uint32_t* d_bits, void* stream);
 

@@ -50,6 +50,8 @@ struct cdvs_ctx {
     int32_t* d_active = nullptr;  // [n][kMaxOctaves] active mask cells
     short* d_cnn_frag = nullptr;  // packed weight fragments of the fused inference kernel
     float* d_scfv_prep = nullptr; // SCFV per-call model constants (kScfvPrepFloats)
+    float* d_scfv_tiles = nullptr;  // SCFV tile blocks of a small batch
+    int scfv_tiles = 0;
     int32_t* d_wh = nullptr;      // per image: width, height
     cdvs_image_desc* d_img = nullptr;  // the image table (front-end output layout)
     // BMLoG variant: per octave, (job, bx, by) of every block; transfer functions
@@ -294,6 +296,7 @@ void cdvs_ctx_destroy(cdvs_ctx* ctx) {
     (void)hipFree(ctx->d_active);
     (void)hipFree(ctx->d_cnn_frag);
     (void)hipFree(ctx->d_scfv_prep);
+    (void)hipFree(ctx->d_scfv_tiles);
     (void)hipFree(ctx->d_wh);
     (void)hipFree(ctx->d_img);
     (void)hipFree(ctx->d_bm_blocks);
@@ -568,6 +571,8 @@ cdvs_status cdvs_ctx_create(const cdvs_params* params, const cdvs_image_desc* im
     ALLOC(c->d_active, sizeof(int32_t) * n * kMaxOctaves);
     ALLOC(c->d_cnn_frag, sizeof(short) * kCnnFragShorts);
     ALLOC(c->d_scfv_prep, sizeof(float) * kScfvPrepFloats);
+    c->scfv_tiles = scfv_tile_blocks(n_images, kp_capacity);
+    if (c->scfv_tiles > 0) ALLOC(c->d_scfv_tiles, sizeof(float) * kScfvTileFloats * (size_t)c->scfv_tiles);
     ALLOC(c->d_wh, sizeof(int32_t) * 2 * n);
     ALLOC(c->d_img, sizeof(cdvs_image_desc) * n);
     ALLOC(c->d_bm_blocks, sizeof(int32_t) * std::max<size_t>(1, c->bm_blocks.size()));
@@ -782,8 +787,8 @@ cdvs_status cdvs_scfv(cdvs_ctx* ctx, const cdvs_scfv_model* model, const float* 
     hipStream_t s = (hipStream_t)stream;
     Bracket b(ctx, CDVS_KERNEL_SCFV, s);
     HIP_OR_FAIL(ctx, launch_scfv(d_desc, d_count, ctx->n, ctx->kp_cap, model->d_pca_mean, model->d_pca_matrix,
-                                 model->d_weights, model->d_means, model->d_variances, ctx->d_scfv_prep, d_gm, d_gv,
-                                 d_delta, d_order, d_bits, s));
+                                 model->d_weights, model->d_means, model->d_variances, ctx->d_scfv_prep,
+                                 ctx->d_scfv_tiles, ctx->scfv_tiles, d_gm, d_gv, d_delta, d_order, d_bits, s));
     return CDVS_OK;
 }
 

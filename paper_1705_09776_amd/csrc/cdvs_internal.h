@@ -256,8 +256,21 @@ constexpr int kScfvPrepIsig = kScfvPrepRsw + kScfvComponents;
 constexpr int kScfvPrepFloats = kScfvPrepIsig + kScfvComponents * kScfvDim;   // 50176
 hipError_t launch_scfv(const float* desc, const int32_t* count, int n_images, int kp_cap, const float* pca_mean,
                        const float* pca_matrix, const float* weights, const float* means, const float* vars,
-                       float* prep, float* gm, float* gv, float* delta, int32_t* order, uint32_t* bits,
-                       hipStream_t s);
+                       float* prep, float* tiles, int tile_blocks, float* gm, float* gv, float* delta, int32_t* order,
+                       uint32_t* bits, hipStream_t s);
+// Small batches form every descriptor tile's posteriors first, independently,
+// into tile blocks (32 descriptors: 512 posteriors, [x | x^2] and scale factors), as many
+// images at a time as the blocks hold, and sum over them afterwards.
+// scfv_tile_blocks: the blocks a context needs, 0 for a batch that takes one
+// workgroup per image instead.
+constexpr int kScfvTileFloats = 32 * (kScfvComponents + 2 * kScfvDim + 8);
+// Up to 80 images: a block costs about 0.14 us, while one workgroup per image
+// takes about 13 us per tile of the longest image, whatever their number
+// (700 to 1000 descriptors: 1 image 37 us, 56 images 245, 96 images 416, 128
+// images 569, against 330 to 415).
+constexpr int kScfvTilesMax = 448;         // 33 MB: 14 images of 1000 descriptors at a time
+constexpr int kScfvTilesMaxImages = 80;
+int scfv_tile_blocks(int n_images, int kp_cap);
 // The allocation-free form keeps the same constants and, for small
 // batches, per-part sums S0, S1, S2 (kScfvPartialFloats each) of images
 // split into parts, in one file-scope device array per GPU: the constants

@@ -52,17 +52,25 @@ __device__ __forceinline__ f4 mfma16(float a, float b, f4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+// Where entry k of component j of the logits' B operand lies: 32 components
+// at a time, in the order in which a wave's lanes read it (step s = k / 2 of
+// lane 32 (k % 2) + j % 32, four steps together), so that a read of four
+// steps is 1 KB of consecutive memory instead of 64 lines.
+__device__ __forceinline__ int b_at(int j, int k) {
+    return ((j >> 5) * 8 + (k >> 3)) * 256 + (32 * (k & 1) + (j & 31)) * 4 + ((k >> 1) & 3);
+}
+
 // Per-component constants of one call, derived on the device from the
-// caller's model: B[j][0..31] = M_j ./ V_j, B[j][32..63] = -1 / (2 V_j);
-// c_j; 1/sqrt(w_j); 1/sigma_jk.
+// caller's model: B[j][0..31] = M_j ./ V_j, B[j][32..63] = -1 / (2 V_j)
+// (at b_at(j, k)); c_j; 1/sqrt(w_j); 1/sigma_jk.
 __global__ __launch_bounds__(256) void k_scfv_prep(const float* __restrict__ w, const float* __restrict__ means,
                                                    const float* __restrict__ vars, float* __restrict__ prep) {
     const int j = blockIdx.x * 8 + (threadIdx.x >> 5), k = threadIdx.x & 31;
     if (j >= NC) return;
     const float m = means[j * PD + k], v = vars[j * PD + k];
     float* B = prep + kScfvPrepB;
-    B[j * 64 + k] = m / v;
-    B[j * 64 + 32 + k] = -0.5f / v;
+    B[b_at(j, k)] = m / v;
+    B[b_at(j, 32 + k)] = -0.5f / v;
     prep[kScfvPrepIsig + j * PD + k] = 1.f / sqrtf(v);
     float t = logf(v) + m * m / v;   // summed over the 32 lanes of this component
 #pragma unroll
@@ -100,12 +108,38 @@ __device__ __forceinline__ float half_sum(float v) {
     return v + xor16(v);
 }
 
+// Outputs of one (component, dimension) entry from its sums: the gradients
+// (Eqs. (7), (12), (14)), and, from the 32 lanes k of the half-wave that hold
+// the component, delta (Eq. (8)) and the sign bits.  Returns delta.
+__device__ __forceinline__ float scfv_entry(int img, int comp, int h, int k, float invK, float S0, float S1, float S2,
+                                            const float* __restrict__ means, const float* __restrict__ vars,
+                                            const float* __restrict__ prep, float* __restrict__ gm_out,
+                                            float* __restrict__ gv_out, float* __restrict__ delta_out,
+                                            uint32_t* __restrict__ bits_out) {
+    const float m = means[comp * PD + k], v = vars[comp * PD + k];
+    const float isg = prep[kScfvPrepIsig + comp * PD + k], rsw = prep[kScfvPrepRsw + comp];
+    const float gm = (S1 - S0 * m) * isg * (invK * rsw);
+    const float gv = (S2 - 2.f * S1 * m + S0 * (m * m - v)) * (isg * isg) * (invK * rsw * 0.70710678118654752f);
+    const int64_t o = ((int64_t)img * NC + comp) * PD + k;
+    gm_out[o] = gm;
+    gv_out[o] = gv;
+    const float mean = half_sum(gm) * (1.f / PD);
+    const float dv = gm - mean;
+    const float dl = sqrtf(half_sum(dv * dv) * (1.f / PD));
+    const uint64_t bm = __ballot(gm > 0.f), bv = __ballot(gv > 0.f);
+    if (k == 0) {
+        delta_out[(int64_t)img * NC + comp] = dl;
+        bits_out[((int64_t)img * NC + comp) * 2] = (uint32_t)(bm >> (32 * h));
+        bits_out[((int64_t)img * NC + comp) * 2 + 1] = (uint32_t)(bv >> (32 * h));
+    }
+    return dl;
+}
+
 // Output stage of one image, shared by the one-workgroup-per-image kernel
 // and the kernel that completes split images: s0s[] holds S0 of every
 // component, acc1/acc2 this lane's S1/S2 entries in the 32x32 MFMA
 // accumulator layout (component 64 wave + 32 t + 8 (i/4) + 4 (lane/32) +
-// i%4, dimension lane%32).  Writes the gradients (Eqs. (7), (12), (14)),
-// delta (Eq. (8)), the sign bits and the component order.
+// i%4, dimension lane%32).  Writes the entries and the component order.
 __device__ __forceinline__ void scfv_output(int img, int K, int wave, int lane, const float* s0s,
                                             const f16v (&acc1)[2], const f16v (&acc2)[2],
                                             const float* __restrict__ means, const float* __restrict__ vars,
@@ -120,22 +154,9 @@ __device__ __forceinline__ void scfv_output(int img, int K, int wave, int lane, 
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const int comp = CPW * wave + 32 * t + 8 * (i >> 2) + 4 * h + (i & 3);
-            const float S0 = s0s[comp], S1 = acc1[t][i], S2 = acc2[t][i];
-            const float m = means[comp * PD + k], v = vars[comp * PD + k];
-            const float isg = prep[kScfvPrepIsig + comp * PD + k], rsw = prep[kScfvPrepRsw + comp];
-            const float gm = (S1 - S0 * m) * isg * (invK * rsw);
-            const float gv = (S2 - 2.f * S1 * m + S0 * (m * m - v)) * (isg * isg) * (invK * rsw * 0.70710678118654752f);
-            const int64_t o = ((int64_t)img * NC + comp) * PD + k;
-            gm_out[o] = gm;
-            gv_out[o] = gv;
-            const float mean = half_sum(gm) * (1.f / PD);
-            const float dv = gm - mean;
-            const float dl = sqrtf(half_sum(dv * dv) * (1.f / PD));
-            const uint64_t bm = __ballot(gm > 0.f), bv = __ballot(gv > 0.f);
+            const float dl = scfv_entry(img, comp, h, k, invK, s0s[comp], acc1[t][i], acc2[t][i], means, vars, prep,
+                                        gm_out, gv_out, delta_out, bits_out);
             if (k == 0) {
-                delta_out[(int64_t)img * NC + comp] = dl;
-                bits_out[((int64_t)img * NC + comp) * 2] = (uint32_t)(bm >> (32 * h));
-                bits_out[((int64_t)img * NC + comp) * 2 + 1] = (uint32_t)(bv >> (32 * h));
                 skey[comp] = dl;
                 sidx[comp] = comp;
             }
@@ -164,15 +185,22 @@ __device__ __forceinline__ void scfv_output(int img, int K, int wave, int lane, 
     order_out[(int64_t)img * NC + tid] = sidx[tid];
 }
 
-// One workgroup of 8 waves per image (SPLIT = false), or per part of an
-// image (SPLIT = true: image blockIdx.x / splits takes descriptor tiles
-// [part * tiles_per_part, (part + 1) * tiles_per_part) and writes its sums
-// S0, S1, S2 to partial block blockIdx.x, which k_scfv_join adds up).
+// One workgroup of 8 waves per image (kWhole), or per part of an image: image
+// blockIdx.x / splits takes descriptor tiles [part * tiles_per_part, (part +
+// 1) * tiles_per_part) and either writes its sums S0, S1, S2 to partial block
+// blockIdx.x, which k_scfv_join adds up (kParts), or, one tile per part, the
+// tile's posteriors (before their scaling) and [X | X.*X] to tile block blockIdx.x, over which
+// k_scfv_sums then sums (kTiles; img0 is the first image).
 // Wave w owns components [64 w, 64 w + 64): their logits and their
 // gradient accumulators live in its registers for the whole range.
-template <bool SPLIT>
+constexpr int kWhole = 0, kParts = 1, kTiles = 2;
+// A tile block: the posteriors' numerators [descriptor][component], [X | X.*X]
+// by rows, and the factor [64 components][descriptor] that scales them.
+constexpr int kTileX = TD * NC, kTileQ = kTileX + TD * 64;
+static_assert(kScfvTileFloats == kTileQ + NW * TD, "tile block");
+template <int FORM>
 __global__ __launch_bounds__(512) void k_scfv(const float* __restrict__ desc, const int32_t* __restrict__ count,
-                                              int kp_cap, int splits, int tiles_per_part,
+                                              int kp_cap, int img0, int splits, int tiles_per_part,
                                               const float* __restrict__ pca_mean,
                                               const float* __restrict__ pca_matrix, const float* __restrict__ means,
                                               const float* __restrict__ vars, const float* __restrict__ prep,
@@ -180,6 +208,7 @@ __global__ __launch_bounds__(512) void k_scfv(const float* __restrict__ desc, co
                                               float* __restrict__ gv_out, float* __restrict__ delta_out,
                                               int32_t* __restrict__ order_out, uint32_t* __restrict__ bits_out) {
     __shared__ float Dl[TD * DSTR];        // descriptor tile minus the PCA mean
+    __shared__ float Al[PD * DSTR];        // PCA matrix
     __shared__ float XXt[64 * TD];         // [X | X.*X] by columns: [k][descriptor]
     __shared__ float XXr[TD * XRS];        // [X | X.*X] by rows: [descriptor][k]
     __shared__ float redm[NW][TD], reds[NW][TD];
@@ -188,12 +217,14 @@ __global__ __launch_bounds__(512) void k_scfv(const float* __restrict__ desc, co
     __shared__ float skey[NC];
     __shared__ int sidx[NC];
 
-    const int img = SPLIT ? blockIdx.x / splits : blockIdx.x;
+    constexpr bool SPLIT = FORM != kWhole;
+    const int img = img0 + (SPLIT ? blockIdx.x / splits : blockIdx.x);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, h = lane >> 5, c32 = lane & 31;
     const int K = min(max(count[img], 0), kp_cap);
     // descriptor range of this workgroup: [tbeg, tend)
     const int tbeg = SPLIT ? min(K, (blockIdx.x % splits) * tiles_per_part * TD) : 0;
     const int tend = SPLIT ? min(K, tbeg + tiles_per_part * TD) : K;
+    if (FORM == kTiles && tbeg >= tend) return;   // uniform over the workgroup
     const float* D = desc + (int64_t)img * kp_cap * kDescDim;
     const float* Bp = prep + kScfvPrepB;
 
@@ -202,7 +233,13 @@ __global__ __launch_bounds__(512) void k_scfv(const float* __restrict__ desc, co
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int s = 0; s < 32; ++s) bf[t][s] = Bp[(CPW * wave + 32 * t + c32) * 64 + 2 * s + h];
+        for (int s4 = 0; s4 < 8; ++s4) {
+            const float4 v = *reinterpret_cast<const float4*>(Bp + ((2 * wave + t) * 8 + s4) * 256 + 4 * lane);
+            bf[t][4 * s4] = v.x;
+            bf[t][4 * s4 + 1] = v.y;
+            bf[t][4 * s4 + 2] = v.z;
+            bf[t][4 * s4 + 3] = v.w;
+        }
     float cc[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) cc[t] = prep[kScfvPrepC + CPW * wave + 32 * t + c32];
@@ -232,6 +269,10 @@ __global__ __launch_bounds__(512) void k_scfv(const float* __restrict__ desc, co
         }
     };
     if (tbeg < tend) fetch(tbeg);
+    // (read from global memory by every tile's projection, the matrix cost
+    // its four waves four round trips a tile)
+#pragma unroll
+    for (int e = tid; e < PD * kDescDim; e += NW * 64) Al[(e / kDescDim) * DSTR + e % kDescDim] = pca_matrix[e];
 
     for (int t0 = tbeg; t0 < tend; t0 += TD) {
         __syncthreads();   // the previous tile's readers are done
@@ -250,7 +291,7 @@ __global__ __launch_bounds__(512) void k_scfv(const float* __restrict__ desc, co
         if (wave < 4) {
             // X tile (rows 16 rt.., cols 16 ct..) = Dl . A^T over k = 0..127
             const int rt = wave >> 1, ct = wave & 1;
-            const float* arow = pca_matrix + (16 * ct + (lane & 15)) * kDescDim + (lane >> 4);
+            const float* arow = Al + (16 * ct + (lane & 15)) * DSTR + (lane >> 4);
             const float* drow = Dl + (16 * rt + (lane & 15)) * DSTR + (lane >> 4);
             f4 x = f4{};
 #pragma unroll 8
@@ -306,10 +347,22 @@ __global__ __launch_bounds__(512) void k_scfv(const float* __restrict__ desc, co
         for (int i = 0; i < 16; ++i) {
             const int d = 8 * (i >> 2) + 4 * h + (i & 3);
             const float q = __expf(redm[wave][d] - rowq[d][0]) * rowq[d][1];
-            L[0][i] *= q;
-            L[1][i] *= q;
-            s0[0] += L[0][i];
-            s0[1] += L[1][i];
+            if constexpr (FORM == kTiles) {
+                float* Q = partial + (int64_t)blockIdx.x * kScfvTileFloats + d * NC + CPW * wave + c32;
+                Q[0] = L[0][i];
+                Q[32] = L[1][i];
+                if (c32 == 0) partial[(int64_t)blockIdx.x * kScfvTileFloats + kTileQ + wave * TD + d] = q;
+            } else {
+                s0[0] = fmaf(L[0][i], q, s0[0]);
+                s0[1] = fmaf(L[1][i], q, s0[1]);
+                L[0][i] *= q;
+                L[1][i] *= q;
+            }
+        }
+        if constexpr (FORM == kTiles) {
+            float* XX = partial + (int64_t)blockIdx.x * kScfvTileFloats + kTileX;
+            for (int e = tid; e < TD * 64; e += NW * 64) XX[e] = XXr[(e >> 6) * XRS + (e & 63)];
+            return;
         }
         // S1 | S2 += Q^T [X | X.*X]: the descriptor (K) index of step i is
         // 8(i/4) + 4(l/32) + i%4 -- the rows this lane's Q registers hold
@@ -331,11 +384,11 @@ __global__ __launch_bounds__(512) void k_scfv(const float* __restrict__ desc, co
     for (int t = 0; t < 2; ++t) {
         const float v = s0[t] + __shfl_xor(s0[t], 32);
         if (h == 0) {
-            if constexpr (SPLIT) partial[(int64_t)blockIdx.x * kScfvPartialFloats + CPW * wave + 32 * t + c32] = v;
+            if constexpr (FORM == kParts) partial[(int64_t)blockIdx.x * kScfvPartialFloats + CPW * wave + 32 * t + c32] = v;
             else s0s[CPW * wave + 32 * t + c32] = v;
         }
     }
-    if constexpr (SPLIT) {
+    if constexpr (FORM == kParts) {
         float* P = partial + (int64_t)blockIdx.x * kScfvPartialFloats + NC;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
@@ -345,7 +398,7 @@ __global__ __launch_bounds__(512) void k_scfv(const float* __restrict__ desc, co
                 P[comp * PD + c32] = acc1[t][i];
                 P[NC * PD + comp * PD + c32] = acc2[t][i];
             }
-    } else {
+    } else if constexpr (FORM == kWhole) {
         __syncthreads();
         scfv_output(img, K, wave, lane, s0s, acc1, acc2, means, vars, prep, gm_out, gv_out, delta_out, order_out,
                     bits_out, skey, sidx);
@@ -400,16 +453,150 @@ __global__ __launch_bounds__(512) void k_scfv_join(const float* __restrict__ par
                 bits_out, skey, sidx);
 }
 
+// Sums and outputs of images whose tiles k_scfv<kTiles> has written: one
+// workgroup per image and 16 components, wave w < 4 taking 16 of the 64
+// columns of [X | X.*X] with 16x16x4 MFMAs, the fifth wave S0.
+//
+// One image is a chain of multiply-adds over its descriptors, in a fixed
+// order; in k_scfv the chain of 32x32x2 MFMAs, with the projection, logits
+// and softmax of each tile in between, is what one image takes (407 us for
+// 1000 descriptors, whatever else the chip does).  Here the tiles' posteriors
+// are formed independently of one another, and what is left of the chain is
+// 8 MFMAs of a quarter of that latency per 32 descriptors, over 32 workgroups.
+// The products are added in the order of k_scfv -- a 32x32x2 step adds the
+// descriptors d and d + 4 one after the other, a 16x16x4 step two such pairs
+// (checked bit for bit on the device) -- so sums, order and bits are the same.
+constexpr int kSumWaves = 5;
+constexpr int kSumAhead = 4;   // tiles whose operands are on the way while one is added
+__global__ __launch_bounds__(64 * kSumWaves) void k_scfv_sums(const float* __restrict__ tiles, int img0, int tiles_per_image,
+                                                              const int32_t* __restrict__ count, int kp_cap,
+                                                              const float* __restrict__ means,
+                                                              const float* __restrict__ vars,
+                                                              const float* __restrict__ prep, float* __restrict__ gm_out,
+                                                              float* __restrict__ gv_out, float* __restrict__ delta_out,
+                                                              uint32_t* __restrict__ bits_out) {
+    __shared__ float S[16][64 + 1], s0s[16];
+    const int rel = blockIdx.x / (NC / 16), c0 = blockIdx.x % (NC / 16) * 16, img = img0 + rel;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, kb = lane >> 4, li = lane & 15;
+    const int K = min(max(count[img], 0), kp_cap), nt = (K + TD - 1) / TD;
+    const float* T = tiles + (int64_t)rel * tiles_per_image * kScfvTileFloats;
+    if (wave < 4) {
+        // step j adds descriptors i = 2 j and 2 j + 1 of k_scfv's order, each
+        // as the pair (h = 0, h = 1): lane group kb carries i = 2 j + kb / 2,
+        // h = kb % 2
+        f4 acc = f4{};
+        float a[kSumAhead][8], b[kSumAhead][8], q[kSumAhead][8];
+        auto load = [&](int u, int t) {
+            const float* Q = T + (int64_t)min(t, nt - 1) * kScfvTileFloats;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int i = 2 * j + (kb >> 1), d = 8 * (i >> 2) + 4 * (kb & 1) + (i & 3);
+                a[u][j] = Q[d * NC + c0 + li];
+                b[u][j] = Q[kTileX + d * 64 + 16 * wave + li];
+                q[u][j] = Q[kTileQ + c0 / CPW * TD + d];
+            }
+        };
+        if (nt > 0) {
+#pragma unroll
+            for (int u = 0; u < kSumAhead; ++u) load(u, u);
+        }
+        for (int t = 0; t < nt; t += kSumAhead) {
+#pragma unroll
+            for (int u = 0; u < kSumAhead; ++u) {
+                if (t + u < nt) {   // uniform over the workgroup
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) acc = mfma16(a[u][j] * q[u][j], b[u][j], acc);
+                    load(u, t + u + kSumAhead);   // (past the end: the last tile again, not used)
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) S[4 * kb + r][16 * wave + li] = acc[r];
+    } else {
+        // lanes 0..15: the descriptors of h = 0, lanes 16..31: of h = 1
+        float v = 0.f;
+        for (int t = 0; t < nt; ++t) {
+            const float* Q = T + (int64_t)t * kScfvTileFloats;
+            float e[16], q[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int d = 8 * (i >> 2) + 4 * (kb & 1) + (i & 3);
+                e[i] = Q[d * NC + c0 + li];
+                q[i] = Q[kTileQ + c0 / CPW * TD + d];
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v = fmaf(e[i], q[i], v);
+        }
+        v += __shfl_xor(v, 16);
+        if (lane < 16) s0s[li] = v;
+    }
+    __syncthreads();
+    if (wave >= 4) return;
+    const int h = lane >> 5, k = lane & 31;
+    const float invK = K > 0 ? 1.f / (float)K : 0.f;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int c = 4 * wave + 2 * j + h;
+        scfv_entry(img, c0 + c, h, k, invK, s0s[c], S[c][k], S[c][32 + k], means, vars, prep, gm_out, gv_out, delta_out,
+                   bits_out);
+    }
+}
+
+// Component order of each image by delta, descending, ties by lower index: a
+// component's rank is the number of components before it (delta is not
+// negative, so its bits order as it does).  64 components per workgroup,
+// four lanes each counting a quarter of the others.
+__global__ __launch_bounds__(256) void k_scfv_rank(const float* __restrict__ delta, int32_t* __restrict__ order_out) {
+    __shared__ __align__(16) uint32_t key[NC];
+    const int img = blockIdx.x / (NC / 64), c = blockIdx.x % (NC / 64) * 64 + (threadIdx.x >> 2), q0 = (threadIdx.x & 3) * 4;
+    const uint32_t* bits = reinterpret_cast<const uint32_t*>(delta) + (int64_t)img * NC;
+    for (int i = threadIdx.x; i < NC; i += 256) key[i] = bits[i] & 0x7fffffffu;
+    __syncthreads();
+    const uint32_t mine = key[c];
+    int rank = 0;
+#pragma unroll 4
+    for (int j = q0; j < NC; j += 16) {
+        const uint4 k = *reinterpret_cast<const uint4*>(&key[j]);
+        // before c: greater, or equal with a lower index
+        rank += k.x >= mine + (j >= c);
+        rank += k.y >= mine + (j + 1 >= c);
+        rank += k.z >= mine + (j + 2 >= c);
+        rank += k.w >= mine + (j + 3 >= c);
+    }
+    rank += (int)lane_xor<1>((uint32_t)rank);
+    rank += (int)lane_xor<2>((uint32_t)rank);
+    if ((threadIdx.x & 3) == 0) order_out[(int64_t)img * NC + rank] = c;
+}
+
 }  // namespace
+
+int scfv_tile_blocks(int n_images, int kp_cap) {
+    const int64_t per = (kp_cap + TD - 1) / TD;
+    if (n_images > kScfvTilesMaxImages) return 0;
+    return (int)std::max(per, std::min<int64_t>(per * n_images, kScfvTilesMax) / per * per);
+}
 
 hipError_t launch_scfv(const float* desc, const int32_t* count, int n_images, int kp_cap, const float* pca_mean,
                        const float* pca_matrix, const float* weights, const float* means, const float* vars,
-                       float* prep, float* gm, float* gv, float* delta, int32_t* order, uint32_t* bits,
-                       hipStream_t s) {
+                       float* prep, float* tiles, int tile_blocks, float* gm, float* gv, float* delta, int32_t* order,
+                       uint32_t* bits, hipStream_t s) {
     if (n_images <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_scfv_prep, dim3(NC / 8), dim3(256), 0, s, weights, means, vars, prep);
-    hipLaunchKernelGGL(k_scfv<false>, dim3(n_images), dim3(NW * 64), 0, s, desc, count, kp_cap, 1, 0, pca_mean,
-                       pca_matrix, means, vars, prep, nullptr, gm, gv, delta, order, bits);
+    if (tile_blocks <= 0) {
+        hipLaunchKernelGGL(k_scfv<kWhole>, dim3(n_images), dim3(NW * 64), 0, s, desc, count, kp_cap, 0, 1, 0, pca_mean,
+                           pca_matrix, means, vars, prep, nullptr, gm, gv, delta, order, bits);
+        return hipGetLastError();
+    }
+    // as many images at a time as the tile blocks hold
+    const int per = (kp_cap + TD - 1) / TD, round = tile_blocks / per;
+    for (int i0 = 0; i0 < n_images; i0 += round) {
+        const int m = std::min(round, n_images - i0);
+        hipLaunchKernelGGL(k_scfv<kTiles>, dim3(m * per), dim3(NW * 64), 0, s, desc, count, kp_cap, i0, per, 1, pca_mean,
+                           pca_matrix, means, vars, prep, tiles, nullptr, nullptr, nullptr, nullptr, nullptr);
+        hipLaunchKernelGGL(k_scfv_sums, dim3(m * (NC / 16)), dim3(64 * kSumWaves), 0, s, tiles, i0, per, count, kp_cap,
+                           means, vars, prep, gm, gv, delta, bits);
+    }
+    hipLaunchKernelGGL(k_scfv_rank, dim3(n_images * (NC / 64)), dim3(256), 0, s, delta, order);
     return hipGetLastError();
 }
 
@@ -456,13 +643,13 @@ hipError_t launch_scfv_static(float* scr, int splits, const float* desc, const i
     float* prep = scr;
     hipLaunchKernelGGL(k_scfv_prep, dim3(NC / 8), dim3(256), 0, s, weights, means, vars, prep);
     if (splits <= 1) {
-        hipLaunchKernelGGL(k_scfv<false>, dim3(n_images), dim3(NW * 64), 0, s, desc, count, kp_cap, 1, 0, pca_mean,
+        hipLaunchKernelGGL(k_scfv<kWhole>, dim3(n_images), dim3(NW * 64), 0, s, desc, count, kp_cap, 0, 1, 0, pca_mean,
                            pca_matrix, means, vars, prep, nullptr, gm, gv, delta, order, bits);
     } else {
         float* partial = scr + kScfvStaticPrepFloats;
         const int tiles = (kp_cap + TD - 1) / TD;
         const int per = (tiles + splits - 1) / splits;
-        hipLaunchKernelGGL(k_scfv<true>, dim3(n_images * splits), dim3(NW * 64), 0, s, desc, count, kp_cap, splits,
+        hipLaunchKernelGGL(k_scfv<kParts>, dim3(n_images * splits), dim3(NW * 64), 0, s, desc, count, kp_cap, 0, splits,
                            per, pca_mean, pca_matrix, means, vars, prep, partial, nullptr, nullptr, nullptr, nullptr,
                            nullptr);
         hipLaunchKernelGGL(k_scfv_reduce, dim3(n_images * (kScfvPartialFloats / 512)), dim3(256), 0, s, partial,
