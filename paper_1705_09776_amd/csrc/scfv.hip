@@ -209,10 +209,10 @@ __global__ __launch_bounds__(512) void k_scfv(const float* __restrict__ desc, co
                                               int32_t* __restrict__ order_out, uint32_t* __restrict__ bits_out) {
     __shared__ float Dl[TD * DSTR];        // descriptor tile minus the PCA mean
     __shared__ float Al[PD * DSTR];        // PCA matrix
-    __shared__ float XXt[64 * TD];         // [X | X.*X] by columns: [k][descriptor]
-    __shared__ float XXr[TD * XRS];        // [X | X.*X] by rows: [descriptor][k]
+    __shared__ float XXt[2][64 * TD];      // [X | X.*X] by columns: [k][descriptor], this tile's and the next's
+    __shared__ float XXr[2][TD * XRS];     // [X | X.*X] by rows: [descriptor][k]
     __shared__ float redm[NW][TD], reds[NW][TD];
-    __shared__ float rowq[TD][2];          // per descriptor: global max, 1/sum (0 for padding rows)
+    __shared__ __align__(16) float qs[NW][TD];   // per wave and descriptor: the factor of its posteriors
     __shared__ float s0s[NC];
     __shared__ float skey[NC];
     __shared__ int sidx[NC];
@@ -274,8 +274,8 @@ __global__ __launch_bounds__(512) void k_scfv(const float* __restrict__ desc, co
 #pragma unroll
     for (int e = tid; e < PD * kDescDim; e += NW * 64) Al[(e / kDescDim) * DSTR + e % kDescDim] = pca_matrix[e];
 
-    for (int t0 = tbeg; t0 < tend; t0 += TD) {
-        __syncthreads();   // the previous tile's readers are done
+    // descriptor tile minus the PCA mean, from the registers that hold it
+    auto stage = [&](int t0) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int r = r4 + 16 * j;
@@ -286,32 +286,48 @@ __global__ __launch_bounds__(512) void k_scfv(const float* __restrict__ desc, co
             d[2] = live ? pre[j].z - mq.z : 0.f;
             d[3] = live ? pre[j].w - mq.w : 0.f;
         }
-        if (t0 + TD < tend) fetch(t0 + TD);
-        __syncthreads();
-        if (wave < 4) {
-            // X tile (rows 16 rt.., cols 16 ct..) = Dl . A^T over k = 0..127
-            const int rt = wave >> 1, ct = wave & 1;
-            const float* arow = Al + (16 * ct + (lane & 15)) * DSTR + (lane >> 4);
-            const float* drow = Dl + (16 * rt + (lane & 15)) * DSTR + (lane >> 4);
-            f4 x = f4{};
+    };
+    // X tile (rows 16 rt.., cols 16 ct..) = Dl . A^T over k = 0..127, by the
+    // first four waves
+    auto project = [&](int p) {
+        const int rt = wave >> 1, ct = wave & 1;
+        const float* arow = Al + (16 * ct + (lane & 15)) * DSTR + (lane >> 4);
+        const float* drow = Dl + (16 * rt + (lane & 15)) * DSTR + (lane >> 4);
+        f4 x = f4{};
 #pragma unroll 8
-            for (int s = 0; s < 32; ++s) x = mfma16(drow[4 * s], arow[4 * s], x);
+        for (int s = 0; s < 32; ++s) x = mfma16(drow[4 * s], arow[4 * s], x);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = 16 * rt + 4 * (lane >> 4) + r, col = 16 * ct + (lane & 15);
-                const float v = x[r], v2 = v * v;
-                XXt[col * TD + row] = v;
-                XXt[(32 + col) * TD + row] = v2;
-                XXr[row * XRS + col] = v;
-                XXr[row * XRS + 32 + col] = v2;
-            }
+        for (int r = 0; r < 4; ++r) {
+            const int row = 16 * rt + 4 * (lane >> 4) + r, col = 16 * ct + (lane & 15);
+            const float v = x[r], v2 = v * v;
+            XXt[p][col * TD + row] = v;
+            XXt[p][(32 + col) * TD + row] = v2;
+            XXr[p][row * XRS + col] = v;
+            XXr[p][row * XRS + 32 + col] = v2;
         }
-        __syncthreads();
+    };
+    if (tbeg < tend) {
+        stage(tbeg);
+        if (tbeg + TD < tend) fetch(tbeg + TD);
+    }
+    __syncthreads();
+    if (wave < 4 && tbeg < tend) project(0);
+    __syncthreads();
+
+    // Two barriers a tile: the next tile is staged beside this one's logits
+    // and projected beside its sums (each SIMD holds one of the four waves
+    // that do so), and every wave combines the softmax for itself.
+    for (int t0 = tbeg, p = 0; t0 < tend; t0 += TD, p ^= 1) {
+        const bool more = t0 + TD < tend;
+        if (more) {
+            stage(t0 + TD);
+            if (t0 + 2 * TD < tend) fetch(t0 + 2 * TD);
+        }
         // logits of this wave's 64 components for the tile's 32 descriptors
         f16v L[2] = {f16v{}, f16v{}};
 #pragma unroll
         for (int s = 0; s < 32; ++s) {
-            const float a = XXt[(2 * s + h) * TD + c32];
+            const float a = XXt[p][(2 * s + h) * TD + c32];
             L[0] = mfma32(a, bf[0][s], L[0]);
             L[1] = mfma32(a, bf[1][s], L[1]);
         }
@@ -332,36 +348,50 @@ __global__ __launch_bounds__(512) void k_scfv(const float* __restrict__ desc, co
             }
         }
         __syncthreads();
-        if (tid < TD) {
-            float M = redm[0][tid];
+        if (more && wave < 4) project(p ^ 1);
+        {
+            // lane c32 for descriptor c32: its maximum M and sum S over the
+            // waves, and this wave's factor exp(m - M) / S (0 for padding rows)
+            float mw[NW], M = redm[0][c32];
+            mw[0] = M;
 #pragma unroll
-            for (int w = 1; w < NW; ++w) M = fmaxf(M, redm[w][tid]);
+            for (int w = 1; w < NW; ++w) {
+                mw[w] = redm[w][c32];
+                M = fmaxf(M, mw[w]);
+            }
             float S = 0.f;
 #pragma unroll
-            for (int w = 0; w < NW; ++w) S += reds[w][tid] * __expf(redm[w][tid] - M);
-            rowq[tid][0] = M;
-            rowq[tid][1] = (t0 + tid < tend) ? 1.f / S : 0.f;
+            for (int w = 0; w < NW; ++w) S = fmaf(reds[w][c32], __expf(mw[w] - M), S);
+            const float r = t0 + c32 < tend ? 1.f / S : 0.f;
+            qs[wave][c32] = __expf(redm[wave][c32] - M) * r;   // (both half-waves write the same)
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
         }
-        __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int d = 8 * (i >> 2) + 4 * h + (i & 3);
-            const float q = __expf(redm[wave][d] - rowq[d][0]) * rowq[d][1];
-            if constexpr (FORM == kTiles) {
-                float* Q = partial + (int64_t)blockIdx.x * kScfvTileFloats + d * NC + CPW * wave + c32;
-                Q[0] = L[0][i];
-                Q[32] = L[1][i];
-                if (c32 == 0) partial[(int64_t)blockIdx.x * kScfvTileFloats + kTileQ + wave * TD + d] = q;
-            } else {
-                s0[0] = fmaf(L[0][i], q, s0[0]);
-                s0[1] = fmaf(L[1][i], q, s0[1]);
-                L[0][i] *= q;
-                L[1][i] *= q;
+        for (int i4 = 0; i4 < 4; ++i4) {
+            const float4 q4v = *reinterpret_cast<const float4*>(&qs[wave][8 * i4 + 4 * h]);
+            const float qv[4] = {q4v.x, q4v.y, q4v.z, q4v.w};
+#pragma unroll
+            for (int ii = 0; ii < 4; ++ii) {
+                const int i = 4 * i4 + ii;
+                const float q = qv[ii];
+                if constexpr (FORM == kTiles) {
+                    const int d = 8 * (i >> 2) + 4 * h + (i & 3);
+                    float* Q = partial + (int64_t)blockIdx.x * kScfvTileFloats + d * NC + CPW * wave + c32;
+                    Q[0] = L[0][i];
+                    Q[32] = L[1][i];
+                    if (c32 == 0) partial[(int64_t)blockIdx.x * kScfvTileFloats + kTileQ + wave * TD + d] = q;
+                } else {
+                    s0[0] = fmaf(L[0][i], q, s0[0]);
+                    s0[1] = fmaf(L[1][i], q, s0[1]);
+                    L[0][i] *= q;
+                    L[1][i] *= q;
+                }
             }
         }
         if constexpr (FORM == kTiles) {
             float* XX = partial + (int64_t)blockIdx.x * kScfvTileFloats + kTileX;
-            for (int e = tid; e < TD * 64; e += NW * 64) XX[e] = XXr[(e >> 6) * XRS + (e & 63)];
+            for (int e = tid; e < TD * 64; e += NW * 64) XX[e] = XXr[p][(e >> 6) * XRS + (e & 63)];
             return;
         }
         // S1 | S2 += Q^T [X | X.*X]: the descriptor (K) index of step i is
@@ -369,13 +399,14 @@ __global__ __launch_bounds__(512) void k_scfv(const float* __restrict__ desc, co
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const int d = 8 * (i >> 2) + 4 * h + (i & 3);
-            const float b1 = XXr[d * XRS + c32], b2 = XXr[d * XRS + 32 + c32];
+            const float b1 = XXr[p][d * XRS + c32], b2 = XXr[p][d * XRS + 32 + c32];
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
                 acc1[t] = mfma32(L[t][i], b1, acc1[t]);
                 acc2[t] = mfma32(L[t][i], b2, acc2[t]);
             }
         }
+        __syncthreads();
     }
 
     // S0 per component (this lane's logit column), then either the sums of
