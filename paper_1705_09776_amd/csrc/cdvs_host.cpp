@@ -75,7 +75,8 @@ struct cdvs_ctx {
     std::vector<int32_t> cand_cap;
     int64_t* d_cand_off = nullptr;
     int32_t* d_cand_capv = nullptr;
-    cdvs_keypoint* d_sel = nullptr;            // [image][kCandCap] strongest candidates (only when needed)
+    float* d_absp = nullptr;                   // |p| of each candidate (only when needed)
+    uint32_t* d_sel = nullptr;                 // [image][kCandCap] strongest candidates' indices (only when needed)
     int32_t* d_cand_cnt = nullptr;             // n per-image counts, then kXcds detection work counters
     cdvs_keypoint* d_ori = nullptr;
     int32_t* d_ori_cnt = nullptr;
@@ -288,6 +289,7 @@ void cdvs_ctx_destroy(cdvs_ctx* ctx) {
     (void)hipFree(ctx->d_cand_off);
     (void)hipFree(ctx->d_cand_capv);
     (void)hipFree(ctx->d_sel);
+    (void)hipFree(ctx->d_absp);
     (void)hipFree(ctx->d_cand_cnt);
     (void)hipFree(ctx->d_ori);
     (void)hipFree(ctx->d_ori_cnt);
@@ -561,7 +563,10 @@ cdvs_status cdvs_ctx_create(const cdvs_params* params, const cdvs_image_desc* im
         ALLOC(c->d_cand, sizeof(cdvs_keypoint) * total);
         ALLOC(c->d_cand_off, sizeof(int64_t) * n);
         ALLOC(c->d_cand_capv, sizeof(int32_t) * n);
-        if (cmax > kCandCap) ALLOC(c->d_sel, sizeof(cdvs_keypoint) * n * kCandCap);
+        if (cmax > kCandCap) {
+            ALLOC(c->d_sel, sizeof(uint32_t) * n * kCandCap);
+            ALLOC(c->d_absp, sizeof(float) * total);
+        }
     }
     ALLOC(c->d_cand_cnt, sizeof(int32_t) * (n + kXcds));
     ALLOC(c->d_ori, sizeof(cdvs_keypoint) * n * kp_capacity * kMaxOri);
@@ -684,6 +689,8 @@ cdvs_status cdvs_pyramid_bmlog(cdvs_ctx* ctx, const uint8_t* d_images, float* d_
     return CDVS_OK;
 }
 
+static DetOut det_out(cdvs_ctx* ctx) { return DetOut{ctx->d_cand, ctx->d_cand_cnt, ctx->d_absp, ctx->d_flags}; }
+
 cdvs_status cdvs_alp_detect(cdvs_ctx* ctx, const float* d_pyr, const uint8_t* d_mask, cdvs_keypoint* d_kp,
                             int32_t* d_count, void* stream) {
     if (!ctx) return CDVS_ERR_STATE;
@@ -705,16 +712,13 @@ cdvs_status cdvs_alp_detect(cdvs_ctx* ctx, const float* d_pyr, const uint8_t* d_
         // not rely on the order in which candidates arrive
         Bracket b(ctx, CDVS_KERNEL_DETECT, s);
         HIP_OR_FAIL(ctx, launch_detect_strips(d_pyr, ctx->d_strips, (int)ctx->strips.size(), ctx->detect_variant,
-                                              ctx->detect_grid, ctx->det, gate, ctx->d_cand_cnt + ctx->n,
-                                              ctx->d_cand, ctx->d_cand_cnt, ctx->d_flags, s));
+                                              ctx->detect_grid, ctx->det, gate, ctx->d_cand_cnt + ctx->n, det_out(ctx), s));
     }
     {
         Bracket b(ctx, CDVS_KERNEL_FINALIZE, s);
-        HIP_OR_FAIL(ctx, launch_select(ctx->d_cand, ctx->d_cand_cnt, ctx->d_cand_off, ctx->d_cand_capv, ctx->n,
-                                       ctx->d_sel, s));
-        HIP_OR_FAIL(ctx, launch_finalize(ctx->d_cand, ctx->d_cand_cnt, ctx->d_cand_off, ctx->d_cand_capv, ctx->d_sel,
-                                         ctx->n, ctx->dedup_ratio, ctx->params.topk, ctx->kp_cap, d_kp, d_count,
-                                         ctx->d_flags, s));
+        HIP_OR_FAIL(ctx, launch_finalize(ctx->d_cand, ctx->d_absp, ctx->d_cand_cnt, ctx->d_cand_off, ctx->d_cand_capv,
+                                         ctx->d_sel, ctx->d_wh, ctx->n, ctx->dedup_ratio, ctx->params.topk, ctx->kp_cap, d_kp,
+                                         d_count, ctx->d_flags, s));
     }
     return CDVS_OK;
 }
@@ -1170,8 +1174,8 @@ cdvs_status cdvs_autotune(cdvs_ctx* ctx, const uint8_t* d_images, float* d_pyr, 
                 const GateParams gate{nullptr, nullptr, nullptr, 1.f};
                 HIP_OR_FAIL(ctx, launch_clear(ctx->d_cand_cnt, ctx->n + kXcds, s));
                 HIP_OR_FAIL(ctx, launch_detect_strips(d_pyr, ctx->d_strips, (int)ctx->strips.size(), var,
-                                                      ctx->detect_grid, ctx->det, gate, ctx->d_cand_cnt + ctx->n,
-                                                      ctx->d_cand, ctx->d_cand_cnt, ctx->d_flags, s));
+                                                      ctx->detect_grid, ctx->det, gate, ctx->d_cand_cnt + ctx->n, det_out(ctx),
+                                                      s));
                 return CDVS_OK;
             },
             dus);

@@ -186,6 +186,16 @@ struct GateParams {
     float fmax;              // fraction of active cells above which detection is dense
 };
 
+// Where the detection puts what it finds: candidate records and their number
+// per image, and (unless null) |p| of each once more, contiguous, for the
+// selection in images with many.
+struct DetOut {
+    cdvs_keypoint* cand;
+    int32_t* cnt;
+    float* absp;
+    int32_t* flags;
+};
+
 // Kernel tile shapes (width x height).  Shapes 0..3 are the scale-plane
 // kernel's variants (autotuned); shape 4 is the pre-blur's own, 128 x 32
 // (measured against 64 x 32, 80 x 32, 160 x 16 and 160 x 32: its column
@@ -213,13 +223,14 @@ constexpr int kDetStripW = 60, kDetStripH = 48;
 // from per-XCD counters work[0..7], which must be zero at launch.
 constexpr int kDetectPerStrip = 0, kDetectPersistent = 1, kDetectVariants = 2;
 hipError_t launch_detect_strips(const float* pyr, const DetTile* strips, int nstrips, int variant, int grid,
-                                const DetParams& dp, const GateParams& gate, int32_t* work, cdvs_keypoint* cand,
-                                int32_t* cand_cnt, int32_t* flags, hipStream_t stream);
-hipError_t launch_select(const cdvs_keypoint* cand, const int32_t* cand_cnt, const int64_t* cand_off,
-                         const int32_t* cand_capv, int n_images, cdvs_keypoint* sel, hipStream_t stream);
-hipError_t launch_finalize(const cdvs_keypoint* cand, const int32_t* cand_cnt, const int64_t* cand_off,
-                           const int32_t* cand_capv, const cdvs_keypoint* sel, int n_images, float dedup_ratio,
-                           int topk, int kp_cap, cdvs_keypoint* kp, int32_t* count, int32_t* flags,
+                                const DetParams& dp, const GateParams& gate, int32_t* work, const DetOut& out,
+                                hipStream_t stream);
+// absp (|p| per candidate) and lists (kCandCap indices per image) are used by
+// images with more candidates than kCandCap (both may be null when no image's
+// capacity exceeds it); wh: per image width and height.
+hipError_t launch_finalize(const cdvs_keypoint* cand, const float* absp, const int32_t* cand_cnt, const int64_t* cand_off,
+                           const int32_t* cand_capv, uint32_t* lists, const int32_t* wh, int n_images,
+                           float dedup_ratio, int topk, int kp_cap, cdvs_keypoint* kp, int32_t* count, int32_t* flags,
                            hipStream_t stream);
 hipError_t launch_orient(const float* pyr, const OctGeom* geom, const cdvs_keypoint* kp, const int32_t* count,
                          int n_images, const OriParams& op, cdvs_keypoint* ori, int32_t* ori_cnt,

@@ -10,11 +10,11 @@
 //   candidate list with one ballot and one atomic per pass.  With a cell
 //   mask (the learned gate) only the centres of active cells are examined
 //   and strips without any are skipped before loading anything.
-// k_select (images with more candidates than k_finalize holds): their
-//   strongest kCandCap by |p|.
-// k_finalize: one workgroup per image.  Stage C (cross-octave duplicates)
-//   over adjacent-octave segments, then a bitonic sort in LDS on the 64-bit
-//   key (|p| desc, octave, iy, ix) and the top-k copy-out.
+// k_finalize: one workgroup per image.  (Images with more candidates than it
+//   holds: their strongest kCandCap by |p|.)  Stage C (cross-octave
+//   duplicates) over cells of the adjacent octaves, then a bitonic sort in LDS
+//   on the 64-bit key (|p| desc, octave, iy, ix) of what can be among the top
+//   k, and the copy-out.
 #include <algorithm>
 
 #include "cdvs_internal.h"
@@ -130,20 +130,18 @@ __device__ __forceinline__ bool refine_v(const float (&v)[9], float s, float p, 
 
 // Wave-level compaction of survivors into the image's candidate list: one
 // ballot and one atomic per wave.  Every lane of the wave must call it.
-__device__ __forceinline__ void emit(bool keep, const Cand& c, int gx, int gy, const DetTile& job, const DetParams& dp,
-                                     cdvs_keypoint* __restrict__ cand, int32_t* __restrict__ cand_cnt,
-                                     int32_t* __restrict__ flags) {
+__device__ __forceinline__ void emit(bool keep, const Cand& c, int gx, int gy, const DetTile& job, const DetOut& out) {
     const int lane = threadIdx.x & 63;
     const uint64_t m = __ballot(keep);
     if (!m) return;
     const int leader = __ffsll((unsigned long long)m) - 1;
     int base = 0;
-    if (lane == leader) base = atomicAdd(&cand_cnt[job.image], __popcll(m));
+    if (lane == leader) base = atomicAdd(&out.cnt[job.image], __popcll(m));
     base = __shfl(base, leader);
     if (!keep) return;
     const int slot = base + __popcll(m & ((1ull << lane) - 1ull));
     if (slot >= job.cand_cap) {
-        atomicOr(flags, kFlagCandOverflow);
+        atomicOr(out.flags, kFlagCandOverflow);
         return;
     }
     const float scale = (float)(1 << job.octave);
@@ -160,7 +158,9 @@ __device__ __forceinline__ void emit(bool keep, const Cand& c, int gx, int gy, c
     r.octave = job.octave;
     r.ix = gx;
     r.iy = gy;
-    cand[(int64_t)job.cand_blk * kCandBlock + slot] = r;
+    const int64_t at = (int64_t)job.cand_blk * kCandBlock + slot;
+    out.cand[at] = r;
+    if (out.absp) out.absp[at] = fabsf(c.pr);
 }
 
 // ---------------------------------------------------------------------------
@@ -242,8 +242,7 @@ __device__ __forceinline__ float4 strip_alpha(const StripRow& u, const StripRow&
 // appends the survivors to the image's candidates.  Every lane of the wave
 // calls it.
 __device__ __forceinline__ void strip_flush(float (*q)[kQCap], int base, int n, const DetTile& job,
-                                            const DetParams& dp, cdvs_keypoint* __restrict__ cand,
-                                            int32_t* __restrict__ cand_cnt, int32_t* __restrict__ flags) {
+                                            const DetParams& dp, const DetOut& out) {
     const int lane = threadIdx.x & 63;
     Cand c{};
     bool keep = false;
@@ -261,14 +260,13 @@ __device__ __forceinline__ void strip_flush(float (*q)[kQCap], int base, int n, 
         gy = xy >> 16;
         keep = refine_v(v, q[8][e], q[9][e], q[10][e], dp, c);
     }
-    emit(keep, c, gx, gy, job, dp, cand, cand_cnt, flags);
+    emit(keep, c, gx, gy, job, out);
 }
 
 // Refines everything queued (in passes of 64) and empties the queue.
 __device__ __forceinline__ void strip_drain(float (*q)[kQCap], int& qn, const DetTile& job, const DetParams& dp,
-                                            cdvs_keypoint* __restrict__ cand, int32_t* __restrict__ cand_cnt,
-                                            int32_t* __restrict__ flags) {
-    for (int base = 0; base < qn; base += 64) strip_flush(q, base, min(64, qn - base), job, dp, cand, cand_cnt, flags);
+                                            const DetOut& out) {
+    for (int base = 0; base < qn; base += 64) strip_flush(q, base, min(64, qn - base), job, dp, out);
     qn = 0;
 }
 
@@ -276,8 +274,7 @@ __device__ __forceinline__ void strip_drain(float (*q)[kQCap], int& qn, const De
 // strict extrema are queued (qn: the wave's queue length, uniform).
 __device__ __forceinline__ void strip_centres(const float4& aU, const float4& aM, const float4& aD, bool col_ok, int gx,
                                               int y, float (*q)[kQCap], int& qn, const DetTile& job,
-                                              const DetParams& dp, cdvs_keypoint* __restrict__ cand,
-                                              int32_t* __restrict__ cand_cnt, int32_t* __restrict__ flags) {
+                                              const DetParams& dp, const DetOut& out) {
     float s = 0.f, p = 0.f, pss = 0.f;
     const bool found = alp_extremum(aM, dp.lo, dp.hi, s, p, pss);
     const bool pass = col_ok & found & (fabsf(p) >= dp.contrast);   // no branch: every lane evaluates
@@ -313,7 +310,7 @@ __device__ __forceinline__ void strip_centres(const float4& aU, const float4& aM
         q[11][i] = __int_as_float(gx | (y << 16));
     }
     qn += __popcll(m);
-    if (qn > kQFlush) strip_drain(q, qn, job, dp, cand, cand_cnt, flags);
+    if (qn > kQFlush) strip_drain(q, qn, job, dp, out);
 }
 
 // GATED: an octave-o centre (x, y) is examined only when bit o of the mask
@@ -322,9 +319,7 @@ __device__ __forceinline__ void strip_centres(const float4& aU, const float4& aM
 // (then the octave is examined densely).
 template <bool GATED>
 __device__ __forceinline__ void detect_strip(const float* __restrict__ pyr, const DetTile& job, const DetParams& dp,
-                                             const GateParams& gate, float (*q)[kQCap],
-                                             cdvs_keypoint* __restrict__ cand, int32_t* __restrict__ cand_cnt,
-                                             int32_t* __restrict__ flags) {
+                                             const GateParams& gate, float (*q)[kQCap], const DetOut& out) {
     static_assert(kStripH <= 64, "one activity bit per strip row");
     const int lane = threadIdx.x & 63;
     const int x0 = job.tx0, y0 = job.ty0;
@@ -376,10 +371,10 @@ __device__ __forceinline__ void detect_strip(const float* __restrict__ pyr, cons
             load_row(col, job, min(y + r + kRing, last), g[(r + 2) % kRing]);
             if (y + r < yend)   // uniform over the wave
                 strip_centres(a[r % 3], a[(r + 1) % 3], a[(r + 2) % 3], col_ok && ((rows_on >> (y + r - y0)) & 1ull),
-                              gx, y + r, q, qn, job, dp, cand, cand_cnt, flags);
+                              gx, y + r, q, qn, job, dp, out);
         }
     }
-    strip_drain(q, qn, job, dp, cand, cand_cnt, flags);
+    strip_drain(q, qn, job, dp, out);
 }
 
 // Requests one strip index from this XCD's work counter; the value arrives
@@ -409,15 +404,14 @@ __device__ __forceinline__ int fetch_strip(int32_t* __restrict__ ctr) {
 template <bool GATED, bool PERSISTENT>
 __global__ __launch_bounds__(256) void k_detect_strip(const float* __restrict__ pyr, const DetTile* __restrict__ strips,
                                                       int nstrips, DetParams dp, GateParams gate,
-                                                      int32_t* __restrict__ work, cdvs_keypoint* __restrict__ cand,
-                                                      int32_t* __restrict__ cand_cnt, int32_t* __restrict__ flags) {
+                                                      int32_t* __restrict__ work, DetOut out) {
     __shared__ float queue[4][kQFields][kQCap];
     const int wave = threadIdx.x >> 6;
     if constexpr (!PERSISTENT) {
         const int sidx = __builtin_amdgcn_readfirstlane(xcd_remap(blockIdx.x, gridDim.x) * 4 + wave);
         if (sidx >= nstrips) return;   // uniform over the wave; there are no barriers
         const DetTile job = strips[sidx];
-        detect_strip<GATED>(pyr, job, dp, gate, queue[wave], cand, cand_cnt, flags);
+        detect_strip<GATED>(pyr, job, dp, gate, queue[wave], out);
     } else {
         const int x = blockIdx.x % kXcds;
         const int per = nstrips / kXcds, rem = nstrips % kXcds;
@@ -429,7 +423,7 @@ __global__ __launch_bounds__(256) void k_detect_strip(const float* __restrict__ 
             if (t >= cnt) break;   // uniform over the wave; there are no barriers
             pending = fetch_strip(ctr);
             const DetTile job = strips[base + t];
-            detect_strip<GATED>(pyr, job, dp, gate, queue[wave], cand, cand_cnt, flags);
+            detect_strip<GATED>(pyr, job, dp, gate, queue[wave], out);
         }
     }
 }
@@ -441,63 +435,6 @@ __global__ void k_clear(int32_t* p, int n) {
 
 constexpr int FIN_THREADS = 1024;
 constexpr int FIN_PER = kCandCap / FIN_THREADS;  // candidates per thread
-
-// Top-kCandCap selection by |p| for images with more candidates than the
-// finalisation holds (one workgroup per image; the others return at once).
-// The kCandCap-th largest |p| is found by a three-round radix select on the
-// float bits of |p| (11, 11 and 10 bits; non-negative floats order like
-// their bits), then every candidate above it and enough of those equal to it
-// are copied out (in no particular order: the finalisation sorts).
-__global__ __launch_bounds__(FIN_THREADS) void k_select(const cdvs_keypoint* __restrict__ cand,
-                                                        const int32_t* __restrict__ cand_cnt,
-                                                        const int64_t* __restrict__ cand_off,
-                                                        const int32_t* __restrict__ cand_capv,
-                                                        cdvs_keypoint* __restrict__ sel) {
-    __shared__ int hist[2048];
-    __shared__ uint32_t prefix_s, need_s;
-    __shared__ int n_out, n_tie;
-    const int img = blockIdx.x;
-    const int n = min(cand_cnt[img], cand_capv[img]);
-    if (n <= kCandCap) return;   // uniform over the workgroup
-    const cdvs_keypoint* c = cand + cand_off[img];
-    cdvs_keypoint* out = sel + (int64_t)img * kCandCap;
-    if (threadIdx.x == 0) {
-        prefix_s = 0u;
-        need_s = kCandCap;
-        n_out = 0;
-        n_tie = 0;
-    }
-    uint32_t mask = 0u;   // bits of the threshold fixed so far
-    const int shifts[3] = {21, 10, 0}, widths[3] = {11, 11, 10};
-    for (int round = 0; round < 3; ++round) {
-        const int sh = shifts[round], nb = 1 << widths[round];
-        for (int b = threadIdx.x; b < nb; b += blockDim.x) hist[b] = 0;
-        __syncthreads();
-        const uint32_t prefix = prefix_s;
-        for (int i = threadIdx.x; i < n; i += blockDim.x) {
-            const uint32_t key = __float_as_uint(fabsf(c[i].p));
-            if ((key & mask) == prefix) atomicAdd(&hist[(key >> sh) & (nb - 1)], 1);
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            // walk the bins from the top until `need` keys are covered
-            uint32_t need = need_s;
-            int b = nb - 1;
-            for (; b > 0 && (uint32_t)hist[b] < need; --b) need -= (uint32_t)hist[b];
-            prefix_s = prefix | ((uint32_t)b << sh);
-            need_s = need;   // keys still needed from bin b (the threshold's bin)
-        }
-        mask |= (uint32_t)(nb - 1) << sh;
-        __syncthreads();
-    }
-    const uint32_t thr = prefix_s, ties = need_s;   // keep every key > thr and `ties` keys == thr
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        const uint32_t key = __float_as_uint(fabsf(c[i].p));
-        bool take = key > thr;
-        if (key == thr) take = atomicAdd(&n_tie, 1) < (int)ties;
-        if (take) out[atomicAdd(&n_out, 1)] = c[i];
-    }
-}
 
 // One compare-exchange of a bitonic stage of block size `size` at distance
 // S < 64 for the (key, payload) of element i held by this lane, whose
@@ -590,145 +527,425 @@ __device__ void bitonic_sort(unsigned long long* key, unsigned short* idx, int n
     }
 }
 
-// Stage C + canonical sort + top-k for one image per workgroup.  The
-// candidates are first sorted by (octave, y) so that each one meets only the
-// adjacent-octave candidates in a band of y around it (binary search, then a
-// short scan) instead of every candidate of those octaves; the decisions are
-// the same, as only pairs farther apart in y than the distance limit are
-// skipped.  Then the survivors are sorted by the canonical key.
+// Exclusive prefix sums of v[0 .. 4 * FIN_THREADS) in place, and the total,
+// by the whole workgroup.
+__device__ __forceinline__ int scan4(int* v, int* wsum) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int4 q = reinterpret_cast<int4*>(v)[tid];
+    const int sum = q.x + q.y + q.z + q.w;
+    int incl = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int u = __shfl_up(incl, off);
+        if (lane >= off) incl += u;
+    }
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    int before = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < FIN_THREADS / 64; ++w) {
+        const int u = wsum[w];
+        before += w < wave ? u : 0;
+        total += u;
+    }
+    const int e = before + incl - sum;
+    reinterpret_cast<int4*>(v)[tid] = make_int4(e, e + q.x, e + q.x + q.y, e + q.x + q.y + q.z);
+    __syncthreads();
+    return total;
+}
+
+// Where the count of keys, taken from the highest bin of hist[0 .. 4096)
+// down, reaches `need` (1 <= need <= the keys in hist): that bin, and how
+// many of its keys the count still needs.
+__device__ __forceinline__ void nth_from_top(int* hist, int* wsum, int need, int* bin, int* rest) {
+    const int tid = threadIdx.x;
+    const int4 q = reinterpret_cast<int4*>(hist)[tid];
+    const int total = scan4(hist, wsum);
+    const int4 e = reinterpret_cast<int4*>(hist)[tid];
+    const int cnt[4] = {q.x, q.y, q.z, q.w}, ex[4] = {e.x, e.y, e.z, e.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int above = total - ex[k] - cnt[k];   // keys in higher bins
+        if (above < need && above + cnt[k] >= need) {   // one bin of all
+            *bin = 4 * tid + k;
+            *rest = need - above;
+        }
+    }
+    __syncthreads();
+}
+
+// Minimum and maximum over the wave of unsigned values, in every lane.
+__device__ __forceinline__ void wave_min_max(uint32_t& lo, uint32_t& hi) {
+#define CDVS_STEP(S)                 \
+    lo = min(lo, lane_xor<S>(lo));   \
+    hi = max(hi, lane_xor<S>(hi));
+    CDVS_STEP(1) CDVS_STEP(2) CDVS_STEP(4) CDVS_STEP(8) CDVS_STEP(16) CDVS_STEP(32)
+#undef CDVS_STEP
+}
+
+// The kCandCap strongest by |p| of an image's n > kCandCap candidates, as
+// indices in list[] (in no particular order): the kCandCap-th largest |p| by
+// a radix select on its float bits (non-negative floats order like their
+// bits), over the range they span so that the first round's counts spread,
+// then every candidate above it and enough of those equal to it.
+__device__ __forceinline__ void strongest(const float* __restrict__ absp, int n, int* hist, int* wsum, int* tmp,
+                                          uint32_t* lohi, uint32_t* __restrict__ list) {
+    const int tid = threadIdx.x;
+    // four keys at a time (an image's candidates start on, and its capacity
+    // is, a multiple of 256; what lies past n is skipped)
+    auto each = [&](auto&& f) {
+#pragma unroll 4
+        for (int i = 4 * tid; i < n; i += 4 * FIN_THREADS) {
+            const uint4 k = *reinterpret_cast<const uint4*>(absp + i);
+            f(i, k.x, true);
+            f(i + 1, k.y, i + 1 < n);
+            f(i + 2, k.z, i + 2 < n);
+            f(i + 3, k.w, i + 3 < n);
+        }
+    };
+    uint32_t lo = 0xffffffffu, hi = 0u;
+    each([&](int, uint32_t key, bool in) {
+        lo = in ? min(lo, key) : lo;
+        hi = in ? max(hi, key) : hi;
+    });
+    wave_min_max(lo, hi);
+    if ((tid & 63) == 0) {
+        atomicMin(&lohi[0], lo);
+        atomicMax(&lohi[1], hi);
+    }
+    __syncthreads();
+    lo = lohi[0];
+    // keys are taken from lo; the top bits found so far are prefix, at shift sh
+    const uint32_t range = lohi[1] - lo;
+    int need = kCandCap, sh = 32 - __clz((int)range | 1), width = 0;
+    uint32_t prefix = 0u;
+#pragma unroll 1
+    do {
+        reinterpret_cast<int4*>(hist)[tid] = make_int4(0, 0, 0, 0);
+        __syncthreads();
+        width = min(sh, 12);
+        const int up = sh;
+        sh -= width;
+        each([&](int, uint32_t bits, bool in) {
+            const uint32_t key = bits - lo;
+            if (in && (up > 31 || key >> up == prefix)) atomicAdd(&hist[(key >> sh) & ((1u << width) - 1u)], 1);
+        });
+        __syncthreads();
+        nth_from_top(hist, wsum, need, &tmp[0], &tmp[1]);
+        prefix = (prefix << width) | (uint32_t)tmp[0];
+        need = tmp[1];   // keys still needed from the threshold's bin
+        __syncthreads();
+    } while (sh > 0);
+    prefix += lo;
+    if (tid < 2) tmp[tid] = 0;
+    __syncthreads();
+    const int lane = tid & 63;
+#pragma unroll 2
+    for (int i0 = 0; i0 < n; i0 += 4 * FIN_THREADS) {   // the same for every lane: they count together
+        const int i = i0 + 4 * tid;
+        uint4 k = make_uint4(0u, 0u, 0u, 0u);
+        if (i < n) k = *reinterpret_cast<const uint4*>(absp + i);
+        const uint32_t key[4] = {k.x, k.y, k.z, k.w};
+        bool take[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            take[q] = i + q < n && key[q] > prefix;
+            if (i + q < n && key[q] == prefix) take[q] = atomicAdd(&tmp[1], 1) < need;
+        }
+        int before = 0, all = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint64_t m = __ballot(take[q]);
+            before += __popcll(m & ((1ull << lane) - 1ull));
+            all += __popcll(m);
+        }
+        int base = 0;
+        if (lane == 0 && all) base = atomicAdd(&tmp[0], all);
+        base = __shfl(base, 0) + before;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (take[q]) list[base++] = (uint32_t)(i + q);
+    }
+    __threadfence_block();
+    __syncthreads();
+}
+
+// Stage C + canonical order + top-k for one image per workgroup.
+//
+// The candidates of every octave but the first are binned into square cells
+// (a counting sort in LDS over at most kFinCells cells; of 8 octave pixels, in
+// large images more in the finer octaves), so that each candidate meets only
+// the few of the next octave in the cells around it; the decisions are those
+// of all pairs, as only pairs farther apart than the distance limit are
+// skipped.  The
+// survivors are put in canonical order by a counting sort as well, over 4096
+// bins of their range of |p|, which leaves few in any one bin; an image with
+// more than kFinCrowd in one that it keeps from is sorted in full.
+//
+// One workgroup per image is latency-bound whatever the image: the kernel is
+// a chain of passes with a barrier each.  With two bitonic sorts of every
+// candidate (the first to find the neighbours by binary search, in both
+// adjacent octaves) it took 47 us for one 640x480 image (1262 candidates) and
+// 199 us for 8192 candidates, beside 231 us of a kernel of its own that cut
+// 38,600 candidates to their 8192 strongest (its threshold found by one lane
+// walking the bins); now 13 us, and 63 us with the cut.
+constexpr int kFinCells = 4 * FIN_THREADS;
+constexpr int kFinCrowd = 32;
+static_assert(kFinCells <= 1 << 12 && kCandCap <= 1 << 19, "a cell and a place in one word");
+static_assert(kCandCap == 8 * FIN_THREADS, "8 flags per lane");
+
 __global__ __launch_bounds__(FIN_THREADS) void k_finalize(const cdvs_keypoint* __restrict__ cand,
+                                                          const float* __restrict__ absp,
                                                           const int32_t* __restrict__ cand_cnt,
                                                           const int64_t* __restrict__ cand_off,
                                                           const int32_t* __restrict__ cand_capv,
-                                                          const cdvs_keypoint* __restrict__ sel,
-                                                          float ratio_lim, int topk, int kp_cap,
-                                                          cdvs_keypoint* __restrict__ kp,
+                                                          uint32_t* __restrict__ lists,
+                                                          const int32_t* __restrict__ wh, float ratio_lim, int topk,
+                                                          int kp_cap, cdvs_keypoint* __restrict__ kp,
                                                           int32_t* __restrict__ count,
                                                           int32_t* __restrict__ flags) {
-    // 128 KB: sort keys + payloads, then the records (x, y, sigma, p) in
-    // (octave, y) order, then the final keys + payloads
+    // 128 KB: the records (x, y, sigma, p) by cell, then the keys and
+    // payloads of the sort
     __shared__ float4 rec[kCandCap];
-    __shared__ unsigned short perm[kCandCap];   // original index of each (octave, y)-sorted position
-    __shared__ int seg[kMaxOctaves + 2];        // first sorted position of each octave
-    __shared__ int n_alive;
-    __shared__ uint32_t min_bits;               // smallest |p| (as bits) of a reduced image's set
+    __shared__ __align__(16) int cell[kFinCells + 4];   // counts, then first positions; then the |p| histogram
+    __shared__ int wsum[FIN_THREADS / 64];
+    // an octave's first cell, cells per row and cell side (log2)
+    __shared__ int obase[kMaxOctaves], ocx[kMaxOctaves], oshift[kMaxOctaves];
+    __shared__ int tmp[4];
+    __shared__ uint32_t min_all, lohi[2];               // smallest |p| of a reduced image; range of |p| of the survivors
+    __shared__ int n_alive, crowded;
+    __shared__ __align__(16) uint8_t dead[kCandCap];   // by position: lost to a finer candidate
     unsigned long long* key = reinterpret_cast<unsigned long long*>(rec);
     unsigned short* idx = reinterpret_cast<unsigned short*>(key + kCandCap);
 
-    const int img = blockIdx.x;
-    // an image with more candidates than the LDS holds was reduced to its
-    // kCandCap strongest by k_select (exactly the ones stage C and the top-k
-    // can keep: a candidate only ever loses to a stronger one)
+    const int img = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int n_all = min(cand_cnt[img], cand_capv[img]);
-    const cdvs_keypoint* c = n_all > kCandCap ? sel + (int64_t)img * kCandCap : cand + cand_off[img];
+    const cdvs_keypoint* c = cand + cand_off[img];
+    const int W = wh[2 * img], H = wh[2 * img + 1];
     const int n = min(n_all, kCandCap);
-    const int tid = threadIdx.x;
-    int npow = 128;   // the sort works on whole 128-entry chunks (padding sorts last)
-    while (npow < n) npow <<= 1;
-
-    if (tid < kMaxOctaves + 2) seg[tid] = n;
+    // an image with more candidates than the LDS holds is reduced to its
+    // kCandCap strongest (exactly the ones stage C and the top-k can keep: a
+    // candidate only ever loses to a stronger one)
+    const uint32_t* list = nullptr;
+    if (n_all > kCandCap) {   // uniform over the workgroup
+        uint32_t* l = lists + (int64_t)img * kCandCap;
+        if (tid == 0) {
+            lohi[0] = 0xffffffffu;
+            lohi[1] = 0u;
+        }
+        __syncthreads();
+        strongest(absp + cand_off[img], n_all, cell, wsum, tmp, lohi, l);
+        list = l;
+    }
+    reinterpret_cast<int4*>(cell)[tid] = make_int4(0, 0, 0, 0);
+    reinterpret_cast<uint2*>(dead)[tid] = make_uint2(0u, 0u);
     if (tid == 0) {
-        n_alive = 0;
-        min_bits = 0xffffffffu;
+        min_all = lohi[0] = 0xffffffffu;
+        lohi[1] = 0u;
+        n_alive = crowded = 0;
     }
+    if (tid < 64) {
+        // lane o: octave o's size (halved rounding up), and the smallest cells
+        // with which all octaves' fit
+        const int o = min(lane, kMaxOctaves - 1);
+        const int w = (W + (1 << o) - 1) >> o, h = (H + (1 << o) - 1) >> o;
+        int s = 3, sh, total, incl, cells;
+        do {
+            ++s;
+            sh = max(3, s - o);
+            cells = lane > 0 && lane < kMaxOctaves ? (((w - 1) >> sh) + 1) * (((h - 1) >> sh) + 1) : 0;
+            incl = cells;
+#pragma unroll
+            for (int off = 1; off < kMaxOctaves; off <<= 1) {
+                const int u = __shfl_up(incl, off);
+                if (lane >= off) incl += u;
+            }
+            total = __shfl(incl, kMaxOctaves - 1);
+        } while (total > kFinCells);
+        if (lane < kMaxOctaves) {
+            obase[lane] = incl - cells;
+            ocx[lane] = ((w - 1) >> sh) + 1;
+            oshift[lane] = sh;
+        }
+    }
+    // this thread's candidates: position, scale and response, and the low
+    // word of the canonical key (octave, iy, ix)
+    float4 a[FIN_PER];
+    uint32_t low[FIN_PER], src[FIN_PER];
+    // (all indices first, then all records, so that each is one round trip;
+    // lanes past the end read the last one again)
+#pragma unroll
+    for (int j = 0; j < FIN_PER; ++j)
+        if (j * FIN_THREADS < n) {
+            const int i = min(tid + j * FIN_THREADS, n - 1);
+            src[j] = list ? list[i] : (uint32_t)i;
+        }
+#pragma unroll
+    for (int j = 0; j < FIN_PER; ++j)
+        if (j * FIN_THREADS < n) {
+            const uint4* r = reinterpret_cast<const uint4*>(c + src[j]);
+            const uint4 q = r[0], t = r[2];
+            a[j] = make_float4(__uint_as_float(q.x), __uint_as_float(q.y), __uint_as_float(q.z), __uint_as_float(q.w));
+            low[j] = (t.y << 28) | (t.w << 14) | t.z;
+        }
     __syncthreads();
+    // the cell, along one axis, of base-image coordinate v in an octave of
+    // the given side (beyond the image: the outermost)
+    auto cell_of = [&](float v, int o, int side) {
+        return min(max((int)floorf(__builtin_amdgcn_ldexpf(v, -o)), 0), ((side + (1 << o) - 1) >> o) - 1) >> oshift[o];
+    };
+    int at[FIN_PER];   // the cell, and the place in it
     uint32_t my_min = 0xffffffffu;
-    for (int i = tid; i < npow; i += FIN_THREADS) {
-        // y >= 0, so its float bits order like the value
-        key[i] = i < n ? ((unsigned long long)c[i].octave << 32) | __float_as_uint(c[i].y) : ~0ull;
-        idx[i] = (unsigned short)i;
-        if (i < n) my_min = min(my_min, __float_as_uint(fabsf(c[i].p)));
-    }
-    if (n_all > kCandCap) atomicMin(&min_bits, my_min);
-    __syncthreads();
-    bitonic_sort(key, idx, npow);
-    for (int i = tid; i < n; i += FIN_THREADS) {
-        perm[i] = idx[i];
-        const int o = (int)(key[i] >> 32);
-        const int prev = i == 0 ? -1 : (int)(key[i - 1] >> 32);
-        for (int oo = prev + 1; oo <= o; ++oo) seg[oo] = i;
-    }
-    __syncthreads();   // keys are read; the records overwrite them
-    for (int i = tid; i < n; i += FIN_THREADS) {
-        const cdvs_keypoint a = c[perm[i]];
-        rec[i] = make_float4(a.x, a.y, a.sigma, a.p);
-    }
-    __syncthreads();
-
-    unsigned long long kk[FIN_PER];
-    int local_alive = 0;
 #pragma unroll
     for (int j = 0; j < FIN_PER; ++j) {
-        const int i = tid + j * FIN_THREADS;
-        kk[j] = ~0ull;
-        if (i < n) {
-            const float4 a = rec[i];
-            int ao = 0;
-            while (ao + 1 < kMaxOctaves + 1 && seg[ao + 1] <= i) ++ao;
-            const float aa = fabsf(a.w);
-            bool alive = true;
-            for (int d = -1; d <= 1 && alive; d += 2) {
-                const int o2 = ao + d;
-                if (o2 < 0 || o2 >= kMaxOctaves) continue;
-                const float lim = (float)(1 << max(ao, o2));
-                const float lim2 = lim * lim;
-                // the band searched is one pixel wider than the limit, so
-                // rounding here cannot drop a pair the exact test keeps
-                const float ylo = a.y - (lim + 1.f), yhi = a.y + (lim + 1.f);
-                int lo = seg[o2], hi = seg[o2 + 1];
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (rec[mid].y < ylo) lo = mid + 1;
-                    else hi = mid;
-                }
-                for (int jj = lo; jj < seg[o2 + 1]; ++jj) {
-                    const float4 b = rec[jj];
-                    if (b.y > yhi) break;
-                    if ((a.w > 0.f) != (b.w > 0.f)) continue;
-                    const float dx = a.x - b.x, dy = a.y - b.y;
-                    if (!(dx * dx + dy * dy <= lim2)) continue;
-                    const float shi = fmaxf(a.z, b.z), slo = fminf(a.z, b.z);
-                    if (!(shi <= ratio_lim * slo)) continue;
-                    const float ab = fabsf(b.w);
-                    if (ab > aa || (ab == aa && o2 < ao)) {
-                        alive = false;
-                        break;
+        if (tid + j * FIN_THREADS < n) {
+            const int o = (int)(low[j] >> 28);
+            if (o > 0) {
+                at[j] = obase[o] + cell_of(a[j].y, o, H) * ocx[o] + cell_of(a[j].x, o, W);
+                at[j] |= atomicAdd(&cell[at[j]], 1) << 12;
+            }
+            my_min = min(my_min, __float_as_uint(fabsf(a[j].w)));
+        }
+    }
+    if (list) {
+        uint32_t hi = 0u;
+        wave_min_max(my_min, hi);
+        if (lane == 0) atomicMin(&min_all, my_min);
+    }
+    __syncthreads();
+    const int binned = scan4(cell, wsum);
+    if (tid == 0) cell[kFinCells] = binned;
+#pragma unroll
+    for (int j = 0; j < FIN_PER; ++j)
+        if (tid + j * FIN_THREADS < n && low[j] >> 28 != 0u) rec[cell[at[j] & (kFinCells - 1)] + (at[j] >> 12)] = a[j];
+    __syncthreads();
+
+    // Stage C: each candidate meets those of the next coarser octave, and of
+    // two that are duplicates the weaker one is out (equal: the coarser)
+    uint32_t out = 0u;   // bit j: candidate j is
+#pragma unroll
+    for (int j = 0; j < FIN_PER; ++j) {
+        const int ao = (int)(low[j] >> 28), o2 = ao + 1;
+        if (tid + j * FIN_THREADS < n && o2 < kMaxOctaves) {
+            const float aa = fabsf(a[j].w);
+            const float lim = (float)(1 << o2);
+            const float lim2 = lim * lim;
+            // the cells searched are those of a square one pixel wider than
+            // the limit, so rounding here cannot drop a pair the exact test
+            // keeps
+            const float reach = lim + 1.f;
+            const int x0 = cell_of(a[j].x - reach, o2, W), x1 = cell_of(a[j].x + reach, o2, W);
+            const int y0 = cell_of(a[j].y - reach, o2, H), y1 = cell_of(a[j].y + reach, o2, H);
+            for (int y = y0; y <= y1; ++y) {
+                const int row = obase[o2] + y * ocx[o2];
+                const int end = cell[row + x1 + 1];
+                for (int q = cell[row + x0]; q < end; ++q) {
+                    const float4 b = rec[q];
+                    const float dx = a[j].x - b.x, dy = a[j].y - b.y;
+                    const float shi = fmaxf(a[j].z, b.z), slo = fminf(a[j].z, b.z);
+                    if (((a[j].w > 0.f) == (b.w > 0.f)) & (dx * dx + dy * dy <= lim2) & (shi <= ratio_lim * slo)) {
+                        if (fabsf(b.w) > aa) out |= 1u << j;
+                        else dead[q] = 1;
                     }
                 }
             }
-            if (alive) {
-                ++local_alive;
-                const cdvs_keypoint& r = c[perm[i]];
-                kk[j] = ((unsigned long long)(~__float_as_uint(aa)) << 32) |
-                        ((unsigned long long)ao << 28) | ((unsigned long long)r.iy << 14) |
-                        (unsigned long long)r.ix;
-            }
-        }
-    }
-    if (local_alive) atomicAdd(&n_alive, local_alive);
-    __syncthreads();  // every lane is done reading rec[] before keys overwrite it
-#pragma unroll
-    for (int j = 0; j < FIN_PER; ++j) {
-        const int i = tid + j * FIN_THREADS;
-        if (i < npow) {
-            key[i] = kk[j];
-            idx[i] = (unsigned short)i;
         }
     }
     __syncthreads();
-    bitonic_sort(key, idx, npow);
-
-    const int limit = min(topk > 0 ? topk : kp_cap, kp_cap);
-    const int m = min(n_alive, limit);
-    for (int r = tid; r < m; r += blockDim.x) kp[(int64_t)img * kp_cap + r] = c[perm[idx[r]]];
+    uint32_t alive = 0u;
+    {
+        uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+        for (int j = 0; j < FIN_PER; ++j)
+            if (tid + j * FIN_THREADS < n && !(out >> j & 1u) &&
+                (low[j] >> 28 == 0u || !dead[cell[at[j] & (kFinCells - 1)] + (at[j] >> 12)])) {
+                alive |= 1u << j;
+                lo = min(lo, __float_as_uint(fabsf(a[j].w)));
+                hi = max(hi, __float_as_uint(fabsf(a[j].w)));
+            }
+        wave_min_max(lo, hi);
+        int na = __popc(alive);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) na += __shfl_xor(na, off);
+        if (lane == 0 && na) {   // (one atomic of each kind per wave: a lane's own would queue up 1024 deep)
+            atomicAdd(&n_alive, na);
+            atomicMin(&lohi[0], lo);
+            atomicMax(&lohi[1], hi);
+        }
+    }
+    __syncthreads();   // every lane is done with the records and cells
+    // Canonical order: a histogram of |p| over the survivors' own range,
+    // strongest bin first, puts each one after all of the higher bins, and
+    // the few of its own bin are compared with it by key
+    const int total = n_alive, limit = min(topk > 0 ? topk : kp_cap, kp_cap), m = min(total, limit);
+    const uint32_t top = lohi[1], range = top - lohi[0];
+    const int sh = max(0, 32 - __clz((int)range | 1) - 12);   // range >> sh < kFinCells
+    auto bin_of = [&](int j) { return (int)((top - __float_as_uint(fabsf(a[j].w))) >> sh); };
+    reinterpret_cast<int4*>(cell)[tid] = make_int4(0, 0, 0, 0);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < FIN_PER; ++j)
+        if (alive >> j & 1u) {
+            const int b = bin_of(j), place = atomicAdd(&cell[b], 1);
+            at[j] = b | place << 12;
+        }
+    __syncthreads();
+    scan4(cell, wsum);
+    if (tid == 0) cell[kFinCells] = total;
+#pragma unroll
+    for (int j = 0; j < FIN_PER; ++j)   // a crowded bin among those that are kept from
+        if ((alive >> j & 1u) && (at[j] >> 12) >= kFinCrowd && cell[at[j] & (kFinCells - 1)] < m) crowded = 1;
+    __syncthreads();
+    auto key_of = [&](int j) { return ((unsigned long long)(~__float_as_uint(fabsf(a[j].w))) << 32) | low[j]; };
+    if (!crowded) {   // uniform over the workgroup
+#pragma unroll
+        for (int j = 0; j < FIN_PER; ++j)
+            if (alive >> j & 1u) key[cell[at[j] & (kFinCells - 1)] + (at[j] >> 12)] = key_of(j);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < FIN_PER; ++j)
+            if (alive >> j & 1u) {
+                const int b = at[j] & (kFinCells - 1), beg = cell[b];
+                if (beg < m) {
+                    const unsigned long long k = key_of(j);
+                    int r = beg;
+                    for (int q = beg; q < cell[b + 1]; ++q) r += key[q] < k;
+                    if (r < m) idx[r] = (unsigned short)(tid + j * FIN_THREADS);
+                    if (r == limit - 1) tmp[2] = (int)__float_as_uint(fabsf(a[j].w));   // the last one kept
+                }
+            }
+        __syncthreads();
+    } else {
+        // many responses alike: a bitonic sort of all survivors
+#pragma unroll
+        for (int j = 0; j < FIN_PER; ++j)
+            if (alive >> j & 1u) {
+                const int q = cell[at[j] & (kFinCells - 1)] + (at[j] >> 12);
+                key[q] = key_of(j);
+                idx[q] = (unsigned short)(tid + j * FIN_THREADS);
+            }
+        int npow = 128;   // the sort works on whole 128-entry chunks (padding sorts last)
+        while (npow < total) npow <<= 1;
+        for (int i = total + tid; i < npow; i += FIN_THREADS) {
+            key[i] = ~0ull;
+            idx[i] = 0;
+        }
+        __syncthreads();
+        bitonic_sort(key, idx, npow);
+        if (tid == 0 && total >= limit) tmp[2] = (int)~(uint32_t)(key[limit - 1] >> 32);
+    }
+    for (int r = tid; r < m; r += FIN_THREADS) {
+        const int i = idx[r];
+        kp[(int64_t)img * kp_cap + r] = c[list ? list[i] : (uint32_t)i];
+    }
     if (tid == 0) {
         count[img] = m;
         // A reduced image's output is exact when its last kept keypoint is
-        // stronger than every candidate k_select dropped: each kept one was
+        // stronger than every candidate that was dropped: each kept one was
         // judged against all candidates at least as strong, and no dropped
         // candidate could rank among them.  Otherwise the image is flagged.
-        if (n_all > kCandCap && limit > 0) {
-            const bool exact = n_alive >= limit && ~(uint32_t)(key[limit - 1] >> 32) > min_bits;
+        if (list && limit > 0) {
+            const bool exact = total >= limit && (uint32_t)tmp[2] > min_all;
             if (!exact) atomicOr(flags, kFlagSelectInexact);
         }
     }
@@ -743,12 +960,12 @@ hipError_t launch_clear(int32_t* p, int n, hipStream_t stream) {
 }
 
 hipError_t launch_detect_strips(const float* pyr, const DetTile* strips, int nstrips, int variant, int grid,
-                                const DetParams& dp, const GateParams& gate, int32_t* work, cdvs_keypoint* cand,
-                                int32_t* cand_cnt, int32_t* flags, hipStream_t stream) {
+                                const DetParams& dp, const GateParams& gate, int32_t* work, const DetOut& out,
+                                hipStream_t stream) {
     if (nstrips <= 0) return hipSuccess;
 #define DETECT_LAUNCH(G, P, NB)                                                                                    \
     hipLaunchKernelGGL((k_detect_strip<G, P>), dim3(NB), dim3(256), 0, stream, pyr, strips, nstrips, dp, gate, work, \
-                       cand, cand_cnt, flags)
+                       out)
     if (variant == kDetectPersistent) {
         // a multiple of the XCD count, no larger than one wave per strip
         int g = std::min(grid, (nstrips + 4 * kXcds - 1) / (4 * kXcds) * kXcds);
@@ -768,20 +985,13 @@ hipError_t launch_detect_strips(const float* pyr, const DetTile* strips, int nst
     return hipGetLastError();
 }
 
-hipError_t launch_select(const cdvs_keypoint* cand, const int32_t* cand_cnt, const int64_t* cand_off,
-                         const int32_t* cand_capv, int n_images, cdvs_keypoint* sel, hipStream_t stream) {
-    if (n_images <= 0 || !sel) return hipSuccess;
-    hipLaunchKernelGGL(k_select, dim3(n_images), dim3(FIN_THREADS), 0, stream, cand, cand_cnt, cand_off, cand_capv, sel);
-    return hipGetLastError();
-}
-
-hipError_t launch_finalize(const cdvs_keypoint* cand, const int32_t* cand_cnt, const int64_t* cand_off,
-                           const int32_t* cand_capv, const cdvs_keypoint* sel, int n_images, float dedup_ratio,
-                           int topk, int kp_cap, cdvs_keypoint* kp, int32_t* count, int32_t* flags,
+hipError_t launch_finalize(const cdvs_keypoint* cand, const float* absp, const int32_t* cand_cnt, const int64_t* cand_off,
+                           const int32_t* cand_capv, uint32_t* lists, const int32_t* wh, int n_images,
+                           float dedup_ratio, int topk, int kp_cap, cdvs_keypoint* kp, int32_t* count, int32_t* flags,
                            hipStream_t stream) {
     if (n_images <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_finalize, dim3(n_images), dim3(FIN_THREADS), 0, stream, cand, cand_cnt, cand_off, cand_capv,
-                       sel, dedup_ratio, topk, kp_cap, kp, count, flags);
+    hipLaunchKernelGGL(k_finalize, dim3(n_images), dim3(FIN_THREADS), 0, stream, cand, absp, cand_cnt, cand_off,
+                       cand_capv, lists, wh, dedup_ratio, topk, kp_cap, kp, count, flags);
     return hipGetLastError();
 }
 
