@@ -4,8 +4,8 @@
 //   X_l = relu(conv3x3(X_{l-1})), l = 1..4, 16 -> 16 channels, zero padding,
 //   Z = X4 . Wh + bh (16 -> 6, one logit per octave), mask bit o = Z_o > logit(tau).
 // Activations are bf16 in HWC order (16 channels = 32 bytes per cell); the
-// 3x3 convolutions of the forward pass and of both backward passes are
-// v_mfma_f32_16x16x32_bf16 with fp32 accumulation; the head is fp32 VALU.
+// 3x3 convolutions of the forward pass and of both backward passes are bf16
+// MFMAs with fp32 accumulation; the head is fp32 VALU.
 //
 // Parameter vector (fp32, 9382): for l = 1..4: W_l[9][16][16] ([tap][ci][co],
 // tap = 3(dy+1)+(dx+1)) then b_l[16]; then Wh[16][6] ([c][o]) then bh[6].
@@ -570,9 +570,11 @@ __global__ __launch_bounds__(256) void k_conv_bwd_weight(const uint8_t* __restri
 }
 
 // Input gradient of layer l: dX_{l-1}[p][ci] = sum_t sum_co W[t][ci][co]
-// dP_l[p - d_t][co], then times (X_{l-1} > 0) to give dP_{l-1} (bf16): the
-// forward convolution with the taps reversed and the weights transposed, and
-// the same MFMA operands (two taps per instruction, the tenth zero).
+// dP_l[p - d_t][co], then times (X_{l-1} > 0) to give dP_{l-1} (bf16).  One
+// tap per v_mfma_f32_16x16x16_bf16 (lane l holds A[l%16][4(l/16)+j] and
+// B[4(l/16)+j][l%16] for j = 0..3), in the order of the taps: two taps per
+// instruction add up in another order, whose roundings to bf16 an Adam step
+// then carries on, and the time is the memory's either way (13 us).
 //
 // One 256-lane workgroup per 32 x 16 cells; the tile of dP with its rim is
 // staged in LDS and each wave takes four rows.  Bound by memory: 96 B per
@@ -589,24 +591,17 @@ __global__ __launch_bounds__(256) void k_conv_bwd_data(const short* __restrict__
     const int lt = tile - g.ftile0;
     const int ty0 = (lt / g.ftiles_x) * WTH, tx0 = (lt % g.ftiles_x) * WTW;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, kb = lane >> 4, li = lane & 15;
-    const int half = kb >> 1, c8 = (kb & 1) * 8;
     s8 v[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) {
         const int it = threadIdx.x + 256 * j, cell = it >> 1, r = cell / PW, c = cell % PW;
         v[j] = load_cell8<false>(nullptr, dP, g, it < N ? ty0 - 1 + r : -1, tx0 - 1 + c, it & 1);
     }
-    // A[ci = lane % 16][8 half-tap channels]: reversed tap t reads the cell at
-    // (t / 3 - 1, t % 3 - 1), so its weight is W[8 - t][ci][co]
-    s8 a[kTapPairs];
+    s4 a[9];   // A[ci = lane % 16][co]
 #pragma unroll
-    for (int m = 0; m < kTapPairs; ++m) {
-        const int t = 2 * m + half;
-        const float* w = Wl + ((t < 9 ? 8 - t : 0) * CC + li) * CC + c8;
-        uint32_t p[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) p[j] = t < 9 ? f2bf2(w[2 * j], w[2 * j + 1]) : 0u;
-        a[m] = __builtin_bit_cast(s8, make_uint4(p[0], p[1], p[2], p[3]));
+    for (int t = 0; t < 9; ++t) {
+        const float* w = Wl + (t * CC + li) * CC + 4 * kb;
+        a[t] = __builtin_bit_cast(s4, make_uint2(f2bf2(w[0], w[1]), f2bf2(w[2], w[3])));
     }
 #pragma unroll
     for (int j = 0; j < J; ++j) {
@@ -629,26 +624,18 @@ __global__ __launch_bounds__(256) void k_conv_bwd_data(const short* __restrict__
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        s8 b[kTapPairs][2];
+        s4 b[9][2];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            // tap 0 of this lane's cell; lanes of a pair's second tap are one
-            // cell further (pair 1: the next row's first); the tenth tap is
-            // zero on both sides (a gradient may not be finite)
-            const short* base = &buf[((4 * wave + q) * PW + 16 * h + li) * CC + c8];
-            const short* pa = base + half * CC;
-            b[0][h] = *reinterpret_cast<const s8*>(pa);
-            b[1][h] = *reinterpret_cast<const s8*>(base + half * (PW - 2) * CC + 2 * CC);
-            b[2][h] = *reinterpret_cast<const s8*>(pa + (PW + 1) * CC);
-            b[3][h] = *reinterpret_cast<const s8*>(pa + 2 * PW * CC);
-            b[4][h] = *reinterpret_cast<const s8*>(base + (2 * PW + 2) * CC);
-            if (half) b[4][h] = s8{0, 0, 0, 0, 0, 0, 0, 0};
-        }
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int t = 0; t < 9; ++t)   // the cell at (1 - t / 3, 1 - t % 3) from this lane's
+                b[t][h] = *reinterpret_cast<const s4*>(
+                    &buf[((4 * wave + q + 2 - t / 3) * PW + 16 * h + li + 2 - t % 3) * CC + 4 * kb]);
         f4 acc[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-        for (int m = 0; m < kTapPairs; ++m)
+        for (int t = 0; t < 9; ++t)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) acc[h] = mfma32(a[m], b[m][h], acc[h]);
+            for (int h = 0; h < 2; ++h) acc[h] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[t], b[t][h], acc[h], 0, 0, 0);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             float r[4];
