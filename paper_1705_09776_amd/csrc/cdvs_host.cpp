@@ -67,6 +67,7 @@ struct cdvs_ctx {
     int32_t* d_blur_owner = nullptr;
     std::vector<int32_t> cnn_owner;            // fused CNN tile -> image
     int32_t* d_cnn_owner = nullptr;
+    int strip_h = kDetStripH;      // centre rows of a detection strip
     std::vector<DetTile> strips;   // ungated detection: image-major, then octave, then row-major strips
     DetTile* d_strips = nullptr;
     OctGeom* d_geom = nullptr;
@@ -77,7 +78,7 @@ struct cdvs_ctx {
     int32_t* d_cand_capv = nullptr;
     float* d_absp = nullptr;                   // |p| of each candidate (only when needed)
     uint32_t* d_sel = nullptr;                 // [image][kCandCap] strongest candidates' indices (only when needed)
-    int32_t* d_cand_cnt = nullptr;             // n per-image counts, then kXcds detection work counters
+    int32_t* d_cand_cnt = nullptr;             // n per-image counts, then kXcds detection work counters, kCntStride apart
     cdvs_keypoint* d_ori = nullptr;
     int32_t* d_ori_cnt = nullptr;
     int32_t* d_flags = nullptr;
@@ -408,6 +409,13 @@ static cdvs_status build_layout(cdvs_ctx* c) {
     // whole images (balanced work, and neighbouring strips share halo rows
     // in that XCD's L2)
     c->strips.clear();
+    int64_t tall = 0;   // strips of the full height
+    for (const OctJob& j : c->jobs) {
+        const int cw = j.w - 2 * c->params.border, ch = j.h - 2 * c->params.border;
+        if (cw > 0 && ch > 0)
+            tall += (int64_t)((cw + kDetStripW - 1) / kDetStripW) * ((ch + kDetStripH - 1) / kDetStripH);
+    }
+    c->strip_h = det_strip_height(tall);
     for (int i = 0; i < c->n; ++i)
         for (int o = 0; o < kMaxOctaves; ++o)
             for (const OctJob& j : per_oct[o]) {
@@ -415,7 +423,7 @@ static cdvs_status build_layout(cdvs_ctx* c) {
                 const int b = c->params.border;
                 const int cw = j.w - 2 * b, ch = j.h - 2 * b;
                 if (cw <= 0 || ch <= 0) continue;
-                const int sx = (cw + kDetStripW - 1) / kDetStripW, sy = (ch + kDetStripH - 1) / kDetStripH;
+                const int sx = (cw + kDetStripW - 1) / kDetStripW, sy = (ch + c->strip_h - 1) / c->strip_h;
                 for (int t = 0; t < sx * sy; ++t) {
                     DetTile r;
                     memset(&r, 0, sizeof(r));
@@ -425,7 +433,7 @@ static cdvs_status build_layout(cdvs_ctx* c) {
                     r.w = j.w;
                     r.h = j.h;
                     r.tx0 = b + (t % sx) * kDetStripW;
-                    r.ty0 = b + (t / sx) * kDetStripH;
+                    r.ty0 = b + (t / sx) * c->strip_h;
                     r.image = j.image;
                     r.octave = j.octave;
                     r.cand_cap = c->cand_cap[j.image];
@@ -568,7 +576,7 @@ cdvs_status cdvs_ctx_create(const cdvs_params* params, const cdvs_image_desc* im
             ALLOC(c->d_absp, sizeof(float) * total);
         }
     }
-    ALLOC(c->d_cand_cnt, sizeof(int32_t) * (n + kXcds));
+    ALLOC(c->d_cand_cnt, sizeof(int32_t) * (n + kXcds) * kCntStride);
     ALLOC(c->d_ori, sizeof(cdvs_keypoint) * n * kp_capacity * kMaxOri);
     ALLOC(c->d_ori_cnt, sizeof(int32_t) * n * kp_capacity);
     ALLOC(c->d_flags, sizeof(int32_t));
@@ -608,7 +616,7 @@ cdvs_status cdvs_ctx_create(const cdvs_params* params, const cdvs_image_desc* im
         (e = hipMemcpy(c->d_cand_capv, c->cand_cap.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice)) !=
             hipSuccess ||
         (e = hipMemset(c->d_flags, 0, sizeof(int32_t))) != hipSuccess ||
-        (e = hipMemset(c->d_cand_cnt, 0, sizeof(int32_t) * (n + kXcds))) != hipSuccess) {
+        (e = hipMemset(c->d_cand_cnt, 0, sizeof(int32_t) * (n + kXcds) * kCntStride)) != hipSuccess) {
         fail(nullptr, CDVS_ERR_HIP, "context upload: %s", hipGetErrorString(e));
         cdvs_ctx_destroy(c);
         return CDVS_ERR_HIP;
@@ -711,8 +719,8 @@ cdvs_status cdvs_alp_detect(cdvs_ctx* ctx, const float* d_pyr, const uint8_t* d_
         // one launch over the strips of every octave; the finalisation does
         // not rely on the order in which candidates arrive
         Bracket b(ctx, CDVS_KERNEL_DETECT, s);
-        HIP_OR_FAIL(ctx, launch_detect_strips(d_pyr, ctx->d_strips, (int)ctx->strips.size(), ctx->detect_variant,
-                                              ctx->detect_grid, ctx->det, gate, ctx->d_cand_cnt + ctx->n, det_out(ctx), s));
+        HIP_OR_FAIL(ctx, launch_detect_strips(d_pyr, ctx->d_strips, (int)ctx->strips.size(), ctx->strip_h, ctx->detect_variant,
+                                              ctx->detect_grid, ctx->det, gate, ctx->d_cand_cnt + ctx->n * kCntStride, det_out(ctx), s));
     }
     {
         Bracket b(ctx, CDVS_KERNEL_FINALIZE, s);
@@ -1173,8 +1181,8 @@ cdvs_status cdvs_autotune(cdvs_ctx* ctx, const uint8_t* d_images, float* d_pyr, 
             [&](int var) -> cdvs_status {
                 const GateParams gate{nullptr, nullptr, nullptr, 1.f};
                 HIP_OR_FAIL(ctx, launch_clear(ctx->d_cand_cnt, ctx->n + kXcds, s));
-                HIP_OR_FAIL(ctx, launch_detect_strips(d_pyr, ctx->d_strips, (int)ctx->strips.size(), var,
-                                                      ctx->detect_grid, ctx->det, gate, ctx->d_cand_cnt + ctx->n, det_out(ctx),
+                HIP_OR_FAIL(ctx, launch_detect_strips(d_pyr, ctx->d_strips, (int)ctx->strips.size(), ctx->strip_h, var,
+                                                      ctx->detect_grid, ctx->det, gate, ctx->d_cand_cnt + ctx->n * kCntStride, det_out(ctx),
                                                       s));
                 return CDVS_OK;
             },

@@ -186,6 +186,11 @@ struct GateParams {
     float fmax;              // fraction of active cells above which detection is dense
 };
 
+// Counters that many waves add to lie this many words apart: additions to
+// one line queue up (about 4.4 ns each, whichever word of it they go to), and
+// 16 images' counters in one line held the detection of a 1280x960 batch back.
+constexpr int kCntStride = 32;
+
 // Where the detection puts what it finds: candidate records and their number
 // per image, and (unless null) |p| of each once more, contiguous, for the
 // selection in images with many.
@@ -213,16 +218,26 @@ hipError_t launch_preblur(const uint8_t* images, float* pyr, const OctJob* jobs,
                           const Taps& taps, hipStream_t stream);
 hipError_t launch_scales(float* pyr, const OctJob* jobs, const int32_t* owner, int ntiles, int variant,
                          const Taps& taps, hipStream_t stream);
-hipError_t launch_clear(int32_t* p, int n, hipStream_t stream);
-// Detection over strips of 60 x kDetStripH centres inside the detection
-// border (tx0, ty0 = the strip's first centre), one wave at a time each;
-// gated by gate.mask unless it is null.
+hipError_t launch_clear(int32_t* p, int n, hipStream_t stream);   // n counters, kCntStride apart
+// Detection over strips of 60 x strip_h centres inside the detection border
+// (tx0, ty0 = the strip's first centre), one wave at a time each; gated by
+// gate.mask unless it is null.  A wave takes a strip's rows one after the
+// other, so a batch with fewer strips than the chip holds waves (7168) is cut
+// lower: each strip then reads and differentiates four rows beside its own,
+// but there are more of them at work (whole pass, by the strip height 6, 12,
+// 24, 48: one 640x480 image 98, 99, 105, 118 us; 4 of them 114, 115, 119, 129;
+// 16 of them 196, 196, 198, 204; 16 of 1280x960 452, 437, 431, 435; 256 of
+// 640x480 1952, 1898, 1868, 1867).  All heights are multiples of the 6 rows
+// that the kernel's loop takes at a time.
 constexpr int kDetStripW = 60, kDetStripH = 48;
+inline int det_strip_height(int64_t tall_strips) {   // tall_strips: the batch's strips of kDetStripH rows
+    return tall_strips <= 1024 ? 6 : tall_strips <= 4096 ? 12 : tall_strips <= 16384 ? 24 : kDetStripH;
+}
 // Launch forms (the detection's tunable variant): one wave per strip, or
 // persistent: `grid` workgroups (rounded to a multiple of 8) pulling strips
-// from per-XCD counters work[0..7], which must be zero at launch.
+// from per-XCD counters (work, kCntStride apart), which must be zero at launch.
 constexpr int kDetectPerStrip = 0, kDetectPersistent = 1, kDetectVariants = 2;
-hipError_t launch_detect_strips(const float* pyr, const DetTile* strips, int nstrips, int variant, int grid,
+hipError_t launch_detect_strips(const float* pyr, const DetTile* strips, int nstrips, int strip_h, int variant, int grid,
                                 const DetParams& dp, const GateParams& gate, int32_t* work, const DetOut& out,
                                 hipStream_t stream);
 // absp (|p| per candidate) and lists (kCandCap indices per image) are used by

@@ -128,44 +128,54 @@ __device__ __forceinline__ bool refine_v(const float (&v)[9], float s, float p, 
     return true;
 }
 
-// Wave-level compaction of survivors into the image's candidate list: one
-// ballot and one atomic per wave.  Every lane of the wave must call it.
-__device__ __forceinline__ void emit(bool keep, const Cand& c, int gx, int gy, const DetTile& job, const DetOut& out) {
-    const int lane = threadIdx.x & 63;
-    const uint64_t m = __ballot(keep);
-    if (!m) return;
-    const int leader = __ffsll((unsigned long long)m) - 1;
-    int base = 0;
-    if (lane == leader) base = atomicAdd(&out.cnt[job.image], __popcll(m));
-    base = __shfl(base, leader);
-    if (!keep) return;
-    const int slot = base + __popcll(m & ((1ull << lane) - 1ull));
+// A centre that came through the refinement (keep) or not.
+struct Refined {
+    Cand c;
+    int gx, gy;
+    bool keep;
+};
+
+// A survivor's record, at a slot of its image's candidates.
+__device__ __forceinline__ void store_candidate(const Refined& v, int slot, const DetTile& job, const DetOut& out) {
     if (slot >= job.cand_cap) {
         atomicOr(out.flags, kFlagCandOverflow);
         return;
     }
     const float scale = (float)(1 << job.octave);
     cdvs_keypoint r;
-    r.x = ((float)gx + c.ox) * scale;
-    r.y = ((float)gy + c.oy) * scale;
-    r.sigma = c.s * scale;
-    r.p = c.pr;
+    r.x = ((float)v.gx + v.c.ox) * scale;
+    r.y = ((float)v.gy + v.c.oy) * scale;
+    r.sigma = v.c.s * scale;
+    r.p = v.c.pr;
     r.theta = 0.f;
-    r.rho = c.rho;
-    r.p_ss = c.pss;
+    r.rho = v.c.rho;
+    r.p_ss = v.c.pss;
     r.peak = 0.f;
     r.image = job.image;
     r.octave = job.octave;
-    r.ix = gx;
-    r.iy = gy;
+    r.ix = v.gx;
+    r.iy = v.gy;
     const int64_t at = (int64_t)job.cand_blk * kCandBlock + slot;
     out.cand[at] = r;
-    if (out.absp) out.absp[at] = fabsf(c.pr);
+    if (out.absp) out.absp[at] = fabsf(v.c.pr);
+}
+
+// Wave-level compaction of survivors into the image's candidate list: one
+// ballot and one atomic per wave.  Every lane of the wave must call it.
+__device__ __forceinline__ void emit(const Refined& v, const DetTile& job, const DetOut& out) {
+    const int lane = threadIdx.x & 63;
+    const uint64_t m = __ballot(v.keep);
+    if (!m) return;
+    const int leader = __ffsll((unsigned long long)m) - 1;
+    int base = 0;
+    if (lane == leader) base = atomicAdd(&out.cnt[job.image * kCntStride], __popcll(m));
+    base = __shfl(base, leader);
+    if (v.keep) store_candidate(v, base + __popcll(m & ((1ull << lane) - 1ull)), job, out);
 }
 
 // ---------------------------------------------------------------------------
 // k_detect_strip: the detection, one wave per strip of kStripW
-// centre columns x kStripH centre rows of one (image, octave) inside the
+// centre columns x strip_h centre rows of one (image, octave) inside the
 // detection border; lane l holds image column x0 - 2 + l (lanes 0, 1, 62
 // and 63 are halo).  The wave walks down its strip one row at a time with
 // no LDS staging and no barriers: each row's five plane values arrive by one
@@ -180,7 +190,6 @@ __device__ __forceinline__ void emit(bool keep, const Cand& c, int gx, int gy, c
 // in passes of up to 64 once more than 36 are waiting (dense lanes; one
 // global atomic per pass).
 constexpr int kStripW = kDetStripW;
-constexpr int kStripH = kDetStripH;
 constexpr int kQCap = 96;              // flushed above 36, and one row adds at most 60
 constexpr int kQFlush = kQCap - 60;
 constexpr int kQFields = 12;           // the eight neighbour values, s, p, pss, (x | y << 16)
@@ -238,17 +247,11 @@ __device__ __forceinline__ float4 strip_alpha(const StripRow& u, const StripRow&
     return a;
 }
 
-// Refines queued centres base .. base+n-1 (n <= 64) of this wave and
-// appends the survivors to the image's candidates.  Every lane of the wave
-// calls it.
-__device__ __forceinline__ void strip_flush(float (*q)[kQCap], int base, int n, const DetTile& job,
-                                            const DetParams& dp, const DetOut& out) {
-    const int lane = threadIdx.x & 63;
-    Cand c{};
-    bool keep = false;
-    int gx = 0, gy = 0;
-    if (lane < n) {
-        const int e = base + lane;
+// The refinement of this lane's queued centre, base + lane, of n in all.
+__device__ __forceinline__ Refined strip_refine(float (*q)[kQCap], int base, int n, const DetParams& dp) {
+    Refined r{};
+    const int e = base + (threadIdx.x & 63);
+    if (e < n) {
         float v[9];
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = q[i][e];
@@ -256,18 +259,50 @@ __device__ __forceinline__ void strip_flush(float (*q)[kQCap], int base, int n, 
 #pragma unroll
         for (int i = 5; i < 9; ++i) v[i] = q[i - 1][e];
         const int xy = __float_as_int(q[11][e]);
-        gx = xy & 0xffff;
-        gy = xy >> 16;
-        keep = refine_v(v, q[8][e], q[9][e], q[10][e], dp, c);
+        r.gx = xy & 0xffff;
+        r.gy = xy >> 16;
+        r.keep = refine_v(v, q[8][e], q[9][e], q[10][e], dp, r.c);
     }
-    emit(keep, c, gx, gy, job, out);
+    return r;
 }
 
-// Refines everything queued (in passes of 64) and empties the queue.
+// Refines everything queued (in passes of 64), appends the survivors to the
+// image's candidates and empties the queue.  Every lane of the wave calls it.
 __device__ __forceinline__ void strip_drain(float (*q)[kQCap], int& qn, const DetTile& job, const DetParams& dp,
                                             const DetOut& out) {
-    for (int base = 0; base < qn; base += 64) strip_flush(q, base, min(64, qn - base), job, dp, out);
+    for (int base = 0; base < qn; base += 64) emit(strip_refine(q, base, qn, dp), job, out);
     qn = 0;
+}
+
+// What the four strips of a workgroup have left in their queues, appended
+// with one atomic for all those of one image (a large image's strips would
+// otherwise queue up at its counter: 5,600 additions of 7 ns for 4000x3000
+// pixels).  Every lane of the workgroup calls it.
+__device__ __forceinline__ void workgroup_drain(float (*q)[kQCap], int qn, const DetTile& job, const DetParams& dp,
+                                                const DetOut& out) {
+    __shared__ int cnt_s[4], img_s[4], base_s[4];
+    static_assert(kQCap <= 128, "two passes");
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const Refined r0 = strip_refine(q, 0, qn, dp), r1 = strip_refine(q, 64, qn, dp);
+    const uint64_t m0 = __ballot(r0.keep), m1 = __ballot(r1.keep);
+    if (lane == 0) {
+        cnt_s[wave] = __popcll(m0) + __popcll(m1);
+        img_s[wave] = job.image;
+    }
+    __syncthreads();
+    if (lane == 0 && (wave == 0 || img_s[wave - 1] != job.image)) {
+        // the first wave of an image's run (strips are image by image)
+        int sum = 0;
+        for (int w = wave; w < 4 && img_s[w] == job.image; ++w) sum += cnt_s[w];
+        base_s[wave] = sum ? atomicAdd(&out.cnt[job.image * kCntStride], sum) : 0;
+    }
+    __syncthreads();
+    int before = 0, first = wave;
+    while (first > 0 && img_s[first - 1] == job.image) before += cnt_s[--first];
+    const int base = base_s[first] + before;
+    const uint64_t lower = (1ull << lane) - 1ull;
+    if (r0.keep) store_candidate(r0, base + __popcll(m0 & lower), job, out);
+    if (r1.keep) store_candidate(r1, base + __popcll(m0) + __popcll(m1 & lower), job, out);
 }
 
 // Centre tests of one row y from the coefficients of rows y-1, y, y+1;
@@ -317,13 +352,15 @@ __device__ __forceinline__ void strip_centres(const float4& aU, const float4& aM
 // cell holding (x 2^o, y 2^o) / 4 is set, unless more than gate.fmax of the
 // image's cells have bit o set, or o is beyond the gate's kCnnHeads bits
 // (then the octave is examined densely).
+// Returns how many strict extrema are left in the wave's queue.
 template <bool GATED>
-__device__ __forceinline__ void detect_strip(const float* __restrict__ pyr, const DetTile& job, const DetParams& dp,
+__device__ __forceinline__ int detect_strip(const float* __restrict__ pyr, const DetTile& job, int strip_h,
+                                             const DetParams& dp,
                                              const GateParams& gate, float (*q)[kQCap], const DetOut& out) {
-    static_assert(kStripH <= 64, "one activity bit per strip row");
+    static_assert(kDetStripH <= 64, "one activity bit per strip row");
     const int lane = threadIdx.x & 63;
     const int x0 = job.tx0, y0 = job.ty0;
-    const int xend = min(x0 + kStripW, job.w - dp.border), yend = min(y0 + kStripH, job.h - dp.border);
+    const int xend = min(x0 + kStripW, job.w - dp.border), yend = min(y0 + strip_h, job.h - dp.border);
     const int gx = x0 - 2 + lane;
     const bool col_ok = lane >= 2 && gx < xend;
     // bit i: this lane's centre on row y0 + i is examined
@@ -342,7 +379,7 @@ __device__ __forceinline__ void detect_strip(const float* __restrict__ pyr, cons
                     rows_on |= (uint64_t)((m[(int64_t)cy * cg.W4] >> job.octave) & 1) << (y - y0);
                 }
             }
-            if (!__ballot(rows_on != 0ull)) return;   // nothing active: the strip is not even loaded
+            if (!__ballot(rows_on != 0ull)) return 0;   // nothing active: the strip is not even loaded
         }
     }
     const StripPlanes col = strip_planes(pyr, job, gx);
@@ -374,7 +411,7 @@ __device__ __forceinline__ void detect_strip(const float* __restrict__ pyr, cons
                               gx, y + r, q, qn, job, dp, out);
         }
     }
-    strip_drain(q, qn, job, dp, out);
+    return qn;
 }
 
 // Requests one strip index from this XCD's work counter; the value arrives
@@ -403,34 +440,35 @@ __device__ __forceinline__ int fetch_strip(int32_t* __restrict__ ctr) {
 // share their halo rows through its L2.
 template <bool GATED, bool PERSISTENT>
 __global__ __launch_bounds__(256) void k_detect_strip(const float* __restrict__ pyr, const DetTile* __restrict__ strips,
-                                                      int nstrips, DetParams dp, GateParams gate,
+                                                      int nstrips, int strip_h, DetParams dp, GateParams gate,
                                                       int32_t* __restrict__ work, DetOut out) {
     __shared__ float queue[4][kQFields][kQCap];
     const int wave = threadIdx.x >> 6;
     if constexpr (!PERSISTENT) {
         const int sidx = __builtin_amdgcn_readfirstlane(xcd_remap(blockIdx.x, gridDim.x) * 4 + wave);
-        if (sidx >= nstrips) return;   // uniform over the wave; there are no barriers
-        const DetTile job = strips[sidx];
-        detect_strip<GATED>(pyr, job, dp, gate, queue[wave], out);
+        const DetTile job = strips[min(sidx, nstrips - 1)];
+        const int qn = sidx < nstrips ? detect_strip<GATED>(pyr, job, strip_h, dp, gate, queue[wave], out) : 0;
+        workgroup_drain(queue[wave], qn, job, dp, out);   // (the only barriers)
     } else {
         const int x = blockIdx.x % kXcds;
         const int per = nstrips / kXcds, rem = nstrips % kXcds;
         const int base = x * per + min(x, rem), cnt = per + (x < rem ? 1 : 0);
-        int32_t* ctr = work + x;
+        int32_t* ctr = work + x * kCntStride;
         int pending = fetch_strip(ctr);
         for (;;) {
             const int t = __builtin_amdgcn_readfirstlane(pending);
             if (t >= cnt) break;   // uniform over the wave; there are no barriers
             pending = fetch_strip(ctr);
             const DetTile job = strips[base + t];
-            detect_strip<GATED>(pyr, job, dp, gate, queue[wave], out);
+            int qn = detect_strip<GATED>(pyr, job, strip_h, dp, gate, queue[wave], out);
+            strip_drain(queue[wave], qn, job, dp, out);
         }
     }
 }
 
 __global__ void k_clear(int32_t* p, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
+    if (i < n) p[i * kCntStride] = 0;
 }
 
 constexpr int FIN_THREADS = 1024;
@@ -719,7 +757,7 @@ __global__ __launch_bounds__(FIN_THREADS) void k_finalize(const cdvs_keypoint* _
     unsigned short* idx = reinterpret_cast<unsigned short*>(key + kCandCap);
 
     const int img = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-    const int n_all = min(cand_cnt[img], cand_capv[img]);
+    const int n_all = min(cand_cnt[img * kCntStride], cand_capv[img]);
     const cdvs_keypoint* c = cand + cand_off[img];
     const int W = wh[2 * img], H = wh[2 * img + 1];
     const int n = min(n_all, kCandCap);
@@ -959,13 +997,13 @@ hipError_t launch_clear(int32_t* p, int n, hipStream_t stream) {
     return hipGetLastError();
 }
 
-hipError_t launch_detect_strips(const float* pyr, const DetTile* strips, int nstrips, int variant, int grid,
+hipError_t launch_detect_strips(const float* pyr, const DetTile* strips, int nstrips, int strip_h, int variant, int grid,
                                 const DetParams& dp, const GateParams& gate, int32_t* work, const DetOut& out,
                                 hipStream_t stream) {
     if (nstrips <= 0) return hipSuccess;
 #define DETECT_LAUNCH(G, P, NB)                                                                                    \
-    hipLaunchKernelGGL((k_detect_strip<G, P>), dim3(NB), dim3(256), 0, stream, pyr, strips, nstrips, dp, gate, work, \
-                       out)
+    hipLaunchKernelGGL((k_detect_strip<G, P>), dim3(NB), dim3(256), 0, stream, pyr, strips, nstrips, strip_h, dp, gate, \
+                       work, out)
     if (variant == kDetectPersistent) {
         // a multiple of the XCD count, no larger than one wave per strip
         int g = std::min(grid, (nstrips + 4 * kXcds - 1) / (4 * kXcds) * kXcds);
