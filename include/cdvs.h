@@ -238,7 +238,8 @@ cdvs_status cdvs_graph_launch(cdvs_ctx* ctx, void* stream);
 
 /* Autotuning of two kernels on the context's batch.  CDVS_KERNEL_SCALES has
  * CDVS_TUNE_VARIANTS tile shapes (64x32, 128x16, 32x32, 64x16; every shape
- * produces bit-identical planes); CDVS_KERNEL_DETECT has
+ * produces bit-identical planes; octaves of fewer than 256 tiles always take
+ * 64x16); CDVS_KERNEL_DETECT has
  * CDVS_DETECT_VARIANTS launch forms (0: one wave per strip, dispatched by the
  * hardware; 1: persistent, a fixed grid pulling strips from per-XCD work
  * counters; both find the same candidates).  cdvs_autotune times each

@@ -668,14 +668,14 @@ cdvs_status cdvs_pyramid(cdvs_ctx* ctx, const uint8_t* d_images, float* d_pyr, v
     hipStream_t s = (hipStream_t)stream;
     {
         Bracket b(ctx, CDVS_KERNEL_PREBLUR, s);
+        const int v = blur_shape(kPreblurVariant, ctx->blur_tiles[kPreblurVariant][0]);
         HIP_OR_FAIL(ctx, launch_preblur(d_images, d_pyr, ctx->d_jobs + ctx->job_start[0],
-                                        ctx->d_blur_owner + ctx->blur_owner_start[kPreblurVariant][0],
-                                        ctx->blur_tiles[kPreblurVariant][0],
+                                        ctx->d_blur_owner + ctx->blur_owner_start[v][0], ctx->blur_tiles[v][0], v,
                                         ctx->taps, s));
     }
     for (int o = 0; o < ctx->max_oct; ++o) {
         Bracket b(ctx, CDVS_KERNEL_SCALES, s);
-        const int v = ctx->blur_variant;
+        const int v = blur_shape(ctx->blur_variant, ctx->blur_tiles[ctx->blur_variant][o]);
         HIP_OR_FAIL(ctx, launch_scales(d_pyr, ctx->d_jobs + ctx->job_start[o],
                                        ctx->d_blur_owner + ctx->blur_owner_start[v][o], ctx->blur_tiles[v][o], v,
                                        ctx->taps, s));

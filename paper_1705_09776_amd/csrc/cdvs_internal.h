@@ -211,11 +211,18 @@ constexpr int kBlurTilings = 5;
 constexpr int kBlurV = 8;
 __host__ __device__ constexpr int blur_tw(int v) { return v == 1 || v == 4 ? 128 : v == 2 ? 32 : 64; }
 __host__ __device__ constexpr int blur_th(int v) { return v == 1 || v == 3 ? 16 : 32; }
+// An octave of fewer tiles than this leaves compute units without any, and its
+// time is that of one tile, so it takes the small shape (64 x 16) instead of
+// the one its context has chosen (planes are the same in every shape): one
+// 640x480 image 98 -> 93 us for the whole pass, 4000x3000 338 -> 332; at 512
+// and 1024 the same, and 256 images unchanged (1856 to 1867 throughout).
+constexpr int kBlurFewTiles = 256, kBlurSmallShape = 3;
+constexpr int blur_shape(int chosen, int tiles) { return tiles < kBlurFewTiles ? kBlurSmallShape : chosen; }
 static_assert(sizeof(OctJob::tiles_x_blur) / sizeof(int32_t) == kBlurTilings, "one tiling per blur tile shape");
 
 // Launchers (each enqueues on `stream`, returns the launch error).
 hipError_t launch_preblur(const uint8_t* images, float* pyr, const OctJob* jobs, const int32_t* owner, int ntiles,
-                          const Taps& taps, hipStream_t stream);
+                          int variant, const Taps& taps, hipStream_t stream);
 hipError_t launch_scales(float* pyr, const OctJob* jobs, const int32_t* owner, int ntiles, int variant,
                          const Taps& taps, hipStream_t stream);
 hipError_t launch_clear(int32_t* p, int n, hipStream_t stream);   // n counters, kCntStride apart
