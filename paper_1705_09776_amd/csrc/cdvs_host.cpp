@@ -42,9 +42,10 @@ struct cdvs_ctx {
     float dedup_ratio = 0.f;
     int wgrad_grid = 0;   // grid of the CNN weight-gradient kernels
     int detect_grid = 0;  // persistent detection grid (workgroups)
+    bool det_unfinished = false;  // a call ended between the detection and the finalisation that clears its counters
     // surrogate CNN cell grid
     std::vector<CnnImage> cnn;
-    int64_t ncells = 0;
+    int64_t ncells = 0, max_cells = 0;   // of the batch, of the largest image
     int cnn_ftiles = 0;
     CnnImage* d_cnn = nullptr;
     int32_t* d_active = nullptr;  // [n][kMaxOctaves] active mask cells
@@ -462,6 +463,7 @@ static cdvs_status build_layout(cdvs_ctx* c) {
         ftiles += g.ftiles_x * ((g.H4 + kCnnFusedH - 1) / kCnnFusedH);
         c->cnn_owner.resize(ftiles, i);
         cell += (int64_t)g.H4 * g.W4;
+        c->max_cells = std::max(c->max_cells, (int64_t)g.H4 * g.W4);
     }
     c->ncells = cell;
     c->cnn_ftiles = ftiles;
@@ -616,6 +618,7 @@ cdvs_status cdvs_ctx_create(const cdvs_params* params, const cdvs_image_desc* im
         (e = hipMemcpy(c->d_cand_capv, c->cand_cap.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice)) !=
             hipSuccess ||
         (e = hipMemset(c->d_flags, 0, sizeof(int32_t))) != hipSuccess ||
+        (e = hipMemset(c->d_active, 0, sizeof(int32_t) * n * kMaxOctaves)) != hipSuccess ||
         (e = hipMemset(c->d_cand_cnt, 0, sizeof(int32_t) * (n + kXcds) * kCntStride)) != hipSuccess) {
         fail(nullptr, CDVS_ERR_HIP, "context upload: %s", hipGetErrorString(e));
         cdvs_ctx_destroy(c);
@@ -706,14 +709,15 @@ cdvs_status cdvs_alp_detect(cdvs_ctx* ctx, const float* d_pyr, const uint8_t* d_
     if (((uintptr_t)d_pyr & 255) != 0) return fail(ctx, CDVS_ERR_ARG, "cdvs_alp_detect: d_pyr not 256-byte aligned");
     hipStream_t s = (hipStream_t)stream;
     GateParams gate{nullptr, nullptr, nullptr, 1.f};
+    if (ctx->det_unfinished) {
+        HIP_OR_FAIL(ctx, launch_clear(ctx->d_cand_cnt, ctx->n + kXcds, kCntStride, s));
+        HIP_OR_FAIL(ctx, launch_clear(ctx->d_active, ctx->n * kMaxOctaves, 1, s));
+    }
+    ctx->det_unfinished = true;
     if (d_mask) {
         Bracket b(ctx, CDVS_KERNEL_MASK_COUNT, s);
-        HIP_OR_FAIL(ctx, launch_mask_count(d_mask, ctx->d_cnn, ctx->n, ctx->d_active, s));
+        HIP_OR_FAIL(ctx, launch_mask_count(d_mask, ctx->d_cnn, ctx->n, ctx->max_cells, ctx->d_active, s));
         gate = GateParams{d_mask, ctx->d_active, ctx->d_cnn, ctx->params.mask_fmax};
-    }
-    {
-        Bracket b(ctx, CDVS_KERNEL_CLEAR, s);
-        HIP_OR_FAIL(ctx, launch_clear(ctx->d_cand_cnt, ctx->n + kXcds, s));   // counts and work counters
     }
     {
         // one launch over the strips of every octave; the finalisation does
@@ -725,9 +729,10 @@ cdvs_status cdvs_alp_detect(cdvs_ctx* ctx, const float* d_pyr, const uint8_t* d_
     {
         Bracket b(ctx, CDVS_KERNEL_FINALIZE, s);
         HIP_OR_FAIL(ctx, launch_finalize(ctx->d_cand, ctx->d_absp, ctx->d_cand_cnt, ctx->d_cand_off, ctx->d_cand_capv,
-                                         ctx->d_sel, ctx->d_wh, ctx->n, ctx->dedup_ratio, ctx->params.topk, ctx->kp_cap, d_kp,
+                                         d_mask ? ctx->d_active : nullptr, ctx->d_sel, ctx->d_wh, ctx->n, ctx->dedup_ratio, ctx->params.topk, ctx->kp_cap, d_kp,
                                          d_count, ctx->d_flags, s));
     }
+    ctx->det_unfinished = false;
     return CDVS_OK;
 }
 
@@ -1180,7 +1185,7 @@ cdvs_status cdvs_autotune(cdvs_ctx* ctx, const uint8_t* d_images, float* d_pyr, 
             kDetectVariants,
             [&](int var) -> cdvs_status {
                 const GateParams gate{nullptr, nullptr, nullptr, 1.f};
-                HIP_OR_FAIL(ctx, launch_clear(ctx->d_cand_cnt, ctx->n + kXcds, s));
+                HIP_OR_FAIL(ctx, launch_clear(ctx->d_cand_cnt, ctx->n + kXcds, kCntStride, s));
                 HIP_OR_FAIL(ctx, launch_detect_strips(d_pyr, ctx->d_strips, (int)ctx->strips.size(), ctx->strip_h, var,
                                                       ctx->detect_grid, ctx->det, gate, ctx->d_cand_cnt + ctx->n * kCntStride, det_out(ctx),
                                                       s));
@@ -1188,6 +1193,9 @@ cdvs_status cdvs_autotune(cdvs_ctx* ctx, const uint8_t* d_images, float* d_pyr, 
             },
             dus);
         if (st == CDVS_OK) best_dv = argmin(dus, kDetectVariants);
+        // as the finalisation would have left them
+        const hipError_t ec = launch_clear(ctx->d_cand_cnt, ctx->n + kXcds, kCntStride, s);
+        if (st == CDVS_OK && ec != hipSuccess) st = fail(ctx, CDVS_ERR_HIP, "cdvs_autotune: %s", hipGetErrorString(ec));
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);

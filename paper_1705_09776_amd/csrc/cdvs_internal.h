@@ -225,7 +225,7 @@ hipError_t launch_preblur(const uint8_t* images, float* pyr, const OctJob* jobs,
                           int variant, const Taps& taps, hipStream_t stream);
 hipError_t launch_scales(float* pyr, const OctJob* jobs, const int32_t* owner, int ntiles, int variant,
                          const Taps& taps, hipStream_t stream);
-hipError_t launch_clear(int32_t* p, int n, hipStream_t stream);   // n counters, kCntStride apart
+hipError_t launch_clear(int32_t* p, int n, int stride, hipStream_t stream);   // n words, stride apart
 // Detection over strips of 60 x strip_h centres inside the detection border
 // (tx0, ty0 = the strip's first centre), one wave at a time each; gated by
 // gate.mask unless it is null.  A wave takes a strip's rows one after the
@@ -250,8 +250,10 @@ hipError_t launch_detect_strips(const float* pyr, const DetTile* strips, int nst
 // absp (|p| per candidate) and lists (kCandCap indices per image) are used by
 // images with more candidates than kCandCap (both may be null when no image's
 // capacity exceeds it); wh: per image width and height.
-hipError_t launch_finalize(const cdvs_keypoint* cand, const float* absp, const int32_t* cand_cnt, const int64_t* cand_off,
-                           const int32_t* cand_capv, uint32_t* lists, const int32_t* wh, int n_images,
+// cand_cnt and active (null without a gate) are left at zero for the next
+// detection, cand_cnt's kXcds work counters (after the images') too.
+hipError_t launch_finalize(const cdvs_keypoint* cand, const float* absp, int32_t* cand_cnt, const int64_t* cand_off,
+                           const int32_t* cand_capv, int32_t* active, uint32_t* lists, const int32_t* wh, int n_images,
                            float dedup_ratio, int topk, int kp_cap, cdvs_keypoint* kp, int32_t* count, int32_t* flags,
                            hipStream_t stream);
 hipError_t launch_orient(const float* pyr, const OctGeom* geom, const cdvs_keypoint* kp, const int32_t* count,
@@ -276,7 +278,10 @@ hipError_t launch_cnn_adam(float* p, const float* g, float* m, float* v, int ste
                            float eps, hipStream_t s);
 hipError_t launch_cnn_labels(const cdvs_keypoint* kp, const int32_t* count, int kp_cap, const CnnImage* imgs, int nimg,
                              int64_t ncells, uint32_t* labels, hipStream_t s);
-hipError_t launch_mask_count(const uint8_t* mask, const CnnImage* imgs, int nimg, int32_t* active, hipStream_t s);
+// Adds to active (kMaxOctaves per image), which must be zero at launch;
+// max_cells: of the largest image.
+hipError_t launch_mask_count(const uint8_t* mask, const CnnImage* imgs, int nimg, int64_t max_cells, int32_t* active,
+                             hipStream_t s);
 
 // SCFV aggregation: 512 components of 32 dimensions; per-call constants
 // derived from the model (B = [M./V, -1/(2V)] per component, c, 1/sqrt(w),

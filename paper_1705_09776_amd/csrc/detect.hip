@@ -466,9 +466,9 @@ __global__ __launch_bounds__(256) void k_detect_strip(const float* __restrict__ 
     }
 }
 
-__global__ void k_clear(int32_t* p, int n) {
+__global__ void k_clear(int32_t* p, int n, int stride) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i * kCntStride] = 0;
+    if (i < n) p[(int64_t)i * stride] = 0;
 }
 
 constexpr int FIN_THREADS = 1024;
@@ -734,10 +734,10 @@ static_assert(kCandCap == 8 * FIN_THREADS, "8 flags per lane");
 
 __global__ __launch_bounds__(FIN_THREADS) void k_finalize(const cdvs_keypoint* __restrict__ cand,
                                                           const float* __restrict__ absp,
-                                                          const int32_t* __restrict__ cand_cnt,
+                                                          int32_t* __restrict__ cand_cnt,
                                                           const int64_t* __restrict__ cand_off,
                                                           const int32_t* __restrict__ cand_capv,
-                                                          uint32_t* __restrict__ lists,
+                                                          int32_t* __restrict__ active, uint32_t* __restrict__ lists,
                                                           const int32_t* __restrict__ wh, float ratio_lim, int topk,
                                                           int kp_cap, cdvs_keypoint* __restrict__ kp,
                                                           int32_t* __restrict__ count,
@@ -976,7 +976,12 @@ __global__ __launch_bounds__(FIN_THREADS) void k_finalize(const cdvs_keypoint* _
         const int i = idx[r];
         kp[(int64_t)img * kp_cap + r] = c[list ? list[i] : (uint32_t)i];
     }
+    // the counters are left at zero for the next detection (every lane has read
+    // this image's), which saves it a launch of its own for that
+    if (active && tid < kMaxOctaves) active[img * kMaxOctaves + tid] = 0;
+    if (img == 0 && tid < kXcds) cand_cnt[(gridDim.x + tid) * kCntStride] = 0;
     if (tid == 0) {
+        cand_cnt[img * kCntStride] = 0;
         count[img] = m;
         // A reduced image's output is exact when its last kept keypoint is
         // stronger than every candidate that was dropped: each kept one was
@@ -991,9 +996,9 @@ __global__ __launch_bounds__(FIN_THREADS) void k_finalize(const cdvs_keypoint* _
 
 }  // namespace
 
-hipError_t launch_clear(int32_t* p, int n, hipStream_t stream) {
+hipError_t launch_clear(int32_t* p, int n, int stride, hipStream_t stream) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_clear, dim3((n + 255) / 256), dim3(256), 0, stream, p, n);
+    hipLaunchKernelGGL(k_clear, dim3((n + 255) / 256), dim3(256), 0, stream, p, n, stride);
     return hipGetLastError();
 }
 
@@ -1023,13 +1028,13 @@ hipError_t launch_detect_strips(const float* pyr, const DetTile* strips, int nst
     return hipGetLastError();
 }
 
-hipError_t launch_finalize(const cdvs_keypoint* cand, const float* absp, const int32_t* cand_cnt, const int64_t* cand_off,
-                           const int32_t* cand_capv, uint32_t* lists, const int32_t* wh, int n_images,
+hipError_t launch_finalize(const cdvs_keypoint* cand, const float* absp, int32_t* cand_cnt, const int64_t* cand_off,
+                           const int32_t* cand_capv, int32_t* active, uint32_t* lists, const int32_t* wh, int n_images,
                            float dedup_ratio, int topk, int kp_cap, cdvs_keypoint* kp, int32_t* count, int32_t* flags,
                            hipStream_t stream) {
     if (n_images <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_finalize, dim3(n_images), dim3(FIN_THREADS), 0, stream, cand, absp, cand_cnt, cand_off,
-                       cand_capv, lists, wh, dedup_ratio, topk, kp_cap, kp, count, flags);
+                       cand_capv, active, lists, wh, dedup_ratio, topk, kp_cap, kp, count, flags);
     return hipGetLastError();
 }
 
