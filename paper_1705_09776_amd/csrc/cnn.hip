@@ -71,14 +71,21 @@ __device__ __forceinline__ int find_cell_image(const CnnImage* im, int n, int64_
 // had a kernel per layer, whose waves loaded and converted all the layer's
 // weights for 16 cells each, and for the first layer divided every pixel by
 // 255 nine times over: 182 us for the forward pass of 614,400 cells, now
-// 53 us.)  The workgroup stages the s2d input over the block
+// 43 us.)  The workgroup stages the s2d input over the block
 // plus a 4-cell halo (one cell per layer) and each layer writes its output
 // over a region one cell smaller on every side, so the last layer covers
 // exactly the block.  Cells outside the image are written as zeros at every
 // layer, which is the zero padding of each convolution.
 constexpr int FTW = kCnnFusedW, FTH = kCnnFusedH, FHALO = kCnnLayers;
 constexpr int FFW = FTW + 2 * FHALO, FFH = FTH + 2 * FHALO;   // 40 x 24 frame
-constexpr int FSTR = CC;                                       // shorts per cell (32 B, 16-byte aligned reads)
+// A cell's two halves of 8 channels lie in two planes, 16 bytes per cell each:
+// the 16 lanes of a B operand that read neighbouring cells' halves then read
+// 256 consecutive bytes (32 bytes apart, half of them meet in a bank).  With the cells stepped on by constants instead
+// of divided out, whole cells staged per lane and the head's weights read as
+// scalars this took the kernel from about 179 to 151 us on 128 images of
+// 640x480 (gated batch 888 -> 859 us) and from 48 to 43 us on 32 in training.
+constexpr int FSTR = CC / 2;              // shorts per cell of a plane
+constexpr int FPLANE = FFH * FFW * FSTR;  // shorts per plane
 
 
 // MFMA weight fragments of all layers, packed once per forward call:
@@ -95,7 +102,7 @@ __global__ void k_cnn_pack(const float* __restrict__ P, short* __restrict__ frag
 }
 
 constexpr int FTHREADS = 512;                       // 8 waves: twice the latency hiding of 4 at the same LDS
-constexpr int FSTAGE = (FFH * FFW * 4 + FTHREADS - 1) / FTHREADS;   // 4-pixel cell rows staged per lane
+constexpr int FSTAGE = (FFH * FFW + FTHREADS - 1) / FTHREADS;   // cells staged per lane
 
 template <bool ACTS>
 __global__ __launch_bounds__(FTHREADS, 2) void k_cnn_infer(const uint8_t* __restrict__ images, const float* __restrict__ P,
@@ -104,109 +111,124 @@ __global__ __launch_bounds__(FTHREADS, 2) void k_cnn_infer(const uint8_t* __rest
                                                       const int32_t* __restrict__ owner, short* __restrict__ acts,
                                                       int64_t ncells, float* __restrict__ logits,
                                                       uint8_t* __restrict__ mask, float zthr) {
-    __shared__ __align__(16) short buf[2][FFH * FFW * FSTR];
-    __shared__ short lut[256];
-    __shared__ float head[CC * NHD + NHD];
+    __shared__ __align__(16) short buf[2][2 * FPLANE];
     const int tile = xcd_remap(blockIdx.x, gridDim.x);
-    const CnnImage& g = imgs[owner[tile]];   // per-tile owner table: one load, no search
+    const CnnImage g = imgs[owner[tile]];   // per-tile owner table: one load, no search
     const int lt = tile - g.ftile0;
     const int ty0 = (lt / g.ftiles_x) * FTH, tx0 = (lt % g.ftiles_x) * FTW;
     const int oy = ty0 - FHALO, ox = tx0 - FHALO;   // image cell of frame (0, 0)
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, kb = lane >> 4;
-    const int H4 = g.H4, W4 = g.W4;   // read once (the layer loops test every cell against them)
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, kb = lane >> 4, li = lane & 15;
+    const int H4 = g.H4, W4 = g.W4;
+    // the whole frame lies inside the image (whole cells of it): no cell needs
+    // a test
+    const bool inside = oy >= 0 && ox >= 0 && 4 * (oy + FFH) <= g.H && 4 * (ox + FFW) <= g.W;   // uniform
+    const uint8_t* img = images + g.src;
+    const bool words = ((g.src | g.src_pitch | (int64_t)(uintptr_t)images) & 3) == 0;            // uniform
 
-    // u8 -> bf16(u / 255) table
-    if (threadIdx.x < 256) lut[threadIdx.x] = f2bf((float)threadIdx.x / 255.f);
-    for (int i = threadIdx.x; i < CC * NHD + NHD; i += blockDim.x) head[i] = P[kCnnLayers * LAYER_P + i];
-    // layer 0 input: s2d of the frame, zero outside the image.  Lanes take
-    // consecutive cells of one pixel row (contiguous 4-byte groups); all
-    // loads are issued before the first conversion.
-    uint32_t px[FSTAGE];
+    // layer 0 input: s2d of the frame, zero outside the image.  A lane takes
+    // whole cells (four rows of four pixels; neighbouring lanes neighbouring
+    // cells); all loads are issued before the first conversion.
+    uint32_t px[FSTAGE][4];
 #pragma unroll
     for (int k = 0; k < FSTAGE; ++k) {
-        const int it = threadIdx.x + k * FTHREADS;
-        const int fx = it % FFW, r4 = (it / FFW) & 3, fy = it / (FFW * 4);
-        const int cy = oy + fy, cx = ox + fx;
-        px[k] = 0;
-        if (it < FFH * FFW * 4 && cy >= 0 && cy < H4 && cx >= 0 && cx < W4) {
-            const int y = min(4 * cy + r4, g.H - 1);
-            const uint8_t* row = images + g.src + (int64_t)y * g.src_pitch;
-            const int x0 = 4 * cx;
-            if (x0 + 3 < g.W && ((uintptr_t)(row + x0) & 3) == 0) {
-                px[k] = *reinterpret_cast<const uint32_t*>(row + x0);
-            } else {
+        const int it = min((int)threadIdx.x + k * FTHREADS, FFH * FFW - 1);
+        const int cy = oy + it / FFW, cx = ox + it % FFW;
+        if (inside && words) {
+            const uint8_t* p = img + (int64_t)(4 * cy) * g.src_pitch + 4 * cx;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) px[k] |= (uint32_t)row[min(x0 + j, g.W - 1)] << (8 * j);
+            for (int r = 0; r < 4; ++r) px[k][r] = *reinterpret_cast<const uint32_t*>(p + (int64_t)r * g.src_pitch);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                px[k][r] = 0;
+                if (cy >= 0 && cy < H4 && cx >= 0 && cx < W4) {
+                    const uint8_t* row = img + (int64_t)min(4 * cy + r, g.H - 1) * g.src_pitch;
+                    const int x0 = 4 * cx;
+                    if (words && x0 + 3 < g.W) {
+                        px[k][r] = *reinterpret_cast<const uint32_t*>(row + x0);
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) px[k][r] |= (uint32_t)row[min(x0 + j, g.W - 1)] << (8 * j);
+                    }
+                }
             }
         }
     }
-    __syncthreads();   // lut
-#pragma unroll
-    for (int k = 0; k < FSTAGE; ++k) {
-        const int it = threadIdx.x + k * FTHREADS;
-        if (it >= FFH * FFW * 4) break;
-        const int fx = it % FFW, r4 = (it / FFW) & 3, fy = it / (FFW * 4);
-        const int cy = oy + fy, cx = ox + fx;
-        s4 v = {0, 0, 0, 0};
-        if (cy >= 0 && cy < H4 && cx >= 0 && cx < W4) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = lut[(px[k] >> (8 * j)) & 255u];
-        }
-        *reinterpret_cast<s4*>(&buf[0][(fy * FFW + fx) * FSTR + 4 * r4]) = v;
-    }
-    const int half = kb >> 1, c8 = (kb & 1) * 8;
+    const int half = kb >> 1;
     s8 a[kTapPairs];
+    f4 bias;
     const s8* fr = reinterpret_cast<const s8*>(frag);
 #pragma unroll
     for (int m = 0; m < kTapPairs; ++m) a[m] = fr[m * 64 + lane];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) bias[r] = P[CONV_W + 4 * kb + r];
+#pragma unroll
+    for (int k = 0; k < FSTAGE; ++k) {
+        const int it = threadIdx.x + k * FTHREADS;
+        if (it < FFH * FFW) {
+            // (u * (1 / 255) and u / 255 round to the same bf16 for every u8;
+            // a cell outside the image holds zero bytes)
+            uint32_t w[8];
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    w[2 * r + j] = f2bf2((float)((px[k][r] >> (16 * j)) & 255u) * (1.f / 255.f),
+                                         (float)((px[k][r] >> (16 * j + 8)) & 255u) * (1.f / 255.f));
+            uint4* d = reinterpret_cast<uint4*>(&buf[0][it * FSTR]);
+            d[0] = make_uint4(w[0], w[1], w[2], w[3]);
+            d[FPLANE / 8] = make_uint4(w[4], w[5], w[6], w[7]);
+        }
+    }
     __syncthreads();
 
-    // The layers are unrolled, so each layer's output region is a constant
-    // and a cell index splits into (row, column) by constant division.  A
-    // lane's B operand of tap pair m is read at a per-lane base plus a
-    // constant offset: the base points at tap 0 of its cell (the cell at
-    // (-1, -1)), shifted for the lanes carrying the pair's second tap by
-    // that tap's distance from the first, which is one cell for pairs 0, 2
-    // and 3 and FFW - 2 cells for pair 1; pair 4's second tap is zero.  All
-    // ten loads of a step are issued before its MFMAs.
-    const int c8b = 2 * c8;                 // byte offset of this lane's 8 channels
+    // The layers are unrolled, so each layer's output region is a constant.  A
+    // lane's cell is stepped on by constants from one pair of 16-cell groups
+    // to the wave's next, with its offset in a plane; the B operand of tap
+    // pair m is read at one of three per-lane bases plus a constant: tap 0 of
+    // the cell (the cell at (-1, -1)), shifted for the lanes that carry the
+    // pair's second tap by that tap's distance from the first, which is one
+    // cell for pairs 0, 2 and 3 and FFW - 2 cells for pair 1, and not at all
+    // for pair 4, whose second tap is zero.  All ten loads of a step are
+    // issued before its MFMAs.
+    constexpr int CB = FSTR * 2;            // bytes per cell of a plane
+    constexpr int STEP = 32 * (FTHREADS / 64);
 #pragma unroll
     for (int l = 0; l < kCnnLayers; ++l) {
-        f4 bias;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) bias[r] = P[l * LAYER_P + CONV_W + 4 * kb + r];
         // the next layer's fragments load while this layer computes
         s8 an[kTapPairs];
+        f4 bn;
         const int ln = l + 1 < kCnnLayers ? l + 1 : l;
 #pragma unroll
         for (int m = 0; m < kTapPairs; ++m) an[m] = fr[(ln * kTapPairs + m) * 64 + lane];
-        const char* X = reinterpret_cast<const char*>(buf[l & 1]);
-        short* Y = buf[(l + 1) & 1];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) bn[r] = P[ln * LAYER_P + CONV_W + 4 * kb + r];
+        const char* X = reinterpret_cast<const char*>(buf[l & 1]) + (kb & 1) * (FPLANE * 2);
+        const char* XA = X + half * CB;
+        const char* XB = X + half * (FFW - 2) * CB;
+        char* Y = reinterpret_cast<char*>(buf[(l + 1) & 1]) + half * (FPLANE * 2) + 8 * (kb & 1) + (FFW + 1) * CB;
         const int lo = l + 1, C = FFW - 2 * lo, n = (FFH - 2 * lo) * C;
-        constexpr int CB = FSTR * 2;        // bytes per cell
         // tap t = 3 (dy + 1) + (dx + 1) at byte offset (dy + 1) FFW CB + (dx + 1) CB from tap 0
         auto toff = [](int t) { return ((t / 3) * FFW + t % 3) * CB; };
-        for (int q0 = wave * 32; q0 < n; q0 += 32 * (FTHREADS / 64)) {
-            int fy[2], fx[2];
-            const char* pa[2];
-            const char* pb[2];
+        int fy[2], fx[2], off[2];
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int q = min(q0 + 16 * h + (lane & 15), n - 1);
-                fy[h] = lo + q / C;
-                fx[h] = lo + q % C;
-                const char* base = X + ((fy[h] - 1) * FFW + fx[h] - 1) * CB + c8b;
-                pa[h] = base + half * CB;
-                pb[h] = base + half * (FFW - 2) * CB;
-            }
+        for (int h = 0; h < 2; ++h) {
+            const int q = min(wave * 32 + 16 * h + li, n - 1);
+            fy[h] = lo + q / C;
+            fx[h] = lo + q % C;
+            off[h] = ((fy[h] - 1) * FFW + fx[h] - 1) * CB;
+        }
+        for (int q0 = wave * 32; q0 < n; q0 += STEP) {
             s8 b[kTapPairs][2];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                b[0][h] = *reinterpret_cast<const s8*>(pa[h] + toff(0));
-                b[1][h] = *reinterpret_cast<const s8*>(pb[h] + toff(2));
-                b[2][h] = *reinterpret_cast<const s8*>(pa[h] + toff(4));
-                b[3][h] = *reinterpret_cast<const s8*>(pa[h] + toff(6));
-                b[4][h] = *reinterpret_cast<const s8*>(pa[h] - half * CB + toff(8));
+                // (past the region's end: its last cell again, not written)
+                const int o = min(off[h], ((FFH - lo - 2) * FFW + FFW - lo - 2) * CB);
+                b[0][h] = *reinterpret_cast<const s8*>(XA + o + toff(0));
+                b[1][h] = *reinterpret_cast<const s8*>(XB + o + toff(2));
+                b[2][h] = *reinterpret_cast<const s8*>(XA + o + toff(4));
+                b[3][h] = *reinterpret_cast<const s8*>(XA + o + toff(6));
+                b[4][h] = *reinterpret_cast<const s8*>(X + o + toff(8));
             }
             f4 acc[2] = {bias, bias};
 #pragma unroll
@@ -218,52 +240,67 @@ __global__ __launch_bounds__(FTHREADS, 2) void k_cnn_infer(const uint8_t* __rest
                     // non-negative, so those products add exact zeros)
                     acc[h] = mfma32(a[m], b[m][h], acc[h]);
                 }
-            // relu, bf16, zero outside the image: computed for every lane and
-            // selected (no branch per element), one 8-byte store per cell
+            // relu, bf16, zero outside the image (selected, no branch), one
+            // 8-byte store per cell.  Both groups' values are settled before
+            // the first store: a uniform branch right behind the MFMAs was
+            // compiled with 7 wait states up to the first read of their result on
+            // its taken side, where straight-line code gets 8, and read old values.
+            uint2 o[2];
+            bool in[2];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const int cy = oy + fy[h], cx = ox + fx[h];
-                const bool in = (unsigned)cy < (unsigned)H4 && (unsigned)cx < (unsigned)W4;
-                uint2 o;
-                o.x = f2bf2(relu(acc[h][0]), relu(acc[h][1]));
-                o.y = f2bf2(relu(acc[h][2]), relu(acc[h][3]));
-                o.x = in ? o.x : 0u;
-                o.y = in ? o.y : 0u;
-                if (q0 + 16 * h + (lane & 15) < n) {
-                    *reinterpret_cast<uint2*>(&Y[(fy[h] * FFW + fx[h]) * FSTR + 4 * kb]) = o;
+                in[h] = (unsigned)(oy + fy[h]) < (unsigned)H4 && (unsigned)(ox + fx[h]) < (unsigned)W4;
+                o[h].x = f2bf2(relu(acc[h][0]), relu(acc[h][1]));
+                o[h].y = f2bf2(relu(acc[h][2]), relu(acc[h][3]));
+                o[h].x = in[h] ? o[h].x : 0u;
+                o[h].y = in[h] ? o[h].y : 0u;
+            }
+            asm volatile("" : "+v"(o[0].x), "+v"(o[0].y), "+v"(o[1].x), "+v"(o[1].y));
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (q0 + 16 * h + li < n) {
+                    *reinterpret_cast<uint2*>(Y + off[h]) = o[h];
                     // the block's own cells also go out for the backward pass
-                    if (ACTS && in && (unsigned)(fy[h] - FHALO) < (unsigned)FTH && (unsigned)(fx[h] - FHALO) < (unsigned)FTW)
-                        *reinterpret_cast<uint2*>(acts + ((int64_t)l * ncells + g.cell0 + (int64_t)cy * W4 + cx) * CC +
-                                                  4 * kb) = o;
+                    if (ACTS && in[h] && (unsigned)(fy[h] - FHALO) < (unsigned)FTH && (unsigned)(fx[h] - FHALO) < (unsigned)FTW)
+                        *reinterpret_cast<uint2*>(acts + ((int64_t)l * ncells + g.cell0 +
+                                                          (int64_t)(oy + fy[h]) * W4 + ox + fx[h]) * CC + 4 * kb) = o[h];
                 }
+                // the wave's next group
+                fx[h] += STEP % C;
+                fy[h] += STEP / C;
+                const bool wrap = fx[h] >= lo + C;
+                off[h] += (STEP / C * FFW + STEP % C) * CB + (wrap ? (FFW - C) * CB : 0);
+                fx[h] -= wrap ? C : 0;
+                fy[h] += wrap ? 1 : 0;
             }
         }
 #pragma unroll
         for (int m = 0; m < kTapPairs; ++m) a[m] = an[m];
+        bias = bn;
         __syncthreads();
     }
 
-    // head on the last layer's output (kCnnLayers is even: it is in buf[0])
-    const short* X4 = buf[kCnnLayers & 1];
-    for (int q = threadIdx.x; q < FTH * FTW; q += blockDim.x) {
-        const int cy = ty0 + q / FTW, cx = tx0 + q % FTW;
-        if (cy >= H4 || cx >= W4) continue;
-        const short* xs = &X4[((FHALO + q / FTW) * FFW + FHALO + q % FTW) * FSTR];
-        float x[CC];
+    // head on the last layer's output (kCnnLayers is even: it is in buf[0]),
+    // one cell per lane; the weights are the same for every lane
+    static_assert(FTH * FTW == FTHREADS, "one cell per lane");
+    const int hy = threadIdx.x / FTW, hx = threadIdx.x % FTW;
+    if (ty0 + hy >= H4 || tx0 + hx >= W4) return;
+    const uint4* xs = reinterpret_cast<const uint4*>(&buf[kCnnLayers & 1][((FHALO + hy) * FFW + FHALO + hx) * FSTR]);
+    const uint4 xa = xs[0], xb = xs[FPLANE / 8];
+    const uint32_t xw[8] = {xa.x, xa.y, xa.z, xa.w, xb.x, xb.y, xb.z, xb.w};
+    const float* Wh = P + kCnnLayers * LAYER_P;
+    const int64_t c = g.cell0 + (int64_t)(ty0 + hy) * W4 + tx0 + hx;
+    uint32_t bits = 0;
 #pragma unroll
-        for (int ch = 0; ch < CC; ++ch) x[ch] = bf2f(xs[ch]);
-        const int64_t c = g.cell0 + (int64_t)cy * W4 + cx;
-        uint32_t bits = 0;
+    for (int o = 0; o < NHD; ++o) {
+        float z = Wh[CC * NHD + o];
 #pragma unroll
-        for (int o = 0; o < NHD; ++o) {
-            float s = head[CC * NHD + o];
-#pragma unroll
-            for (int ch = 0; ch < CC; ++ch) s = fmaf(x[ch], head[ch * NHD + o], s);
-            if (logits) logits[c * NHD + o] = s;
-            if (o < g.n_oct && s > zthr) bits |= 1u << o;
-        }
-        if (mask) mask[c] = (uint8_t)bits;
+        for (int ch = 0; ch < CC; ++ch)
+            z = fmaf(__uint_as_float(ch & 1 ? xw[ch / 2] & 0xFFFF0000u : xw[ch / 2] << 16), Wh[ch * NHD + o], z);
+        if (logits) logits[c * NHD + o] = z;
+        if (o < g.n_oct && z > zthr) bits |= 1u << o;
     }
+    if (mask) mask[c] = (uint8_t)bits;
 }
 
 __device__ __forceinline__ float softplus(float z) { return fmaxf(z, 0.f) + log1pf(expf(-fabsf(z))); }
