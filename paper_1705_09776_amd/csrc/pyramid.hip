@@ -17,6 +17,8 @@ namespace cdvs {
 
 namespace {
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return min(max(v, lo), hi); }
 
 // Radius of tap set k: 0 = input pre-blur, 1..4 = scale images.
@@ -24,16 +26,30 @@ __host__ __device__ constexpr int radius_of(int k) {
     return k == 0 ? kR0 : k == 1 ? kR1 : k == 2 ? kR2 : k == 3 ? kR3 : kR4;
 }
 
+// A uniform value in a vector register: an fma, add or multiply whose
+// operands all lie in vector registers issues in nearly half the time of one
+// with a scalar operand (2.4 cycles against 4.2 per wave, measured).  (The
+// matrix instructions for f32 gain nothing over them: 10.4 and 35 cycles for
+// 4x4x1 and 16x16x4, during which no other wave's fma issues; both passes
+// on them measured 780 us where these take 600.)
+__device__ __forceinline__ float in_vector(float x) {
+    asm("" : "+v"(x));
+    return x;
+}
+
 // Column pass of tap set K over a register window of V + 2*HALO rows:
 // out[r] = sum_{p=-R..R} g_K[p] * win[r + HALO + p], taps in order p = -R..R.
 template <int K, int HALO, int V>
 __device__ __forceinline__ void column_pass(const float (&win)[V + 2 * HALO], const Taps& taps, float (&out)[V]) {
     constexpr int R = radius_of(K);
+    float g[R + 1];
+#pragma unroll
+    for (int p = 0; p <= R; ++p) g[p] = in_vector(taps.g[K][p + R]);
 #pragma unroll
     for (int r = 0; r < V; ++r) {
         float acc = 0.f;
 #pragma unroll
-        for (int p = -R; p <= R; ++p) acc = fmaf(taps.g[K][p + R], win[r + HALO + p], acc);
+        for (int p = -R; p <= R; ++p) acc = fmaf(g[p < 0 ? -p : p], win[r + HALO + p], acc);
         out[r] = acc;
     }
 }
@@ -46,19 +62,27 @@ template <int HALO, int V, int CP, int TH>
 __device__ __forceinline__ void column_pass_scales(const float (&win)[V + 2 * HALO], const Taps& taps, int row0,
                                                    int scol, float (*T)[TH][CP]) {
     static_assert(HALO >= kR4 && kR4 >= kR3 && kR3 >= kR2 && kR2 >= kR1, "radii");
+    float g1[kR1 + 1], g2[kR2 + 1], g3[kR3 + 1], g4[kR4 + 1];
+#pragma unroll
+    for (int p = 0; p <= kR4; ++p) {
+        if (p <= kR1) g1[p] = in_vector(taps.g[1][kR1 + p]);
+        if (p <= kR2) g2[p] = in_vector(taps.g[2][kR2 + p]);
+        if (p <= kR3) g3[p] = in_vector(taps.g[3][kR3 + p]);
+        g4[p] = in_vector(taps.g[4][kR4 + p]);
+    }
 #pragma unroll
     for (int r = 0; r < V; ++r) {
         const float c = win[r + HALO];
         float pr[kR4 + 1];
 #pragma unroll
         for (int p = 1; p <= kR4; ++p) pr[p] = win[r + HALO + p] + win[r + HALO - p];
-        float a1 = taps.g[1][kR1] * c, a2 = taps.g[2][kR2] * c, a3 = taps.g[3][kR3] * c, a4 = taps.g[4][kR4] * c;
+        float a1 = g1[0] * c, a2 = g2[0] * c, a3 = g3[0] * c, a4 = g4[0] * c;
 #pragma unroll
         for (int p = 1; p <= kR4; ++p) {
-            if (p <= kR1) a1 = fmaf(taps.g[1][kR1 + p], pr[p], a1);
-            if (p <= kR2) a2 = fmaf(taps.g[2][kR2 + p], pr[p], a2);
-            if (p <= kR3) a3 = fmaf(taps.g[3][kR3 + p], pr[p], a3);
-            a4 = fmaf(taps.g[4][kR4 + p], pr[p], a4);
+            if (p <= kR1) a1 = fmaf(g1[p], pr[p], a1);
+            if (p <= kR2) a2 = fmaf(g2[p], pr[p], a2);
+            if (p <= kR3) a3 = fmaf(g3[p], pr[p], a3);
+            a4 = fmaf(g4[p], pr[p], a4);
         }
         T[0][row0 + r][scol] = a1;
         T[1][row0 + r][scol] = a2;
@@ -69,20 +93,33 @@ __device__ __forceinline__ void column_pass_scales(const float (&win)[V + 2 * HA
 
 // Row pass of tap set K for outputs 8 cg .. 8 cg + 7 of one LDS row (row
 // points at column 0 of the T buffer, whose column c is image column
-// x0 - HALO + c).  (A row layout skewed against bank conflicts measured
-// slower: its extra LDS cost a workgroup per CU.)
+// x0 - HALO + c).  A lane's window is read in 16-byte pieces: the 8 lanes that
+// LDS serves at a time then read every other 16 bytes of 256, from different
+// banks, where single words 32 bytes apart met in 8 banks (98 reads of 4
+// bytes per 8 x 4 outputs; 28 of 16 now).  Such reads and taps in vector
+// registers: octave 0 of 256 images 640x480 474 -> 442 us, one image
+// 4000x3000 332 -> 320 us for the whole pass.  What bounds it now: the
+// arithmetic alone is 324 us there and the stores alone 221, in part one
+// after the other.
 template <int K, int HALO>
 __device__ __forceinline__ void row_pass(const float* row, int cg, const Taps& taps, float (&out)[8]) {
     constexpr int R = radius_of(K);
     const float* base = row + 8 * cg;
-    float in[8 + 2 * R];
+    constexpr int F = (HALO - R) & ~3, N = (HALO + R + 8 - F + 3) / 4;   // 16-byte reads from column F on
+    float g[R + 1], in[4 * N];
 #pragma unroll
-    for (int i = 0; i < 8 + 2 * R; ++i) in[i] = base[HALO - R + i];
+    for (int p = 0; p <= R; ++p) g[p] = in_vector(taps.g[K][p + R]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(base + F + 4 * i);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) in[4 * i + j] = v[j];
+    }
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
         float acc = 0.f;
 #pragma unroll
-        for (int p = -R; p <= R; ++p) acc = fmaf(taps.g[K][p + R], in[c + R + p], acc);
+        for (int p = -R; p <= R; ++p) acc = fmaf(g[p < 0 ? -p : p], in[HALO - F + c + p], acc);
         out[c] = acc;
     }
 }
@@ -93,8 +130,6 @@ __device__ __forceinline__ void row_pass(const float* row, int cg, const Taps& t
 // (scale planes 0.660 -> 0.619 ms and detection, which reads them back,
 // 0.507 -> 0.450 ms per 256 images; plain stores of the same values
 // otherwise).
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
 __device__ __forceinline__ void store8(float* dst, int x0, int w, const float (&v)[8]) {
     if (x0 + 8 <= w) {
         const f32x4 a = {v[0], v[1], v[2], v[3]}, b = {v[4], v[5], v[6], v[7]};
@@ -133,9 +168,9 @@ __global__ __launch_bounds__(256) void k_blur(const uint8_t* __restrict__ images
     constexpr int TW = blur_tw(VAR), TH = blur_th(VAR), V = U8 ? 2 * kBlurV : kBlurV;
     static_assert(TH % V == 0 && TW % 8 == 0, "tile shape");
     constexpr int C = TW + 2 * HALO;
-    constexpr int CP = C + 1;
+    constexpr int CP = (C + 3) / 4 * 4;
     constexpr int NG = TH / V;
-    __shared__ float T[NK][TH][CP];
+    __shared__ __align__(16) float T[NK][TH][CP];
 
     const int tile = xcd_remap(blockIdx.x, gridDim.x);
     const OctJob& job = jobs[owner[tile]];   // per-tile owner table: one load, no search
