@@ -168,15 +168,15 @@ struct Nbrs {
     float l, r, d, u;   // (u-1, v), (u+1, v), (u, v-1), (u, v+1)
 };
 
-// (A 32-bit byte offset from the keypoint's plane base: one offset and two
-// additions per pixel instead of four 64-bit addresses.  Row and pitch are
-// below 2^24 (image sides are at most CDVS_MAX_SIDE), so the row offset is a
-// full-rate 24-bit multiply.)
-__device__ __forceinline__ Nbrs load_nbrs(const KpGeom& g, int u, int v) {
+// (One 32-bit byte offset per pixel from four scalar bases, the plane's shifted
+// by one pixel or row each way: no address arithmetic per neighbour.  An
+// interior pixel's neighbours lie in the plane, whose bytes are below 2^32,
+// as sides are at most CDVS_MAX_SIDE.)
+__device__ __forceinline__ Nbrs load_nbrs(const KpGeom& g, uint32_t off) {
     const char* base = reinterpret_cast<const char*>(g.plane);
-    const uint32_t off = (__umul24((uint32_t)v, (uint32_t)g.pitch) + (uint32_t)u) * 4u, dy = 4u * (uint32_t)g.pitch;
-    return Nbrs{*reinterpret_cast<const float*>(base + (off - 4u)), *reinterpret_cast<const float*>(base + (off + 4u)),
-                *reinterpret_cast<const float*>(base + (off - dy)), *reinterpret_cast<const float*>(base + (off + dy))};
+    const int64_t dy = 4 * (int64_t)g.pitch;
+    return Nbrs{*reinterpret_cast<const float*>(base - 4 + off), *reinterpret_cast<const float*>(base + 4 + off),
+                *reinterpret_cast<const float*>(base - dy + off), *reinterpret_cast<const float*>(base + dy + off)};
 }
 
 __device__ __forceinline__ void gradient(const Nbrs& n, float& mag, float& ang) {
@@ -192,9 +192,25 @@ __device__ __forceinline__ void gradient(const Nbrs& n, float& mag, float& ang) 
 // and DescParams .fix) is the largest power of two for which no bin can
 // overflow 32 bits; the host derives it from the window radius (2^14 for the
 // orientation window and 2^12 for the descriptor window at the defaults).
-// Histogram copies per wave: lane l adds into copy l % kCopies; copies are
-// staggered by one bank.
+// Histogram copies per wave: lane l adds into copy l % kCopies; a bin's copies
+// are neighbouring words.  Eight neighbouring lanes, whose pixels mostly share
+// a cell and a bin, then add to eight different banks, and so do lanes of
+// different copies whatever their bins (copies of their own, one bank apart:
+// 5.4 LDS cycles per add against 4.7).  With the walk below and the scalar bases
+// of load_nbrs, 256 images 640x480: k_describe 594 -> 554 us, k_orient 277 ->
+// 264.  What bounds both: vector issue (some 100 operations per pixel, a third
+// of them at half rate) and, for the descriptor, LDS adds about as much; loading
+// a step ahead, 64-bit adds of two bins, and walking the disk's pixels instead
+// of its box's measured 568, 560 and 563 us.
 constexpr int kCopies = 8;
+
+// A bin's sum over the copies.
+__device__ __forceinline__ uint32_t copies_sum(const uint32_t* hist, int bin) {
+    static_assert(kCopies == 8, "two 16-byte reads");
+    const uint4* q = reinterpret_cast<const uint4*>(hist + bin * kCopies);
+    const uint4 a = q[0], b = q[1];
+    return a.x + a.y + a.z + a.w + b.x + b.y + b.z + b.w;
+}
 
 // Keypoints (waves) per workgroup.  Each wave owns its keypoint's histogram
 // outright, so waves never wait for each other: wave_sync() only orders one
@@ -207,19 +223,17 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
 }
-// Orientation histogram copy: 36 bins plus bins 36 and 37, which take the
+// Orientation histogram: 36 bins plus bins 36 and 37, which take the
 // shares of bins 0 and 1 that wrap around (from bin 35, and from an angle
 // of 2 pi, which rounding can give), folded into bins 0 and 1 at the end,
-// so no bin index is wrapped per pixel; the stride of 38 words starts the
-// eight copies on eight different banks.
-constexpr int kOriStride = kOriBins + 2;
-// Descriptor histogram copy: 4 x 4 cells of 9 bins, bin 8 taking the share
+// so no bin index is wrapped per pixel.
+constexpr int kOriHist = kOriBins + 2;
+// Descriptor histogram: 4 x 4 cells of 9 bins, bin 8 taking the share
 // of orientation bin 0 that wraps around from bin 7 (folded into bin 0 at
 // the end, which leaves every integer sum unchanged), so that the eight
-// adds of one pixel sit at fixed offsets from one base address; plus one
-// word so that copies start on different banks.
+// adds of one pixel sit at fixed offsets from one base address.
 constexpr int kDescCellBins = 9;
-constexpr int kDescStride = 16 * kDescCellBins + 1;
+constexpr int kDescHist = 16 * kDescCellBins;
 
 // Zeroes the N words (a multiple of 4) of a 16-byte-aligned LDS histogram
 // with the wave's 64 lanes, 16 bytes per lane and store, fully unrolled.
@@ -234,26 +248,45 @@ __device__ __forceinline__ void wave_zero(uint32_t* h, int lane) {
     }
 }
 
-// Walks the bounding box [u0, u0+bw) x [v0, ...) in row-major order, 64
-// pixels per step, without integer division in the loop; a lane is past the
-// box's last row exactly when its pixel index is past the box.
+// A uniform value in a vector register (operations whose operands all lie in
+// vector registers issue in nearly half the time of those with a scalar one).
+template <class T>
+__device__ __forceinline__ T in_vector(T x) {
+    asm("" : "+v"(x));
+    return x;
+}
+
+// Walks the bounding box [u0, u0+bw) x [v0, v1] in row-major order, 64 pixels
+// per step, without integer division in the loop; a lane is past the box's
+// last row exactly when its pixel index is past the box.  The pixel is kept
+// as floats (integers below 2^24, exact) and as a byte offset in the plane,
+// each advanced by one of two steps: no conversion and no multiplication per
+// pixel.
 struct BoxWalk {
-    int u, v, du, dv, u1;
-    __device__ __forceinline__ BoxWalk(int lane, int u0, int v0, int bw) {
-        int q, r;
+    float u, v;
+    uint32_t off;
+    float ulim, du0, du1, dv0, dv1;   // past ulim the step wraps into the next row (du1, dv1, doff1)
+    uint32_t doff0, doff1;
+    __device__ __forceinline__ BoxWalk(int lane, int u0, int v0, int bw, int pitch) {
+        int q, r, du, dv;
         divmod_est(lane, bw, q, r);
-        u = u0 + r;
-        v = v0 + q;
+        u = (float)(u0 + r);
+        v = (float)(v0 + q);
+        off = ((uint32_t)(v0 + q) * (uint32_t)pitch + (uint32_t)(u0 + r)) * 4u;
         divmod_est(64, bw, dv, du);
-        u1 = u0 + bw - 1;
+        ulim = in_vector((float)(u0 + bw - 1 - du));
+        du0 = in_vector((float)du);
+        du1 = in_vector((float)(du - bw));
+        dv0 = in_vector((float)dv);
+        dv1 = in_vector((float)(dv + 1));
+        doff0 = in_vector(((uint32_t)dv * (uint32_t)pitch + (uint32_t)du) * 4u);
+        doff1 = in_vector(((uint32_t)(dv + 1) * (uint32_t)pitch + (uint32_t)du - (uint32_t)bw) * 4u);
     }
-    __device__ __forceinline__ void next(int bw) {
-        u += du;
-        v += dv;
-        if (u > u1) {
-            u -= bw;
-            ++v;
-        }
+    __device__ __forceinline__ void next() {
+        const bool wrap = u > ulim;
+        u += wrap ? du1 : du0;
+        v += wrap ? dv1 : dv0;
+        off += wrap ? doff1 : doff0;
     }
 };
 
@@ -261,7 +294,7 @@ __global__ __launch_bounds__(64 * kKpWaves) void k_orient(const float* __restric
                                                 const cdvs_keypoint* __restrict__ kp,
                                                 const int32_t* __restrict__ count, int n_images, OriParams op,
                                                 cdvs_keypoint* __restrict__ ori, int32_t* __restrict__ ori_cnt) {
-    __shared__ __align__(16) uint32_t hist[kKpWaves][kCopies * kOriStride];
+    __shared__ __align__(16) uint32_t hist[kKpWaves][kCopies * kOriHist];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     // the slot is the same in every lane: taken apart in scalar registers
     const uint32_t slot = (uint32_t)__builtin_amdgcn_readfirstlane(xcd_remap(blockIdx.x, gridDim.x) * kKpWaves + wave);
@@ -279,11 +312,11 @@ __global__ __launch_bounds__(64 * kKpWaves) void k_orient(const float* __restric
         if (lane == 0) ori_cnt[(int64_t)img * op.kp_cap + i] = 0;
         return;
     }
-    wave_zero<kCopies * kOriStride>(hist[wave], lane);
+    wave_zero<kCopies * kOriHist>(hist[wave], lane);
     wave_sync();
 
     {
-        uint32_t* hc = &hist[wave][(lane & (kCopies - 1)) * kOriStride];
+        uint32_t* hc = &hist[wave][lane & (kCopies - 1)];
         const KpGeom g = keypoint_geometry(pyr, og, k, op.sigma0);
         const float R = op.radius * g.s;
         const float R2 = R * R;
@@ -292,18 +325,18 @@ __global__ __launch_bounds__(64 * kKpWaves) void k_orient(const float* __restric
         // 2^(d^2 nid + log2 fix), fix being a power of two
         // (the hardware reciprocal, 1 ulp: these per-keypoint constants need
         // no correctly rounded division)
-        const float nid = -1.4426950408889634f * __builtin_amdgcn_rcpf(2.f * ws * ws), lfix = op.lfix;
+        const float nid = -1.4426950408889634f * __builtin_amdgcn_rcpf(2.f * ws * ws), lfix = in_vector(op.lfix);
         const int u0 = max((int)ceilf(g.cx - R), 1), u1 = min((int)floorf(g.cx + R), g.w - 2);
         const int v0 = max((int)ceilf(g.cy - R), 1), v1 = min((int)floorf(g.cy + R), g.h - 2);
         const int bw = u1 - u0 + 1, bh = v1 - v0 + 1;
         if (bw > 0 && bh > 0) {
-            BoxWalk bwk(lane, u0, v0, bw);
-            for (; bwk.v <= v1; bwk.next(bw)) {   // row-major: past the box once v > v1
-                const int u = bwk.u, v = bwk.v;
-                const float dx = (float)u - g.cx, dy = (float)v - g.cy;
+            BoxWalk bwk(lane, u0, v0, bw, g.pitch);
+            const float vlast = in_vector((float)v1);
+            for (; bwk.v <= vlast; bwk.next()) {   // row-major: past the box once v > v1
+                const float dx = bwk.u - g.cx, dy = bwk.v - g.cy;
                 const float d2 = disk_d2(dx, dy);
                 if (!(d2 < R2)) continue;
-                const Nbrs nb = load_nbrs(g, u, v);
+                const Nbrs nb = load_nbrs(g, bwk.off);
                 float mag, ang;
                 gradient(nb, mag, ang);
                 const float wt = mag * __builtin_amdgcn_exp2f(fmaf(d2, nid, lfix));
@@ -311,18 +344,16 @@ __global__ __launch_bounds__(64 * kKpWaves) void k_orient(const float* __restric
                 const float f0 = floorf(fb);
                 const float fr = fb - f0;
                 const int b0 = (int)f0;   // 0 .. 36 (36 only for an angle of 2 pi)
-                atomicAdd(hc + b0, (uint32_t)(wt - wt * fr + 0.5f));
-                atomicAdd(hc + b0 + 1, (uint32_t)(wt * fr + 0.5f));   // bins 36, 37 are bins 0, 1
+                atomicAdd(hc + b0 * kCopies, (uint32_t)(wt - wt * fr + 0.5f));
+                atomicAdd(hc + b0 * kCopies + kCopies, (uint32_t)(wt * fr + 0.5f));   // bins 36, 37 are bins 0, 1
             }
         }
     }
     wave_sync();
 
     auto bin = [&](int b) {
-        uint32_t t = 0u;
-#pragma unroll
-        for (int c = 0; c < kCopies; ++c)
-            t += hist[wave][c * kOriStride + b] + (b < 2 ? hist[wave][c * kOriStride + kOriBins + b] : 0u);
+        uint32_t t = copies_sum(hist[wave], b);
+        if (b < 2) t += copies_sum(hist[wave], kOriBins + b);
         return (float)t * op.inv_fix;
     };
     // every lane reads its bin and both neighbours from the summed copies
@@ -408,7 +439,7 @@ __global__ __launch_bounds__(64 * kKpWaves) void k_describe(const float* __restr
                                                   const cdvs_keypoint* __restrict__ kp,
                                                   const int32_t* __restrict__ count, int n_images, DescParams dp,
                                                   float* __restrict__ desc) {
-    __shared__ __align__(16) uint32_t hist[kKpWaves][kCopies * kDescStride];
+    __shared__ __align__(16) uint32_t hist[kKpWaves][kCopies * kDescHist];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     // the slot is the same in every lane: taken apart in scalar registers
     const uint32_t slot = (uint32_t)__builtin_amdgcn_readfirstlane(xcd_remap(blockIdx.x, gridDim.x) * kKpWaves + wave);
@@ -428,11 +459,11 @@ __global__ __launch_bounds__(64 * kKpWaves) void k_describe(const float* __restr
         out[lane + 64] = 0.f;
         return;
     }
-    wave_zero<kCopies * kDescStride>(hist[wave], lane);
+    wave_zero<kCopies * kDescHist>(hist[wave], lane);
     wave_sync();
 
     {
-        uint32_t* hc = &hist[wave][(lane & (kCopies - 1)) * kDescStride];
+        uint32_t* hc = &hist[wave][lane & (kCopies - 1)];
         const KpGeom g = keypoint_geometry(pyr, og, k, dp.sigma0);
         const float th = k.theta;
         // hardware sine and cosine: theta is in [0, 2 pi), where they are
@@ -451,18 +482,18 @@ __global__ __launch_bounds__(64 * kKpWaves) void k_describe(const float* __restr
         const float ws = dp.wsigma * g.s;
         // Gaussian weight in fixed-point units: fix exp(-d^2 / (2 ws^2)) =
         // 2^(d^2 nid + log2 fix), fix being a power of two
-        const float nid = -1.4426950408889634f * __builtin_amdgcn_rcpf(2.f * ws * ws), lfix = dp.lfix;
+        const float nid = -1.4426950408889634f * __builtin_amdgcn_rcpf(2.f * ws * ws), lfix = in_vector(dp.lfix);
         const int u0 = max((int)ceilf(g.cx - R), 1), u1 = min((int)floorf(g.cx + R), g.w - 2);
         const int v0 = max((int)ceilf(g.cy - R), 1), v1 = min((int)floorf(g.cy + R), g.h - 2);
         const int bw = u1 - u0 + 1, bh = v1 - v0 + 1;
         if (bw > 0 && bh > 0) {
-            BoxWalk bwk(lane, u0, v0, bw);
-            for (; bwk.v <= v1; bwk.next(bw)) {   // row-major: past the box once v > v1
-                const int u = bwk.u, v = bwk.v;
-                const float dx = (float)u - g.cx, dy = (float)v - g.cy;
+            BoxWalk bwk(lane, u0, v0, bw, g.pitch);
+            const float vlast = in_vector((float)v1);
+            for (; bwk.v <= vlast; bwk.next()) {   // row-major: past the box once v > v1
+                const float dx = bwk.u - g.cx, dy = bwk.v - g.cy;
                 const float d2 = disk_d2(dx, dy);
                 if (!(d2 < R2)) continue;
-                const Nbrs nb = load_nbrs(g, u, v);
+                const Nbrs nb = load_nbrs(g, bwk.off);
                 const float fx = fmaf(cti, dx, fmaf(sti, dy, 1.5f));    // cell units, grid from 0
                 const float fy = fmaf(cti, dy, fmaf(-sti, dx, 1.5f));
                 float mag, ang;
@@ -488,18 +519,19 @@ __global__ __launch_bounds__(64 * kKpWaves) void k_describe(const float* __restr
                 const float wx1 = __builtin_amdgcn_fmed3f(tx, 2.f - tx, 0.f);     // the column after it
                 const float wy0 = fmaxf(0.f, 1.f - fabsf(ty));
                 const float wy1 = __builtin_amdgcn_fmed3f(ty, 2.f - ty, 0.f);
-                // base cell's first bin: (4 by + bx) x 9, exact in float
-                const int cell0 = (int)fmaf(cy0, 4.f * kDescCellBins, cx0 * (float)kDescCellBins);
-                uint32_t* cell = hc + cell0 + o0;
+                // base cell's first bin, (4 by + bx) x 9, in bytes, exact in float
+                constexpr float kCellBytes = 4.f * kCopies * kDescCellBins;
+                const int cell0 = (int)fmaf(cy0, 4.f * kCellBytes, cx0 * kCellBytes);
+                uint32_t* cell = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(hc) + cell0) + o0 * kCopies;
 #pragma unroll
                 for (int jy = 0; jy < 2; ++jy) {
                     const float wy = wt * (jy ? wy1 : wy0);
 #pragma unroll
                     for (int jx = 0; jx < 2; ++jx) {
                         const float wyx = wy * (jx ? wx1 : wx0);
-                        uint32_t* c = cell + (jy * 4 + jx) * kDescCellBins;
+                        uint32_t* c = cell + (jy * 4 + jx) * (kDescCellBins * kCopies);
                         atomicAdd(c, (uint32_t)fmaf(wyx, bo, 0.5f));      // rounded to nearest
-                        atomicAdd(c + 1, (uint32_t)fmaf(wyx, ao, 0.5f));
+                        atomicAdd(c + kCopies, (uint32_t)fmaf(wyx, ao, 0.5f));
                     }
                 }
             }
@@ -508,14 +540,11 @@ __global__ __launch_bounds__(64 * kKpWaves) void k_describe(const float* __restr
     wave_sync();
 
     // element e = cell * 8 + bin; bin 0 also takes the cell's wrap bin
-    uint32_t i0 = 0u, i1 = 0u;
     const int e0 = (lane >> 3) * kDescCellBins + (lane & 7), e1 = e0 + 8 * kDescCellBins;
-    const bool wrap = (lane & 7) == 0;
-#pragma unroll
-    for (int c = 0; c < kCopies; ++c) {
-        const uint32_t* h = &hist[wave][c * kDescStride];
-        i0 += h[e0] + (wrap ? h[e0 + 8] : 0u);
-        i1 += h[e1] + (wrap ? h[e1 + 8] : 0u);
+    uint32_t i0 = copies_sum(hist[wave], e0), i1 = copies_sum(hist[wave], e1);
+    if ((lane & 7) == 0) {
+        i0 += copies_sum(hist[wave], e0 + 8);
+        i1 += copies_sum(hist[wave], e1 + 8);
     }
     const float h0 = (float)i0 * dp.inv_fix, h1 = (float)i1 * dp.inv_fix;
     float* out = desc + (((int64_t)img * dp.kp_cap + i) * kDescDim);
