@@ -37,6 +37,8 @@
 // over rows (or columns), so with the row stride of 65 complex the LDS
 // accesses of a wave are conflict-free or at the two-cycle minimum of
 // 64-bit accesses.
+#include <algorithm>
+
 #include "cdvs_internal.h"
 
 namespace cdvs {
@@ -125,21 +127,28 @@ __device__ __forceinline__ void dft(float2 (&x)[N]) {
     stages_from<2, INV>(x);
 }
 
+constexpr int kBmOut(bool u8) { return u8 ? 5 : 4; }   // output scales
+
 // One block of one octave: U8 = octave 0 (input the u8 image; outputs
 // G_{0,0..4} through H rows 0 and 5..8), else input G_{o,0} and outputs
 // G_{o,1..4} through H rows 1..4.
 template <bool U8>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_bmlog(const uint8_t* __restrict__ images, float* __restrict__ pyr,
                                               const OctJob* __restrict__ jobs, const int32_t* __restrict__ blocks,
-                                              const float* __restrict__ Ht) {
-    constexpr int NOUT = U8 ? 5 : 4;
+                                              const float* __restrict__ Ht, int nwhole, int split) {
+    constexpr int NOUT = kBmOut(U8);
     __shared__ float2 W[BN * RS];   // work buffer
     __shared__ float2 P0[BN];       // spectrum of the packed column, by storage row
     __shared__ float2 tw[BN];       // exp(-2 pi i j / 128)
     __shared__ float Hs[NOUT][BN];  // the transfer functions applied here
 
     const int t = threadIdx.x;
-    const int* blk = blocks + 3 * blockIdx.x;
+    // the first nwhole workgroups take a block with all its scales, the others
+    // every split-th scale of one
+    const bool whole = (int)blockIdx.x < nwhole;   // uniform
+    const int rest = (int)blockIdx.x - nwhole, parts = whole ? 1 : split;
+    const int part = whole ? 0 : rest % split;
+    const int* blk = blocks + 3 * (whole ? (int)blockIdx.x : nwhole + rest / split);
     const OctJob& job = jobs[blk[0]];
     const int bx = blk[1], by = blk[2];
     const int w = job.w, h = job.h;
@@ -268,7 +277,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
 
     // unnormalised transforms: 128-point columns, then 64-point packed rows
     const float scale = 1.f / (float)(BN * HN);
-    for (int q = 0; q < NOUT; ++q) {
+    for (int q = part; q < NOUT; q += parts) {
         const float* H = Hs[q];
         // inverse columns, pass A: the filtered spectrum run (frequency
         // v = k1 + 8 k2) -> 16-point inverse DFT over k2 -> rows 16 k1 + n2
@@ -392,13 +401,25 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
 
 }  // namespace
 
+// A compute unit holds two workgroups, and a launch takes as many rounds of
+// 2 cus blocks as it needs; blocks left over take a round of their own, in
+// which most of the chip idles, for the time of a block with all its scales (a
+// workgroup alone on its unit: 8 us for the forward transform, 6 per scale;
+// beside another one half as much again).  So the scales of the blocks left
+// over are split over as many workgroups as leave each unit one (each
+// transforms the block forward for itself): 32 images 640x480 268 -> 216 us,
+// 8 of them 177 -> 120, one 152 -> 69, 100 of them 587 -> 568; filling 1.5 and 2
+// workgroups per unit instead measured 230 and 220 us for the 32.
 hipError_t launch_bmlog(const uint8_t* images, float* pyr, const OctJob* jobs, const int32_t* blocks, int nblocks,
-                        const float* H, bool octave0, hipStream_t stream) {
+                        const float* H, bool octave0, int cus, hipStream_t stream) {
     if (nblocks <= 0) return hipSuccess;
+    const int rest = nblocks % (2 * cus), nwhole = nblocks - rest;
+    const int split = rest > 0 ? std::max(1, std::min(cus / rest, kBmOut(octave0))) : 1;
+    const dim3 grid(nwhole + rest * split);
     if (octave0)
-        hipLaunchKernelGGL(k_bmlog<true>, dim3(nblocks), dim3(NT), 0, stream, images, pyr, jobs, blocks, H);
+        hipLaunchKernelGGL(k_bmlog<true>, grid, dim3(NT), 0, stream, images, pyr, jobs, blocks, H, nwhole, split);
     else
-        hipLaunchKernelGGL(k_bmlog<false>, dim3(nblocks), dim3(NT), 0, stream, images, pyr, jobs, blocks, H);
+        hipLaunchKernelGGL(k_bmlog<false>, grid, dim3(NT), 0, stream, images, pyr, jobs, blocks, H, nwhole, split);
     return hipGetLastError();
 }
 

@@ -41,6 +41,7 @@ struct cdvs_ctx {
     DescParams desc{};
     float dedup_ratio = 0.f;
     int wgrad_grid = 0;   // grid of the CNN weight-gradient kernels
+    int cus = 256;        // compute units
     int detect_grid = 0;  // persistent detection grid (workgroups)
     bool det_unfinished = false;  // a call ended between the detection and the finalisation that clears its counters
     // surrogate CNN cell grid
@@ -630,6 +631,7 @@ cdvs_status cdvs_ctx_create(const cdvs_params* params, const cdvs_image_desc* im
         if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) cus = v;
     }
     c->wgrad_grid = std::max(kXcds, cus * 2);
+    c->cus = cus;
     // persistent detection: five 256-lane workgroups per compute unit (its
     // registers allow five waves per SIMD)
     c->detect_grid = std::max(kXcds, cus * 5 / kXcds * kXcds);
@@ -695,7 +697,7 @@ cdvs_status cdvs_pyramid_bmlog(cdvs_ctx* ctx, const uint8_t* d_images, float* d_
         Bracket b(ctx, CDVS_KERNEL_BMLOG, s);
         HIP_OR_FAIL(ctx, launch_bmlog(d_images, d_pyr, ctx->d_jobs + ctx->job_start[o],
                                       ctx->d_bm_blocks + 3 * (int64_t)ctx->bm_start[o], ctx->bm_count[o],
-                                      ctx->d_bm_H, o == 0, s));
+                                      ctx->d_bm_H, o == 0, ctx->cus, s));
     }
     return CDVS_OK;
 }

@@ -341,7 +341,7 @@ hipError_t launch_relevance(const cdvs_keypoint* kp_in, const int32_t* count_in,
 // then g0 g1 .. g0 g4).
 constexpr int kBmN = 128, kBmR = 16, kBmStep = kBmN - 2 * kBmR, kBmTransfers = 9;
 hipError_t launch_bmlog(const uint8_t* images, float* pyr, const OctJob* jobs, const int32_t* blocks, int nblocks,
-                        const float* H, bool octave0, hipStream_t stream);
+                        const float* H, bool octave0, int cus, hipStream_t stream);
 
 // Front end: longer side brought down to kFrontLongSide; the output size
 // (the longer side 640, the shorter rounded half up, at least 1; images
