@@ -356,12 +356,17 @@ __global__ __launch_bounds__(kSumCols * kSumRows) void k_sum_parts(const float* 
 // loss is the mean over images of each image's mean over cells and its
 // octaves.
 //
-// Bound by memory (64 B read and 32 B written per cell).  Each lane sums its
+// 64 B read and 32 B written per cell would take 9 us for 614,400 cells at a
+// copy's rate; what bounds it is the issue of the six exponentials, logarithms
+// and divisions per cell at two waves per SIMD.  Each lane sums its
 // own cells' 103 products in registers; adding them up used to take 6
 // exchanges per value and one global atomic per value and wave, all on the
 // same 7 cache lines, which was nearly all of the kernel's time (931 us for
 // 614,400 cells); with the halving exchange, one row of sums per workgroup
-// and no atomics it takes 31 us, and the rows' sum 5.
+// and no atomics it took 34 us, and the rows' sum 5.  Two waves per SIMD (the
+// sums take the registers) hide little: with the next cell's values fetched
+// ahead, no image lookup per cell, and dZ Wh^T as 24 matrix instructions
+// instead of 96 FMAs with spilled scalar weights it takes 28.
 constexpr int kHeadSums = CC * NHD + NHD + 1;   // dWh, dbh, loss: 103
 constexpr int kHeadRow = 104;                   // floats per row of sums
 __global__ __launch_bounds__(256) void k_head_bwd(const short* __restrict__ X4, const float* __restrict__ P,
@@ -371,6 +376,12 @@ __global__ __launch_bounds__(256) void k_head_bwd(const short* __restrict__ X4, 
                                                   float* __restrict__ part) {
     __shared__ float red[4][128];
     const float* Wh = P + kCnnLayers * LAYER_P;
+    // A operands: the lane's weight, channel 4 q + (lane & 3) to head o
+    float wa[CC / 4][NHD];
+#pragma unroll
+    for (int q = 0; q < CC / 4; ++q)
+#pragma unroll
+        for (int o = 0; o < NHD; ++o) wa[q][o] = Wh[(4 * q + (threadIdx.x & 3)) * NHD + o];
     // values 0..95: dWh[channel][head]; 96..101: dbh; 102: loss; the rest 0
     float g0[64], g1[64];
 #pragma unroll
@@ -379,39 +390,74 @@ __global__ __launch_bounds__(256) void k_head_bwd(const short* __restrict__ X4, 
         if (i < 64) g0[i] += v;
         else g1[i - 64] += v;
     };
-    // a contiguous range of cells per workgroup: the image is searched for
-    // once and then only stepped forward
+    // a contiguous range of cells per workgroup: its first cell's image is
+    // searched for once (the same for all lanes), and a lane reads the next
+    // one's entry only where its cells reach it
     const int64_t beg = (int64_t)blockIdx.x * per_block, end = min(beg + per_block, ncells);
     int64_t c = beg + threadIdx.x;
-    int im = c < end ? find_cell_image(imgs, nimg, c) : 0;
-    for (; c < end; c += blockDim.x) {
-        while (im + 1 < nimg && imgs[im + 1].cell0 <= c) ++im;
+    int im = find_cell_image(imgs, nimg, beg), n_oct;
+    int64_t next_cell0;   // where the next image starts
+    float scale;
+    auto enter = [&]() {
         const CnnImage& g = imgs[im];
-        const int n_oct = g.n_oct;
-        const float scale = 1.f / ((float)g.H4 * (float)g.W4 * (float)n_oct * (float)nimg);
-        const uint32_t y = labels[c];
-        const s8u *xp = reinterpret_cast<const s8u*>(X4 + c * CC);
-        const s8 xa = xp[0], xb = xp[1];
-        const float* zc = logits + c * NHD;
+        n_oct = g.n_oct;
+        scale = 1.f / ((float)g.H4 * (float)g.W4 * (float)n_oct * (float)nimg);
+        next_cell0 = im + 1 < nimg ? imgs[im + 1].cell0 : ncells;
+    };
+    enter();
+    // (the next cell's values are on the way while this one's are used)
+    s8 na{}, nb{};
+    float nz[NHD] = {};
+    uint32_t ny = 0u;
+    auto fetch = [&](int64_t cell) {
+        const s8u* xp = reinterpret_cast<const s8u*>(X4 + cell * CC);
+        na = xp[0];
+        nb = xp[1];
+#pragma unroll
+        for (int o = 0; o < NHD; ++o) nz[o] = logits[cell * NHD + o];
+        ny = labels[cell];
+    };
+    if (c < end) fetch(c);
+    for (int64_t c0 = beg; c0 < end; c0 += blockDim.x, c += blockDim.x) {   // uniform: matrix instructions run on whole waves
+        const bool in = c < end;
+        while (in && c >= next_cell0) {
+            ++im;
+            enter();
+        }
+        const uint32_t y = ny;
+        const s8 xa = na, xb = nb;
+        float zc[NHD];
+#pragma unroll
+        for (int o = 0; o < NHD; ++o) zc[o] = nz[o];
+        if (c + blockDim.x < end) fetch(c + blockDim.x);
         float dz[NHD];
 #pragma unroll
         for (int o = 0; o < NHD; ++o) {
             const float z = zc[o];
             const float yo = (float)((y >> o) & 1u), w = pos_w[o];
             const float s = 1.f / (1.f + expf(-z));
-            const bool on = o < n_oct;
+            const bool on = in && o < n_oct;
             dz[o] = on ? (s * (w * yo + 1.f - yo) - w * yo) * scale : 0.f;
             add(102, on ? (w * yo * softplus(-z) + (1.f - yo) * softplus(z)) * scale : 0.f);
             add(96 + o, dz[o]);
         }
         s8 oa, ob;
+        // dZ Wh^T: step o of the 4x4x1 products adds head o's dZ of the lane's
+        // cell times its weights to four channels at a time, each product
+        // rounded as an fma, so the same chain as fma(Wh, dz, d) over o
+        f4 dq[CC / 4];
+#pragma unroll
+        for (int q = 0; q < CC / 4; ++q) dq[q] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int o = 0; o < NHD; ++o)
+#pragma unroll
+            for (int q = 0; q < CC / 4; ++q) dq[q] = __builtin_amdgcn_mfma_f32_4x4x1f32(wa[q][o], dz[o], dq[q], 0, 0, 0);
 #pragma unroll
         for (int ch = 0; ch < CC; ++ch) {
             const float x = bf2f(ch < 8 ? xa[ch] : xb[ch - 8]);
-            float d = 0.f;
+            const float d = dq[ch / 4][ch % 4];
 #pragma unroll
             for (int o = 0; o < NHD; ++o) {
-                d = fmaf(Wh[ch * NHD + o], dz[o], d);
                 const int i = ch * NHD + o;
                 if (i < 64) g0[i] = fmaf(x, dz[o], g0[i]);
                 else g1[i - 64] = fmaf(x, dz[o], g1[i - 64]);
@@ -420,9 +466,11 @@ __global__ __launch_bounds__(256) void k_head_bwd(const short* __restrict__ X4, 
             if (ch < 8) oa[ch] = v;
             else ob[ch - 8] = v;
         }
-        s8u* dst = reinterpret_cast<s8u*>(dP4 + c * CC);
-        dst[0] = oa;
-        dst[1] = ob;
+        if (in) {
+            s8u* dst = reinterpret_cast<s8u*>(dP4 + c * CC);
+            dst[0] = oa;
+            dst[1] = ob;
+        }
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     red[wave][lane] = wave_sums(g0, lane);
