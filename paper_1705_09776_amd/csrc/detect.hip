@@ -374,10 +374,20 @@ __device__ __forceinline__ int detect_strip(const float* __restrict__ pyr, const
             rows_on = 0ull;
             if (col_ok) {
                 const uint8_t* m = gate.mask + cg.cell0 + min((gx << job.octave) >> 2, cg.W4 - 1);
-                for (int y = y0; y < yend; ++y) {
+                // rows of one cell row share its byte: one load for the 4, 2
+                // or 1 rows of a cell, several on the way at a time (against
+                // a load per row: 128 gated images 836 -> 824 us, 40 of them
+                // 344 -> 337)
+                const int per = job.octave < 2 ? 4 >> job.octave : 1;
+                const uint32_t run = (1u << per) - 1u;
+#pragma unroll 4
+                for (int y = y0 - y0 % per; y < yend; y += per) {
                     const int cy = min((y << job.octave) >> 2, cg.H4 - 1);
-                    rows_on |= (uint64_t)((m[(int64_t)cy * cg.W4] >> job.octave) & 1) << (y - y0);
+                    const uint32_t bit = (m[(int64_t)cy * cg.W4] >> job.octave) & 1u;
+                    const uint64_t rows = bit ? run : 0u;
+                    rows_on |= y < y0 ? rows >> (y0 - y) : rows << (y - y0);
                 }
+                rows_on &= (1ull << (yend - y0)) - 1ull;   // (the last cell's rows past the strip; at most 48 rows)
             }
             if (!__ballot(rows_on != 0ull)) return 0;   // nothing active: the strip is not even loaded
         }
