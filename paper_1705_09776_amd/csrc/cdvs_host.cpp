@@ -52,6 +52,7 @@ struct cdvs_ctx {
     int32_t* d_active = nullptr;  // [n][kMaxOctaves] active mask cells
     short* d_cnn_frag = nullptr;  // packed weight fragments of the fused inference kernel
     float* d_scfv_prep = nullptr; // SCFV per-call model constants (kScfvPrepFloats)
+    float* d_cnn_sums = nullptr;    // rows of sums of the CNN's backward pass (at most 19 MB)
     float* d_scfv_tiles = nullptr;  // SCFV tile blocks of a small batch
     int scfv_tiles = 0;
     int32_t* d_wh = nullptr;      // per image: width, height
@@ -302,6 +303,7 @@ void cdvs_ctx_destroy(cdvs_ctx* ctx) {
     (void)hipFree(ctx->d_cnn_frag);
     (void)hipFree(ctx->d_scfv_prep);
     (void)hipFree(ctx->d_scfv_tiles);
+    (void)hipFree(ctx->d_cnn_sums);
     (void)hipFree(ctx->d_wh);
     (void)hipFree(ctx->d_img);
     (void)hipFree(ctx->d_bm_blocks);
@@ -548,6 +550,13 @@ cdvs_status cdvs_ctx_create(const cdvs_params* params, const cdvs_image_desc* im
     c->images.assign(images, images + n_images);
     build_layout(c);
     build_constants(c);
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) == hipSuccess) {
+        int v = 0;
+        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) cus = v;
+    }
+    c->wgrad_grid = std::max(kXcds, cus * 2);
+    c->cus = cus;
     hipError_t e = hipSuccess;
     const size_t n = (size_t)n_images;
 #define ALLOC(ptr, bytes)                                                        \
@@ -587,6 +596,7 @@ cdvs_status cdvs_ctx_create(const cdvs_params* params, const cdvs_image_desc* im
     ALLOC(c->d_active, sizeof(int32_t) * n * kMaxOctaves);
     ALLOC(c->d_cnn_frag, sizeof(short) * kCnnFragShorts);
     ALLOC(c->d_scfv_prep, sizeof(float) * kScfvPrepFloats);
+    ALLOC(c->d_cnn_sums, sizeof(float) * (size_t)cnn_sum_floats(c->ncells, c->cnn_ftiles, c->wgrad_grid));
     c->scfv_tiles = scfv_tile_blocks(n_images, kp_capacity);
     if (c->scfv_tiles > 0) ALLOC(c->d_scfv_tiles, sizeof(float) * kScfvTileFloats * (size_t)c->scfv_tiles);
     ALLOC(c->d_wh, sizeof(int32_t) * 2 * n);
@@ -625,16 +635,9 @@ cdvs_status cdvs_ctx_create(const cdvs_params* params, const cdvs_image_desc* im
         cdvs_ctx_destroy(c);
         return CDVS_ERR_HIP;
     }
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) {
-        int v = 0;
-        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) cus = v;
-    }
-    c->wgrad_grid = std::max(kXcds, cus * 2);
-    c->cus = cus;
     // persistent detection: five 256-lane workgroups per compute unit (its
     // registers allow five waves per SIMD)
-    c->detect_grid = std::max(kXcds, cus * 5 / kXcds * kXcds);
+    c->detect_grid = std::max(kXcds, c->cus * 5 / kXcds * kXcds);
     *out = c;
     return CDVS_OK;
 }
@@ -952,7 +955,7 @@ cdvs_status cdvs_cnn_backward(cdvs_ctx* ctx, const uint8_t* d_images, const floa
         return fail(ctx, CDVS_ERR_ARG, "cdvs_cnn_backward: d_acts and d_work must be 8-byte aligned");
     HIP_OR_FAIL(ctx, launch_cnn_backward(d_images, d_params, (const short*)d_acts, ctx->ncells, ctx->d_cnn, ctx->n,
                                          ctx->d_cnn_owner, ctx->cnn_ftiles, d_logits, d_labels,
-                                         d_pos_weight, (short*)d_work, d_grad, d_loss, ctx->wgrad_grid,
+                                         d_pos_weight, (short*)d_work, d_grad, d_loss, ctx->wgrad_grid, ctx->d_cnn_sums,
                                          (hipStream_t)stream));
     return CDVS_OK;
 }

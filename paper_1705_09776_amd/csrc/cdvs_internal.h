@@ -270,10 +270,12 @@ constexpr int kCnnFragShorts = kCnnLayers * 5 * 64 * 8;   // packed MFMA weight 
 hipError_t launch_cnn_forward(const uint8_t* images, const float* params, short* frag, const CnnImage* imgs,
                               const int32_t* owner, int ntiles, short* acts, int64_t ncells, float* logits,
                               uint8_t* mask, float zthr, hipStream_t s);
+// rows: cnn_sum_floats floats of scratch, the workgroups' sums.
+int64_t cnn_sum_floats(int64_t ncells, int ntiles, int wgrid);
 hipError_t launch_cnn_backward(const uint8_t* images, const float* params, const short* acts, int64_t ncells,
                                const CnnImage* imgs, int nimg, const int32_t* owner, int ntiles,
                                const float* logits, const uint32_t* labels, const float* pos_w, short* dbuf,
-                               float* grad, float* loss, int wgrid, hipStream_t s);
+                               float* grad, float* loss, int wgrid, float* rows, hipStream_t s);
 hipError_t launch_cnn_adam(float* p, const float* g, float* m, float* v, int step, float lr, float b1, float b2,
                            float eps, hipStream_t s);
 hipError_t launch_cnn_labels(const cdvs_keypoint* kp, const int32_t* count, int kp_cap, const CnnImage* imgs, int nimg,

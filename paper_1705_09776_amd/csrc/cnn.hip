@@ -327,14 +327,13 @@ __device__ __forceinline__ float wave_sums(float (&v)[N], int lane) {
 }
 
 // The first `n` words of out[] (the last in out_last when that is not null)
-// as the sums of `parts` rows of `stride` floats: 32 columns per workgroup,
-// whose 32 lane rows take every 32nd row each.
+// as the sums of `parts` rows of `stride` floats: 32 columns per workgroup
+// (the block-th), whose 32 lane rows take every 32nd row each.
 constexpr int kSumCols = 32, kSumRows = 32;
-__global__ __launch_bounds__(kSumCols * kSumRows) void k_sum_parts(const float* __restrict__ part, int parts, int stride,
-                                                                   int n, float* __restrict__ out,
-                                                                   float* __restrict__ out_last) {
+__device__ __forceinline__ void sum_parts(int block, const float* __restrict__ part, int parts, int stride, int n,
+                                          float* __restrict__ out, float* __restrict__ out_last) {
     __shared__ float red[kSumRows][kSumCols + 1];
-    const int c = threadIdx.x % kSumCols, r = threadIdx.x / kSumCols, col = blockIdx.x * kSumCols + c;
+    const int c = threadIdx.x % kSumCols, r = threadIdx.x / kSumCols, col = block * kSumCols + c;
     float s = 0.f;
     if (col < n) {
 #pragma unroll 4
@@ -352,7 +351,7 @@ __global__ __launch_bounds__(kSumCols * kSumRows) void k_sum_parts(const float* 
 
 // Head backward + loss: per cell dZ, the masked gradient dP4 = (dZ Wh^T) *
 // (X4 > 0) as bf16, and the sums of dWh, dbh and the loss over this
-// workgroup's cells as one row of `part` (k_sum_parts adds the rows).  The
+// workgroup's cells as one row of `part` (k_sum_all adds the rows).  The
 // loss is the mean over images of each image's mean over cells and its
 // octaves.
 //
@@ -363,7 +362,7 @@ __global__ __launch_bounds__(kSumCols * kSumRows) void k_sum_parts(const float* 
 // exchanges per value and one global atomic per value and wave, all on the
 // same 7 cache lines, which was nearly all of the kernel's time (931 us for
 // 614,400 cells); with the halving exchange, one row of sums per workgroup
-// and no atomics it took 34 us, and the rows' sum 5.  Two waves per SIMD (the
+// and no atomics it took 34 us.  Two waves per SIMD (the
 // sums take the registers) hide little: with the next cell's values fetched
 // ahead, no image lookup per cell, and dZ Wh^T as 24 matrix instructions
 // instead of 96 FMAs with spilled scalar weights it takes 28.
@@ -493,13 +492,12 @@ __global__ __launch_bounds__(256) void k_head_bwd(const short* __restrict__ X4, 
 // read on different banks).  A wave takes four rows: a row of X is read once
 // and, shifted by a cell either way in registers, serves the nine taps of up
 // to three rows of dP.  The workgroup's four waves are added up in LDS and
-// written as one row of sums for k_sum_parts (a single workgroup writes the
-// gradient itself).
+// written as one row of sums for k_sum_all.
 //
 // Bound by memory: 64 B per cell.  Gathering operands two bytes at a time and
 // adding every wave's sums with global atomics took 272 us for 614,400 cells
 // (303 us for the first layer, which also divided per pixel); this takes
-// 13 us (18 us), the rows' sum 5.
+// 13 us (18 us).
 constexpr int WTW = kCnnFusedW, WTH = kCnnFusedH;   // 32 x 16 cells
 constexpr int WXS = 56, WPS = 40;                   // LDS strides of a channel's row of X and dP (shorts)
 constexpr int WX0 = 8;                              // position of the tile's first cell in a row of X
@@ -825,7 +823,38 @@ __global__ __launch_bounds__(kCountThreads) void k_mask_count(const uint8_t* __r
     if (threadIdx.x < NHD && cnt[threadIdx.x]) atomicAdd(&active[img * kMaxOctaves + threadIdx.x], cnt[threadIdx.x]);
 }
 
+// All of a backward pass's sums in one launch: the head's rows, then the
+// layers'.  (A launch for each takes 4.6 us, mostly its latency: one for all
+// took the training step of 32 images 640x480 from 194 to 183 us, of one image
+// from 78 to 68.)
+constexpr int kHeadBlocks = (kHeadSums + kSumCols - 1) / kSumCols, kConvBlocks = (kConvSums + kSumCols - 1) / kSumCols;
+__global__ __launch_bounds__(kSumCols * kSumRows) void k_sum_all(const float* __restrict__ rows, int head_rows,
+                                                                 int conv_rows, float* __restrict__ grad,
+                                                                 float* __restrict__ loss) {
+    const int b = blockIdx.x;
+    const float* conv = rows + (int64_t)head_rows * kHeadRow;
+    if (b < kHeadBlocks) {   // uniform
+        sum_parts(b, rows, head_rows, kHeadRow, kHeadSums, grad + kCnnLayers * LAYER_P, loss);
+    } else {
+        const int l = (b - kHeadBlocks) / kConvBlocks;
+        sum_parts((b - kHeadBlocks) % kConvBlocks, conv + (int64_t)l * conv_rows * kConvSums, conv_rows, kConvSums,
+                  kConvSums, grad + l * LAYER_P, nullptr);
+    }
+}
+
+// Workgroups of the backward kernels that leave a row of sums each: of the
+// head one per 256 cells, or wgrid of them with a longer range each; of a
+// layer's weights one per tile, or wgrid with several.
+int head_groups(int64_t ncells, int wgrid) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>((ncells + 255) / 256, wgrid));
+}
+int conv_groups(int ntiles, int wgrid) { return std::max(1, std::min(ntiles, wgrid)); }
+
 }  // namespace
+
+int64_t cnn_sum_floats(int64_t ncells, int ntiles, int wgrid) {
+    return (int64_t)head_groups(ncells, wgrid) * kHeadRow + (int64_t)kCnnLayers * conv_groups(ntiles, wgrid) * kConvSums;
+}
 
 hipError_t launch_cnn_forward(const uint8_t* images, const float* params, short* frag, const CnnImage* imgs,
                               const int32_t* owner, int ntiles, short* acts, int64_t ncells, float* logits,
@@ -844,41 +873,26 @@ hipError_t launch_cnn_forward(const uint8_t* images, const float* params, short*
 hipError_t launch_cnn_backward(const uint8_t* images, const float* params, const short* acts, int64_t ncells,
                                const CnnImage* imgs, int nimg, const int32_t* owner, int ntiles,
                                const float* logits, const uint32_t* labels, const float* pos_w, short* dbuf,
-                               float* grad, float* loss, int wgrid, hipStream_t s) {
+                               float* grad, float* loss, int wgrid, float* rows, hipStream_t s) {
     short* dA = dbuf;
     short* dB = dbuf + ncells * CC;
-    // one workgroup per 256 cells, or wgrid of them with a longer range each;
-    // their sums go to dB, which nothing else uses until the first
-    // k_conv_bwd_data (416 B per workgroup of the 32 B per cell it has; an
-    // image has at least 16 cells)
     const int64_t groups = (ncells + 255) / 256;
-    const int hgrid = (int)std::max<int64_t>(1, std::min<int64_t>(groups, wgrid));
+    const int hgrid = head_groups(ncells, wgrid), parts = conv_groups(ntiles, wgrid);
     const int per_block = (int)((groups + hgrid - 1) / hgrid) * 256;
-    float* part = reinterpret_cast<float*>(dB);
+    float* conv_rows = rows + (int64_t)hgrid * kHeadRow;
     hipLaunchKernelGGL(k_head_bwd, dim3(hgrid), dim3(256), 0, s, acts + (int64_t)(kCnnLayers - 1) * ncells * CC,
-                       params, logits, labels, pos_w, imgs, nimg, ncells, per_block, dA, part);
-    hipLaunchKernelGGL(k_sum_parts, dim3((kHeadSums + kSumCols - 1) / kSumCols), dim3(kSumCols * kSumRows), 0, s, part,
-                       hgrid, kHeadRow, kHeadSums, grad + kCnnLayers * LAYER_P, loss);
+                       params, logits, labels, pos_w, imgs, nimg, ncells, per_block, dA, rows);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // weight gradients: as many workgroups as rows of sums fit in the free
-    // half of the work buffer (32 B per cell), at most two per compute unit;
-    // one alone writes the gradient itself
-    const int parts = (int)std::min<int64_t>(std::min(ntiles, wgrid),
-                                             ncells * CC * (int64_t)sizeof(short) / (kConvSums * (int64_t)sizeof(float)));
     for (int l = kCnnLayers - 1; l >= 0; --l) {
         const float* W = params + l * LAYER_P;
-        float* gl = grad + l * LAYER_P;
         const short* Xprev = l > 0 ? acts + (int64_t)(l - 1) * ncells * CC : nullptr;
-        float* out = parts > 1 ? reinterpret_cast<float*>(dB) : gl;
-        const dim3 wg(std::max(parts, 1));
+        float* out = conv_rows + (int64_t)l * parts * kConvSums;
+        const dim3 wg(parts);
         if (l == 0)
             hipLaunchKernelGGL(k_conv_bwd_weight<true>, wg, dim3(256), 0, s, images, nullptr, dA, imgs, owner, ntiles, out);
         else
             hipLaunchKernelGGL(k_conv_bwd_weight<false>, wg, dim3(256), 0, s, images, Xprev, dA, imgs, owner, ntiles, out);
-        if (parts > 1)
-            hipLaunchKernelGGL(k_sum_parts, dim3((kConvSums + kSumCols - 1) / kSumCols), dim3(kSumCols * kSumRows), 0, s,
-                               out, parts, kConvSums, kConvSums, gl, nullptr);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (l > 0) {
             hipLaunchKernelGGL(k_conv_bwd_data, dim3(ntiles), dim3(256), 0, s, dA, W, Xprev, dB, imgs, owner);
@@ -888,7 +902,9 @@ hipError_t launch_cnn_backward(const uint8_t* images, const float* params, const
             dB = t;
         }
     }
-    return hipSuccess;
+    hipLaunchKernelGGL(k_sum_all, dim3(kHeadBlocks + kCnnLayers * kConvBlocks), dim3(kSumCols * kSumRows), 0, s, rows, hgrid,
+                       parts, grad, loss);
+    return hipGetLastError();
 }
 
 hipError_t launch_cnn_adam(float* p, const float* g, float* m, float* v, int step, float lr, float b1, float b2,
