@@ -40,7 +40,7 @@ struct cdvs_ctx {
     OriParams ori{};
     DescParams desc{};
     float dedup_ratio = 0.f;
-    int wgrad_grid = 0;   // grid of the CNN weight-gradient kernels
+    int wgrad_grid = 0;   // grid of the CNN backward kernels
     int cus = 256;        // compute units
     int detect_grid = 0;  // persistent detection grid (workgroups)
     bool det_unfinished = false;  // a call ended between the detection and the finalisation that clears its counters

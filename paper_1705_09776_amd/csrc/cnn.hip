@@ -479,9 +479,11 @@ __global__ __launch_bounds__(256) void k_head_bwd(const short* __restrict__ X4, 
     if (t < kHeadSums) part[(int64_t)blockIdx.x * kHeadRow + t] = (red[0][t] + red[1][t]) + (red[2][t] + red[3][t]);
 }
 
-// Weight and bias gradients of layer l: dW[t][ci][co] = sum_p X_{l-1}[p + d_t][ci]
-// dP_l[p][co], db[co] = sum_p dP_l[p][co], as v_mfma_f32_16x16x32_bf16 with
-// K = 32 cells of one row.
+// Backward of layer l: the weight and bias gradients
+// dW[t][ci][co] = sum_p X_{l-1}[p + d_t][ci] dP_l[p][co], db[co] = sum_p dP_l[p][co],
+// as v_mfma_f32_16x16x32_bf16 with K = 32 cells of one row, and, but for the
+// first layer, the input gradient dX_{l-1}[p][ci] = sum_t sum_co W[t][ci][co]
+// dP_l[p - d_t][co], times (X_{l-1} > 0) to give dP_{l-1} (bf16).
 //
 // One 256-lane workgroup per tile of 32 x 16 cells at a time, the grid
 // striding over the tiles with the sums kept in registers.  Both operands
@@ -494,10 +496,22 @@ __global__ __launch_bounds__(256) void k_head_bwd(const short* __restrict__ X4, 
 // to three rows of dP.  The workgroup's four waves are added up in LDS and
 // written as one row of sums for k_sum_all.
 //
-// Bound by memory: 64 B per cell.  Gathering operands two bytes at a time and
-// adding every wave's sums with global atomics took 272 us for 614,400 cells
-// (303 us for the first layer, which also divided per pixel); this takes
-// 13 us (18 us).
+// The input gradient's operand has its channels along K: the tile of dP with
+// its rim lies in LDS a second time, as in memory (19 KB), and each wave
+// gives the four rows that it has just summed.  One tap per
+// v_mfma_f32_16x16x16_bf16 (lane l holds A[l%16][4(l/16)+j] and
+// B[4(l/16)+j][l%16] for j = 0..3), in the order of the taps: two taps per
+// instruction add up in another order, whose roundings to bf16 an Adam step
+// then carries on.
+//
+// Bound by the latency of a tile's loads and transposes at two workgroups
+// per CU; 96 B per cell are needed (64 in the first layer), 12 us.  For
+// 614,400 cells: gathering operands two bytes at a time, adding every wave's
+// sums with global atomics, and a wave per 16 cells converting all the
+// weights for itself took 272 + 41 us (303 in the first layer, which also
+// divided per pixel); one launch for the weights and one for the inputs, each
+// with tiles of its own, 13 + 13; the two on one tile 22 (first layer 17).
+// The tiles go round the XCDs as they come: neighbours on one XCD gave 23.
 constexpr int WTW = kCnnFusedW, WTH = kCnnFusedH;   // 32 x 16 cells
 constexpr int WXS = 56, WPS = 40;                   // LDS strides of a channel's row of X and dP (shorts)
 constexpr int WX0 = 8;                              // position of the tile's first cell in a row of X
@@ -539,23 +553,33 @@ __device__ __forceinline__ s8 load_cell8(const uint8_t* __restrict__ images, con
 }
 
 template <bool FIRST>
-__global__ __launch_bounds__(256) void k_conv_bwd_weight(const uint8_t* __restrict__ images,
-                                                         const short* __restrict__ Xprev, const short* __restrict__ dP,
-                                                         const CnnImage* __restrict__ imgs,
-                                                         const int32_t* __restrict__ owner, int ntiles,
-                                                         float* __restrict__ part) {
+__global__ __launch_bounds__(256, 2) void k_conv_bwd(const uint8_t* __restrict__ images, const short* __restrict__ Xprev,
+                                                     const short* __restrict__ dP, const float* __restrict__ Wl,
+                                                     const CnnImage* __restrict__ imgs, const int32_t* __restrict__ owner,
+                                                     int ntiles, float* __restrict__ part, short* __restrict__ dPprev) {
     constexpr int XP = WTW / 2 + 2;                      // cell pairs per staged row of X: cells -2 .. 33
     constexpr int NX = (WTH + 2) * XP * 2, NP = WTH * (WTW / 2) * 2;
     constexpr int JX = (NX + 255) / 256, JP = NP / 256;
     static_assert(NP % 256 == 0, "whole rounds");
     __shared__ __align__(16) short Xt[(WTH + 2) * CC * WXS];
     __shared__ __align__(16) short Pt[WTH * CC * WPS];
+    // the tile of dP with its rim, as it lies in memory (input gradients only)
+    constexpr int PW = WTW + 2, PH = WTH + 2, NB = FIRST ? 0 : PW * PH * 2, JB = (NB + 255) / 256;
+    __shared__ __align__(16) short buf[FIRST ? 8 : PH * PW * CC];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, kb = lane >> 4, li = lane & 15;
     f4 acc[9], accb = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < 9; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
     const short one = 0x3F80;   // 1.0: a row of ones sums dP itself
     const s8 ones = {one, one, one, one, one, one, one, one};
+    s4 wt[9];   // A[ci = lane % 16][co]
+    if constexpr (!FIRST) {
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+            const float* w = Wl + (t * CC + li) * CC + 4 * kb;
+            wt[t] = __builtin_bit_cast(s4, make_uint2(f2bf2(w[0], w[1]), f2bf2(w[2], w[3])));
+        }
+    }
     uint32_t* X32 = reinterpret_cast<uint32_t*>(Xt);
     uint32_t* P32 = reinterpret_cast<uint32_t*>(Pt);
     for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
@@ -578,6 +602,12 @@ __global__ __launch_bounds__(256) void k_conv_bwd_weight(const uint8_t* __restri
 #pragma unroll
             for (int c = 0; c < 2; ++c) pv[j][c] = load_cell8<false>(nullptr, dP, g, ty0 + r, tx0 + 2 * k + c, half);
         }
+        s8 bv[JB + 1];
+#pragma unroll
+        for (int j = 0; j < JB; ++j) {
+            const int it = tid + 256 * j, cell = it >> 1, r = cell / PW, c = cell % PW;
+            bv[j] = load_cell8<false>(nullptr, dP, g, it < NB ? ty0 - 1 + r : -1, tx0 - 1 + c, it & 1);
+        }
         __syncthreads();   // the previous tile's readers are done
 #pragma unroll
         for (int j = 0; j < JX; ++j) {
@@ -596,6 +626,24 @@ __global__ __launch_bounds__(256) void k_conv_bwd_weight(const uint8_t* __restri
             for (int c = 0; c < 8; ++c)
                 P32[(r * CC + 8 * half + c) * WPS / 2 + k] =
                     (uint32_t)(uint16_t)pv[j][0][c] | ((uint32_t)(uint16_t)pv[j][1][c] << 16);
+        }
+#pragma unroll
+        for (int j = 0; j < JB; ++j) {
+            const int it = tid + 256 * j;
+            if (it < NB) reinterpret_cast<s8*>(buf)[it] = bv[j];
+        }
+        // the rows' own activations, needed only for the input gradients
+        s4 xp[4][2];
+        if constexpr (!FIRST) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int cy = ty0 + 4 * wave + q, cx = tx0 + 16 * h + li;
+                    xp[q][h] = s4{0, 0, 0, 0};
+                    if (cy < g.H4 && cx < g.W4)
+                        xp[q][h] = *reinterpret_cast<const s4*>(Xprev + (g.cell0 + (int64_t)cy * g.W4 + cx) * CC + 4 * kb);
+                }
         }
         __syncthreads();
         // this wave's rows of dP: 4 wave .. 4 wave + 3; B[k = cell 8 kb + j][co = li]
@@ -624,6 +672,37 @@ __global__ __launch_bounds__(256) void k_conv_bwd_weight(const uint8_t* __restri
                     for (int dx = 0; dx < 3; ++dx) acc[3 * (x - q) + dx] = mfma32(a[dx], b[q], acc[3 * (x - q) + dx]);
                 }
         }
+        // the input gradients of the same rows
+        if constexpr (!FIRST) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                s4 bd[9][2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int t = 0; t < 9; ++t)   // the cell at (1 - t / 3, 1 - t % 3) from this lane's
+                        bd[t][h] = *reinterpret_cast<const s4*>(
+                            &buf[((4 * wave + q + 2 - t / 3) * PW + 16 * h + li + 2 - t % 3) * CC + 4 * kb]);
+                f4 ad[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+                for (int t = 0; t < 9; ++t)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        ad[h] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wt[t], bd[t][h], ad[h], 0, 0, 0);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    float r[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) r[i] = bf2f(xp[q][h][i]) > 0.f ? ad[h][i] : 0.f;
+                    uint2 o;
+                    o.x = f2bf2(r[0], r[1]);
+                    o.y = f2bf2(r[2], r[3]);
+                    const int cy = ty0 + 4 * wave + q, cx = tx0 + 16 * h + li;
+                    if (cy < g.H4 && cx < g.W4)
+                        *reinterpret_cast<uint2*>(dPprev + (g.cell0 + (int64_t)cy * g.W4 + cx) * CC + 4 * kb) = o;
+                }
+            }
+        }
     }
     // acc[t][r] = dW[t][ci = 4 kb + r][co = li]; every row of accb is db[li]
     __syncthreads();
@@ -649,86 +728,6 @@ __global__ __launch_bounds__(256) void k_conv_bwd_weight(const uint8_t* __restri
             }
         const int i = CONV_W + li;
         if (kb == 0) out[i] = (accb[0] + red[i]) + (red[kConvSums + i] + red[2 * kConvSums + i]);
-    }
-}
-
-// Input gradient of layer l: dX_{l-1}[p][ci] = sum_t sum_co W[t][ci][co]
-// dP_l[p - d_t][co], then times (X_{l-1} > 0) to give dP_{l-1} (bf16).  One
-// tap per v_mfma_f32_16x16x16_bf16 (lane l holds A[l%16][4(l/16)+j] and
-// B[4(l/16)+j][l%16] for j = 0..3), in the order of the taps: two taps per
-// instruction add up in another order, whose roundings to bf16 an Adam step
-// then carries on, and the time is the memory's either way (13 us).
-//
-// One 256-lane workgroup per 32 x 16 cells; the tile of dP with its rim is
-// staged in LDS and each wave takes four rows.  Bound by memory: 96 B per
-// cell.  A wave per 16 cells loading and converting all the weights for
-// itself took 41 us for 614,400 cells; this takes 13 us.
-__global__ __launch_bounds__(256) void k_conv_bwd_data(const short* __restrict__ dP, const float* __restrict__ Wl,
-                                                       const short* __restrict__ Xprev, short* __restrict__ dPprev,
-                                                       const CnnImage* __restrict__ imgs,
-                                                       const int32_t* __restrict__ owner) {
-    constexpr int PW = WTW + 2, PH = WTH + 2, N = PW * PH * 2, J = (N + 255) / 256;
-    __shared__ __align__(16) short buf[PH * PW * CC];
-    const int tile = xcd_remap(blockIdx.x, gridDim.x);
-    const CnnImage g = imgs[owner[tile]];
-    const int lt = tile - g.ftile0;
-    const int ty0 = (lt / g.ftiles_x) * WTH, tx0 = (lt % g.ftiles_x) * WTW;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, kb = lane >> 4, li = lane & 15;
-    s8 v[J];
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-        const int it = threadIdx.x + 256 * j, cell = it >> 1, r = cell / PW, c = cell % PW;
-        v[j] = load_cell8<false>(nullptr, dP, g, it < N ? ty0 - 1 + r : -1, tx0 - 1 + c, it & 1);
-    }
-    s4 a[9];   // A[ci = lane % 16][co]
-#pragma unroll
-    for (int t = 0; t < 9; ++t) {
-        const float* w = Wl + (t * CC + li) * CC + 4 * kb;
-        a[t] = __builtin_bit_cast(s4, make_uint2(f2bf2(w[0], w[1]), f2bf2(w[2], w[3])));
-    }
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-        const int it = threadIdx.x + 256 * j;
-        if (it < N) reinterpret_cast<s8*>(buf)[it] = v[j];
-    }
-    // the rows' own activations, needed only after the MFMAs
-    s4 xp[4][2];
-    int64_t off[4][2];
-    bool in[4][2];
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int cy = ty0 + 4 * wave + q, cx = tx0 + 16 * h + li;
-            in[q][h] = cy < g.H4 && cx < g.W4;
-            off[q][h] = (g.cell0 + (int64_t)cy * g.W4 + cx) * CC + 4 * kb;
-            xp[q][h] = in[q][h] ? *reinterpret_cast<const s4*>(Xprev + off[q][h]) : s4{0, 0, 0, 0};
-        }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        s4 b[9][2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int t = 0; t < 9; ++t)   // the cell at (1 - t / 3, 1 - t % 3) from this lane's
-                b[t][h] = *reinterpret_cast<const s4*>(
-                    &buf[((4 * wave + q + 2 - t / 3) * PW + 16 * h + li + 2 - t % 3) * CC + 4 * kb]);
-        f4 acc[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-        for (int t = 0; t < 9; ++t)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) acc[h] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[t], b[t][h], acc[h], 0, 0, 0);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            float r[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) r[i] = bf2f(xp[q][h][i]) > 0.f ? acc[h][i] : 0.f;
-            uint2 o;
-            o.x = f2bf2(r[0], r[1]);
-            o.y = f2bf2(r[2], r[3]);
-            if (in[q][h]) *reinterpret_cast<uint2*>(dPprev + off[q][h]) = o;
-        }
     }
 }
 
@@ -890,13 +889,12 @@ hipError_t launch_cnn_backward(const uint8_t* images, const float* params, const
         float* out = conv_rows + (int64_t)l * parts * kConvSums;
         const dim3 wg(parts);
         if (l == 0)
-            hipLaunchKernelGGL(k_conv_bwd_weight<true>, wg, dim3(256), 0, s, images, nullptr, dA, imgs, owner, ntiles, out);
+            hipLaunchKernelGGL(k_conv_bwd<true>, wg, dim3(256), 0, s, images, nullptr, dA, nullptr, imgs, owner, ntiles, out,
+                               nullptr);
         else
-            hipLaunchKernelGGL(k_conv_bwd_weight<false>, wg, dim3(256), 0, s, images, Xprev, dA, imgs, owner, ntiles, out);
+            hipLaunchKernelGGL(k_conv_bwd<false>, wg, dim3(256), 0, s, images, Xprev, dA, W, imgs, owner, ntiles, out, dB);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (l > 0) {
-            hipLaunchKernelGGL(k_conv_bwd_data, dim3(ntiles), dim3(256), 0, s, dA, W, Xprev, dB, imgs, owner);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
             short* t = dA;
             dA = dB;
             dB = t;

@@ -33,9 +33,9 @@ def _rel(a, b):
 
 # (16, 16): 16 cells; (97, 61): 25 x 16 cells, partial tiles; 40 images of
 # 20 cells in one 256-cell range; 134,400 cells, more than the grid's
-# 512 x 256
+# 512 x 256; 548 tiles, more than its 512
 SHAPES = {"smallest": [(16, 16)], "partial": [(97, 61), (130, 66), (129, 65)], "many_small": [(20, 16)] * 40,
-          "beyond_grid": [(640, 480)] * 7}
+          "beyond_grid": [(640, 480)] * 7, "beyond_tiles": [(130, 66)] * 9 + [(16, 16)] * 512}
 
 
 @pytest.mark.parametrize("shape", list(SHAPES))
