@@ -510,46 +510,71 @@ __global__ __launch_bounds__(256) void k_head_bwd(const short* __restrict__ X4, 
 // sums with global atomics, and a wave per 16 cells converting all the
 // weights for itself took 272 + 41 us (303 in the first layer, which also
 // divided per pixel); one launch for the weights and one for the inputs, each
-// with tiles of its own, 13 + 13; the two on one tile 22 (first layer 17).
-// The tiles go round the XCDs as they come: neighbours on one XCD gave 23.
+// with tiles of its own, 13 + 13; the two on one tile 22.  The first layer,
+// whose loads are eight rows of pixels, has its next tile's out before it
+// works on this one: 17 -> 14.5; the others gain nothing by it and lose 1 us
+// where a workgroup has one tile.  The tiles go round the XCDs as they come:
+// neighbours on one XCD gave 23.
 constexpr int WTW = kCnnFusedW, WTH = kCnnFusedH;   // 32 x 16 cells
 constexpr int WXS = 56, WPS = 40;                   // LDS strides of a channel's row of X and dP (shorts)
 constexpr int WX0 = 8;                              // position of the tile's first cell in a row of X
 constexpr int kConvSums = LAYER_P;                  // dW (9 x 16 x 16), db (16)
 static_assert(WTW == 32 && WTH == 16, "a wave takes four rows of 32 cells");
 
-// The 16 bytes (8 channels, 8 half ..) of cell (cy, cx) of the layer input,
-// or of the space-to-depth image when FIRST; zero outside the image.
+// What 8 channels (8 half ..) of cell (cy, cx) of the layer input are made
+// of: their 16 bytes, or the two rows of four pixels of the space-to-depth
+// image when FIRST; zero outside the image.
 template <bool FIRST>
-__device__ __forceinline__ s8 load_cell8(const uint8_t* __restrict__ images, const short* __restrict__ X,
-                                         const CnnImage& g, int cy, int cx, int half) {
-    s8 v = {0, 0, 0, 0, 0, 0, 0, 0};
+struct Cell8 {
+    using type = s8;
+};
+template <>
+struct Cell8<true> {
+    using type = uint2;
+};
+
+template <bool FIRST>
+__device__ __forceinline__ typename Cell8<FIRST>::type load_cell8(const uint8_t* __restrict__ images,
+                                                                  const short* __restrict__ X, const CnnImage& g, int cy,
+                                                                  int cx, int half) {
+    typename Cell8<FIRST>::type v = {};
     if (cy < 0 || cy >= g.H4 || cx < 0 || cx >= g.W4) return v;
     if constexpr (!FIRST) {
         v = *reinterpret_cast<const s8u*>(X + (g.cell0 + (int64_t)cy * g.W4 + cx) * CC + 8 * half);
     } else {
+        uint32_t px[2] = {0, 0};
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
             const uint8_t* row = images + g.src + (int64_t)min(4 * cy + 2 * half + r, g.H - 1) * g.src_pitch;
             const int x0 = 4 * cx;
-            uint32_t px = 0;
             if (x0 + 3 < g.W && ((uintptr_t)(row + x0) & 3) == 0) {
-                px = *reinterpret_cast<const uint32_t*>(row + x0);
+                px[r] = *reinterpret_cast<const uint32_t*>(row + x0);
             } else {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) px |= (uint32_t)row[min(x0 + j, g.W - 1)] << (8 * j);
+                for (int j = 0; j < 4; ++j) px[r] |= (uint32_t)row[min(x0 + j, g.W - 1)] << (8 * j);
             }
-            // u * (1 / 255) and u / 255 round to the same bf16 for every u8
-            const float k = 1.f / 255.f;
-            const uint32_t lo = f2bf2((float)(px & 255u) * k, (float)((px >> 8) & 255u) * k);
-            const uint32_t hi = f2bf2((float)((px >> 16) & 255u) * k, (float)(px >> 24) * k);
-            v[4 * r] = (short)lo;
-            v[4 * r + 1] = (short)(lo >> 16);
-            v[4 * r + 2] = (short)hi;
-            v[4 * r + 3] = (short)(hi >> 16);
         }
+        v = make_uint2(px[0], px[1]);
     }
     return v;
+}
+
+__device__ __forceinline__ s8 cell8_bf16(s8 v) { return v; }
+__device__ __forceinline__ s8 cell8_bf16(uint2 v) {
+    s8 o;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const uint32_t px = r == 0 ? v.x : v.y;
+        // u * (1 / 255) and u / 255 round to the same bf16 for every u8
+        const float k = 1.f / 255.f;
+        const uint32_t lo = f2bf2((float)(px & 255u) * k, (float)((px >> 8) & 255u) * k);
+        const uint32_t hi = f2bf2((float)((px >> 16) & 255u) * k, (float)(px >> 24) * k);
+        o[4 * r] = (short)lo;
+        o[4 * r + 1] = (short)(lo >> 16);
+        o[4 * r + 2] = (short)hi;
+        o[4 * r + 3] = (short)(hi >> 16);
+    }
+    return o;
 }
 
 template <bool FIRST>
@@ -564,7 +589,8 @@ __global__ __launch_bounds__(256, 2) void k_conv_bwd(const uint8_t* __restrict__
     __shared__ __align__(16) short Xt[(WTH + 2) * CC * WXS];
     __shared__ __align__(16) short Pt[WTH * CC * WPS];
     // the tile of dP with its rim, as it lies in memory (input gradients only)
-    constexpr int PW = WTW + 2, PH = WTH + 2, NB = FIRST ? 0 : PW * PH * 2, JB = (NB + 255) / 256;
+    constexpr int PW = WTW + 2, PH = WTH + 2, NB = FIRST ? 0 : 2 * (PW * PH - WTW * WTH);
+    static_assert(NB <= 256, "the rim in one round");
     __shared__ __align__(16) short buf[FIRST ? 8 : PH * PW * CC];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, kb = lane >> 4, li = lane & 15;
     f4 acc[9], accb = {0.f, 0.f, 0.f, 0.f};
@@ -580,15 +606,23 @@ __global__ __launch_bounds__(256, 2) void k_conv_bwd(const uint8_t* __restrict__
             wt[t] = __builtin_bit_cast(s4, make_uint2(f2bf2(w[0], w[1]), f2bf2(w[2], w[3])));
         }
     }
+    // this thread's half cell of the rim: the top and bottom rows, then the sides
+    const int rim = tid >> 1, side = rim - 2 * PW;
+    const int rim_r = rim < 2 * PW ? (rim < PW ? 0 : PH - 1) : 1 + (side >> 1);
+    const int rim_c = rim < 2 * PW ? (rim < PW ? rim : rim - PW) : (side & 1) * (PW - 1);
     uint32_t* X32 = reinterpret_cast<uint32_t*>(Xt);
     uint32_t* P32 = reinterpret_cast<uint32_t*>(Pt);
-    for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const CnnImage g = imgs[owner[tile]];
+    // Every load of a tile goes out before its first LDS write; an item is
+    // half of the channels of two neighbouring cells.
+    CnnImage g;
+    int ty0, tx0;
+    typename Cell8<FIRST>::type xv[JX][2];
+    s8 pv[JP][2], bv = {0, 0, 0, 0, 0, 0, 0, 0};
+    auto fetch = [&](int tile) {
+        g = imgs[owner[tile]];
         const int lt = tile - g.ftile0;
-        const int ty0 = (lt / g.ftiles_x) * WTH, tx0 = (lt % g.ftiles_x) * WTW;
-        // every load of the tile goes out before the first LDS write; an item
-        // is half of the channels of two neighbouring cells
-        s8 xv[JX][2], pv[JP][2];
+        ty0 = (lt / g.ftiles_x) * WTH;
+        tx0 = (lt % g.ftiles_x) * WTW;
 #pragma unroll
         for (int j = 0; j < JX; ++j) {
             const int it = tid + 256 * j, half = it & 1, k = (it >> 1) % XP, r = (it >> 1) / XP;
@@ -602,21 +636,21 @@ __global__ __launch_bounds__(256, 2) void k_conv_bwd(const uint8_t* __restrict__
 #pragma unroll
             for (int c = 0; c < 2; ++c) pv[j][c] = load_cell8<false>(nullptr, dP, g, ty0 + r, tx0 + 2 * k + c, half);
         }
-        s8 bv[JB + 1];
-#pragma unroll
-        for (int j = 0; j < JB; ++j) {
-            const int it = tid + 256 * j, cell = it >> 1, r = cell / PW, c = cell % PW;
-            bv[j] = load_cell8<false>(nullptr, dP, g, it < NB ? ty0 - 1 + r : -1, tx0 - 1 + c, it & 1);
-        }
+        if constexpr (!FIRST) bv = load_cell8<false>(nullptr, dP, g, tid < NB ? ty0 - 1 + rim_r : -1, tx0 - 1 + rim_c, tid & 1);
+    };
+    if (FIRST && (int)blockIdx.x < ntiles) fetch(blockIdx.x);
+    for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        if (!FIRST) fetch(tile);
         __syncthreads();   // the previous tile's readers are done
 #pragma unroll
         for (int j = 0; j < JX; ++j) {
             const int it = tid + 256 * j, half = it & 1, k = (it >> 1) % XP, r = (it >> 1) / XP;
             if (it < NX) {
+                const s8 x0 = cell8_bf16(xv[j][0]), x1 = cell8_bf16(xv[j][1]);
 #pragma unroll
                 for (int c = 0; c < 8; ++c)
                     X32[((r * CC + 8 * half + c) * WXS + WX0 - 2) / 2 + k] =
-                        (uint32_t)(uint16_t)xv[j][0][c] | ((uint32_t)(uint16_t)xv[j][1][c] << 16);
+                        (uint32_t)(uint16_t)x0[c] | ((uint32_t)(uint16_t)x1[c] << 16);
             }
         }
 #pragma unroll
@@ -626,26 +660,31 @@ __global__ __launch_bounds__(256, 2) void k_conv_bwd(const uint8_t* __restrict__
             for (int c = 0; c < 8; ++c)
                 P32[(r * CC + 8 * half + c) * WPS / 2 + k] =
                     (uint32_t)(uint16_t)pv[j][0][c] | ((uint32_t)(uint16_t)pv[j][1][c] << 16);
-        }
+            if constexpr (!FIRST) {
 #pragma unroll
-        for (int j = 0; j < JB; ++j) {
-            const int it = tid + 256 * j;
-            if (it < NB) reinterpret_cast<s8*>(buf)[it] = bv[j];
+                for (int c = 0; c < 2; ++c)
+                    reinterpret_cast<s8*>(buf)[((r + 1) * PW + 2 * k + c + 1) * 2 + half] = pv[j][c];
+            }
+        }
+        if constexpr (!FIRST) {
+            if (tid < NB) reinterpret_cast<s8*>(buf)[(rim_r * PW + rim_c) * 2 + (tid & 1)] = bv;
         }
         // the rows' own activations, needed only for the input gradients
         s4 xp[4][2];
+        const int cy0 = ty0 + 4 * wave, cx0 = tx0 + li, H4 = g.H4, W4 = g.W4;
+        const int64_t off0 = (g.cell0 + (int64_t)cy0 * W4 + cx0) * CC + 4 * kb;
         if constexpr (!FIRST) {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    const int cy = ty0 + 4 * wave + q, cx = tx0 + 16 * h + li;
                     xp[q][h] = s4{0, 0, 0, 0};
-                    if (cy < g.H4 && cx < g.W4)
-                        xp[q][h] = *reinterpret_cast<const s4*>(Xprev + (g.cell0 + (int64_t)cy * g.W4 + cx) * CC + 4 * kb);
+                    if (cy0 + q < H4 && cx0 + 16 * h < W4)
+                        xp[q][h] = *reinterpret_cast<const s4*>(Xprev + off0 + (int64_t)(q * W4 + 16 * h) * CC);
                 }
         }
         __syncthreads();
+        if (FIRST && tile + (int)gridDim.x < ntiles) fetch(tile + gridDim.x);
         // this wave's rows of dP: 4 wave .. 4 wave + 3; B[k = cell 8 kb + j][co = li]
         s8 b[4];
 #pragma unroll
@@ -697,9 +736,8 @@ __global__ __launch_bounds__(256, 2) void k_conv_bwd(const uint8_t* __restrict__
                     uint2 o;
                     o.x = f2bf2(r[0], r[1]);
                     o.y = f2bf2(r[2], r[3]);
-                    const int cy = ty0 + 4 * wave + q, cx = tx0 + 16 * h + li;
-                    if (cy < g.H4 && cx < g.W4)
-                        *reinterpret_cast<uint2*>(dPprev + (g.cell0 + (int64_t)cy * g.W4 + cx) * CC + 4 * kb) = o;
+                    if (cy0 + q < H4 && cx0 + 16 * h < W4)
+                        *reinterpret_cast<uint2*>(dPprev + off0 + (int64_t)(q * W4 + 16 * h) * CC) = o;
                 }
             }
         }
