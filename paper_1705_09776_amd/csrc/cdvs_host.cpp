@@ -15,6 +15,7 @@
 #include <thread>
 #include <sstream>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "cdvs_internal.h"
@@ -63,7 +64,8 @@ struct cdvs_ctx {
     int32_t* d_bm_blocks = nullptr;
     float* d_bm_H = nullptr;
     float bm_H[kBmTransfers * kBmN] = {};
-    // device
+    // device: all in one allocation
+    void* d_arena = nullptr;
     OctJob* d_jobs = nullptr;
     std::vector<int32_t> blur_owner;           // [variant][octave][tile] -> job (relative to job_start[octave])
     int blur_owner_start[kBlurTilings][kMaxOctaves] = {};
@@ -284,30 +286,7 @@ void cdvs_ctx_destroy(cdvs_ctx* ctx) {
     if (ctx->graph) (void)hipGraphDestroy(ctx->graph);
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
     for (auto& e : ctx->ev) (void)hipEventDestroy(e);
-    (void)hipFree(ctx->d_jobs);
-    (void)hipFree(ctx->d_strips);
-    (void)hipFree(ctx->d_blur_owner);
-    (void)hipFree(ctx->d_cnn_owner);
-    (void)hipFree(ctx->d_geom);
-    (void)hipFree(ctx->d_cand);
-    (void)hipFree(ctx->d_cand_off);
-    (void)hipFree(ctx->d_cand_capv);
-    (void)hipFree(ctx->d_sel);
-    (void)hipFree(ctx->d_absp);
-    (void)hipFree(ctx->d_cand_cnt);
-    (void)hipFree(ctx->d_ori);
-    (void)hipFree(ctx->d_ori_cnt);
-    (void)hipFree(ctx->d_flags);
-    (void)hipFree(ctx->d_cnn);
-    (void)hipFree(ctx->d_active);
-    (void)hipFree(ctx->d_cnn_frag);
-    (void)hipFree(ctx->d_scfv_prep);
-    (void)hipFree(ctx->d_scfv_tiles);
-    (void)hipFree(ctx->d_cnn_sums);
-    (void)hipFree(ctx->d_wh);
-    (void)hipFree(ctx->d_img);
-    (void)hipFree(ctx->d_bm_blocks);
-    (void)hipFree(ctx->d_bm_H);
+    (void)hipFree(ctx->d_arena);
     delete ctx;
 }
 
@@ -420,6 +399,7 @@ static cdvs_status build_layout(cdvs_ctx* c) {
             tall += (int64_t)((cw + kDetStripW - 1) / kDetStripW) * ((ch + kDetStripH - 1) / kDetStripH);
     }
     c->strip_h = det_strip_height(tall);
+    c->strips.reserve((size_t)tall * (kDetStripH / c->strip_h));   // a strip is at most so many
     for (int i = 0; i < c->n; ++i)
         for (int o = 0; o < kMaxOctaves; ++o)
             for (const OctJob& j : per_oct[o]) {
@@ -428,20 +408,20 @@ static cdvs_status build_layout(cdvs_ctx* c) {
                 const int cw = j.w - 2 * b, ch = j.h - 2 * b;
                 if (cw <= 0 || ch <= 0) continue;
                 const int sx = (cw + kDetStripW - 1) / kDetStripW, sy = (ch + c->strip_h - 1) / c->strip_h;
+                DetTile r;
+                memset(&r, 0, sizeof(r));
+                r.plane0 = j.plane0;
+                r.plane_stride = j.plane_stride;
+                r.pitch = j.pitch;
+                r.w = j.w;
+                r.h = j.h;
+                r.image = j.image;
+                r.octave = j.octave;
+                r.cand_cap = c->cand_cap[j.image];
+                r.cand_blk = (int32_t)(c->cand_off[j.image] / kCandBlock);
                 for (int t = 0; t < sx * sy; ++t) {
-                    DetTile r;
-                    memset(&r, 0, sizeof(r));
-                    r.plane0 = j.plane0;
-                    r.plane_stride = j.plane_stride;
-                    r.pitch = j.pitch;
-                    r.w = j.w;
-                    r.h = j.h;
                     r.tx0 = b + (t % sx) * kDetStripW;
                     r.ty0 = b + (t / sx) * c->strip_h;
-                    r.image = j.image;
-                    r.octave = j.octave;
-                    r.cand_cap = c->cand_cap[j.image];
-                    r.cand_blk = (int32_t)(c->cand_off[j.image] / kCandBlock);
                     c->strips.push_back(r);
                 }
             }
@@ -559,78 +539,79 @@ cdvs_status cdvs_ctx_create(const cdvs_params* params, const cdvs_image_desc* im
     c->cus = cus;
     hipError_t e = hipSuccess;
     const size_t n = (size_t)n_images;
-#define ALLOC(ptr, bytes)                                                        \
-    do {                                                                         \
-        e = hipMalloc((void**)&(ptr), (bytes));                                  \
-        if (e != hipSuccess) {                                                   \
-            fail(nullptr, CDVS_ERR_HIP, "hipMalloc(%zu): %s", (size_t)(bytes), hipGetErrorString(e)); \
-            cdvs_ctx_destroy(c);                                                 \
-            return CDVS_ERR_HIP;                                                 \
-        }                                                                        \
+    // One allocation, cut at 256 bytes, whose first part holds the tables and
+    // the counters that start at zero and is written by one copy: each
+    // hipMalloc of 2 MB or more and each copy takes ten microseconds or more,
+    // and images of new sizes need a new context.
+    std::vector<std::pair<void*, size_t>> pieces;   // address of the pointer, offset
+    size_t arena = 0;
+#define ALLOC(ptr, bytes)                                   \
+    do {                                                    \
+        pieces.emplace_back(&(ptr), arena);                 \
+        arena += ((size_t)(bytes) + 255) & ~(size_t)255;    \
     } while (0)
-    ALLOC(c->d_jobs, sizeof(OctJob) * std::max<size_t>(1, c->jobs.size()));
-    ALLOC(c->d_strips, sizeof(DetTile) * std::max<size_t>(1, c->strips.size()));
-    ALLOC(c->d_blur_owner, sizeof(int32_t) * std::max<size_t>(1, c->blur_owner.size()));
-    ALLOC(c->d_cnn_owner, sizeof(int32_t) * std::max<size_t>(1, c->cnn_owner.size()));
-    ALLOC(c->d_geom, sizeof(OctGeom) * c->geom.size());
-    {
-        int64_t total = 0;
-        int32_t cmax = 0;
-        for (int i = 0; i < n; ++i) {
-            total += c->cand_cap[i];
-            cmax = std::max(cmax, c->cand_cap[i]);
-        }
-        ALLOC(c->d_cand, sizeof(cdvs_keypoint) * total);
-        ALLOC(c->d_cand_off, sizeof(int64_t) * n);
-        ALLOC(c->d_cand_capv, sizeof(int32_t) * n);
-        if (cmax > kCandCap) {
-            ALLOC(c->d_sel, sizeof(uint32_t) * n * kCandCap);
-            ALLOC(c->d_absp, sizeof(float) * total);
-        }
-    }
-    ALLOC(c->d_cand_cnt, sizeof(int32_t) * (n + kXcds) * kCntStride);
-    ALLOC(c->d_ori, sizeof(cdvs_keypoint) * n * kp_capacity * kMaxOri);
-    ALLOC(c->d_ori_cnt, sizeof(int32_t) * n * kp_capacity);
-    ALLOC(c->d_flags, sizeof(int32_t));
-    ALLOC(c->d_cnn, sizeof(CnnImage) * n);
-    ALLOC(c->d_active, sizeof(int32_t) * n * kMaxOctaves);
-    ALLOC(c->d_cnn_frag, sizeof(short) * kCnnFragShorts);
-    ALLOC(c->d_scfv_prep, sizeof(float) * kScfvPrepFloats);
-    ALLOC(c->d_cnn_sums, sizeof(float) * (size_t)cnn_sum_floats(c->ncells, c->cnn_ftiles, c->wgrad_grid));
-    c->scfv_tiles = scfv_tile_blocks(n_images, kp_capacity);
-    if (c->scfv_tiles > 0) ALLOC(c->d_scfv_tiles, sizeof(float) * kScfvTileFloats * (size_t)c->scfv_tiles);
-    ALLOC(c->d_wh, sizeof(int32_t) * 2 * n);
-    ALLOC(c->d_img, sizeof(cdvs_image_desc) * n);
-    ALLOC(c->d_bm_blocks, sizeof(int32_t) * std::max<size_t>(1, c->bm_blocks.size()));
-    ALLOC(c->d_bm_H, sizeof(float) * kBmTransfers * kBmN);
-#undef ALLOC
+    std::vector<char> tables;
+    auto fill = [&tables, &arena](const void* src, size_t bytes) {   // the piece just cut
+        const size_t at = tables.size();
+        tables.resize(arena);
+        if (bytes) memcpy(tables.data() + at, src, bytes);
+    };
+#define TABLE(ptr, src, bytes)         \
+    do {                               \
+        ALLOC(ptr, bytes);             \
+        fill(src, bytes);              \
+    } while (0)
     std::vector<int32_t> wh(2 * n);
     for (size_t i = 0; i < n; ++i) {
         wh[2 * i] = images[i].width;
         wh[2 * i + 1] = images[i].height;
     }
-    if ((e = hipMemcpy(c->d_jobs, c->jobs.data(), sizeof(OctJob) * c->jobs.size(), hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemcpy(c->d_strips, c->strips.data(), sizeof(DetTile) * c->strips.size(), hipMemcpyHostToDevice)) !=
-            hipSuccess ||
-        (e = hipMemcpy(c->d_blur_owner, c->blur_owner.data(), sizeof(int32_t) * c->blur_owner.size(),
-                       hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemcpy(c->d_cnn_owner, c->cnn_owner.data(), sizeof(int32_t) * c->cnn_owner.size(),
-                       hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemcpy(c->d_geom, c->geom.data(), sizeof(OctGeom) * c->geom.size(), hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemcpy(c->d_cnn, c->cnn.data(), sizeof(CnnImage) * n, hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemcpy(c->d_wh, wh.data(), sizeof(int32_t) * 2 * n, hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemcpy(c->d_img, images, sizeof(cdvs_image_desc) * n, hipMemcpyHostToDevice)) != hipSuccess ||
-        (!c->bm_blocks.empty() &&
-         (e = hipMemcpy(c->d_bm_blocks, c->bm_blocks.data(), sizeof(int32_t) * c->bm_blocks.size(),
-                        hipMemcpyHostToDevice)) != hipSuccess) ||
-        (e = hipMemcpy(c->d_bm_H, c->bm_H, sizeof(float) * kBmTransfers * kBmN, hipMemcpyHostToDevice)) !=
-            hipSuccess ||
-        (e = hipMemcpy(c->d_cand_off, c->cand_off.data(), sizeof(int64_t) * n, hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemcpy(c->d_cand_capv, c->cand_cap.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice)) !=
-            hipSuccess ||
-        (e = hipMemset(c->d_flags, 0, sizeof(int32_t))) != hipSuccess ||
-        (e = hipMemset(c->d_active, 0, sizeof(int32_t) * n * kMaxOctaves)) != hipSuccess ||
-        (e = hipMemset(c->d_cand_cnt, 0, sizeof(int32_t) * (n + kXcds) * kCntStride)) != hipSuccess) {
+    TABLE(c->d_jobs, c->jobs.data(), sizeof(OctJob) * c->jobs.size());
+    TABLE(c->d_strips, c->strips.data(), sizeof(DetTile) * c->strips.size());
+    TABLE(c->d_blur_owner, c->blur_owner.data(), sizeof(int32_t) * c->blur_owner.size());
+    TABLE(c->d_cnn_owner, c->cnn_owner.data(), sizeof(int32_t) * c->cnn_owner.size());
+    TABLE(c->d_geom, c->geom.data(), sizeof(OctGeom) * c->geom.size());
+    TABLE(c->d_cnn, c->cnn.data(), sizeof(CnnImage) * n);
+    TABLE(c->d_wh, wh.data(), sizeof(int32_t) * 2 * n);
+    TABLE(c->d_img, images, sizeof(cdvs_image_desc) * n);
+    TABLE(c->d_bm_blocks, c->bm_blocks.data(), sizeof(int32_t) * c->bm_blocks.size());
+    TABLE(c->d_bm_H, c->bm_H, sizeof(float) * kBmTransfers * kBmN);
+    TABLE(c->d_cand_off, c->cand_off.data(), sizeof(int64_t) * n);
+    TABLE(c->d_cand_capv, c->cand_cap.data(), sizeof(int32_t) * n);
+#undef TABLE
+    ALLOC(c->d_flags, sizeof(int32_t));
+    ALLOC(c->d_active, sizeof(int32_t) * n * kMaxOctaves);
+    ALLOC(c->d_cand_cnt, sizeof(int32_t) * (n + kXcds) * kCntStride);
+    fill(nullptr, 0);
+    int64_t total = 0;
+    int32_t cmax = 0;
+    for (size_t i = 0; i < n; ++i) {
+        total += c->cand_cap[i];
+        cmax = std::max(cmax, c->cand_cap[i]);
+    }
+    ALLOC(c->d_cand, sizeof(cdvs_keypoint) * total);
+    if (cmax > kCandCap) {
+        ALLOC(c->d_sel, sizeof(uint32_t) * n * kCandCap);
+        ALLOC(c->d_absp, sizeof(float) * total);
+    }
+    ALLOC(c->d_ori, sizeof(cdvs_keypoint) * n * kp_capacity * kMaxOri);
+    ALLOC(c->d_ori_cnt, sizeof(int32_t) * n * kp_capacity);
+    ALLOC(c->d_cnn_frag, sizeof(short) * kCnnFragShorts);
+    ALLOC(c->d_scfv_prep, sizeof(float) * kScfvPrepFloats);
+    ALLOC(c->d_cnn_sums, sizeof(float) * (size_t)cnn_sum_floats(c->ncells, c->cnn_ftiles, c->wgrad_grid));
+    c->scfv_tiles = scfv_tile_blocks(n_images, kp_capacity);
+    if (c->scfv_tiles > 0) ALLOC(c->d_scfv_tiles, sizeof(float) * kScfvTileFloats * (size_t)c->scfv_tiles);
+#undef ALLOC
+    if ((e = hipMalloc(&c->d_arena, arena)) != hipSuccess) {
+        fail(nullptr, CDVS_ERR_HIP, "hipMalloc(%zu): %s", arena, hipGetErrorString(e));
+        cdvs_ctx_destroy(c);
+        return CDVS_ERR_HIP;
+    }
+    for (const auto& piece : pieces) {
+        void* at = (char*)c->d_arena + piece.second;
+        memcpy(piece.first, &at, sizeof(at));
+    }
+    if ((e = hipMemcpy(c->d_arena, tables.data(), tables.size(), hipMemcpyHostToDevice)) != hipSuccess) {
         fail(nullptr, CDVS_ERR_HIP, "context upload: %s", hipGetErrorString(e));
         cdvs_ctx_destroy(c);
         return CDVS_ERR_HIP;
