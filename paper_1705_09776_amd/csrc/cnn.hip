@@ -328,24 +328,27 @@ __device__ __forceinline__ float wave_sums(float (&v)[N], int lane) {
 
 // The first `n` words of out[] (the last in out_last when that is not null)
 // as the sums of `parts` rows of `stride` floats: 32 columns per workgroup
-// (the block-th), whose 32 lane rows take every 32nd row each.
+// (the block-th), whose 32 lane rows take every 32nd row each.  The rows are
+// large against their sum (gradients cancel), so they are added in 64 bits, at
+// no cost in a launch that waits for its loads (training step of 32 images
+// 154.7 us either way; the four waves' sums of k_conv_bwd too: 156.9).
 constexpr int kSumCols = 32, kSumRows = 32;
 __device__ __forceinline__ void sum_parts(int block, const float* __restrict__ part, int parts, int stride, int n,
                                           float* __restrict__ out, float* __restrict__ out_last) {
-    __shared__ float red[kSumRows][kSumCols + 1];
+    __shared__ double red[kSumRows][kSumCols + 1];
     const int c = threadIdx.x % kSumCols, r = threadIdx.x / kSumCols, col = block * kSumCols + c;
-    float s = 0.f;
+    double s = 0.0;
     if (col < n) {
 #pragma unroll 4
-        for (int p = r; p < parts; p += kSumRows) s += part[(int64_t)p * stride + col];
+        for (int p = r; p < parts; p += kSumRows) s += (double)part[(int64_t)p * stride + col];
     }
     red[r][c] = s;
     __syncthreads();
     if (r == 0 && col < n) {
 #pragma unroll
         for (int i = 1; i < kSumRows; ++i) s += red[i][c];
-        if (out_last && col == n - 1) *out_last = s;
-        else out[col] = s;
+        if (out_last && col == n - 1) *out_last = (float)s;
+        else out[col] = (float)s;
     }
 }
 
