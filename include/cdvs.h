@@ -576,7 +576,8 @@ int32_t cdvs_standin_consume(void* user, int32_t chunk, int32_t n_images, int32_
 typedef enum {
     CDVS_KERNEL_PREBLUR = 0,  /* u8 input -> G_{0,0} */
     CDVS_KERNEL_SCALES,       /* G_{o,0} -> G_{o,1..4} and G_{o+1,0}, one launch per octave */
-    CDVS_KERNEL_CLEAR,        /* (no launches: the finalisation leaves the counters at zero) */
+    CDVS_KERNEL_CLEAR,        /* (never bracketed: the finalisation leaves the counters at zero, and they are cleared
+                                  by launches of their own only after a call that failed before it) */
     CDVS_KERNEL_DETECT,       /* LoG + ALP + NMS + refinement: one launch over all octaves */
     CDVS_KERNEL_FINALIZE,     /* cross-octave duplicates, sort, top-k */
     CDVS_KERNEL_ORIENT,       /* orientation histograms and peaks */

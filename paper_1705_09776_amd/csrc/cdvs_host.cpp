@@ -44,7 +44,7 @@ struct cdvs_ctx {
     int wgrad_grid = 0;   // grid of the CNN backward kernels
     int cus = 256;        // compute units
     int detect_grid = 0;  // persistent detection grid (workgroups)
-    bool det_unfinished = false;  // a call ended between the detection and the finalisation that clears its counters
+    bool counters_dirty = false;  // detection counters may not be at zero (see clear_counters)
     // surrogate CNN cell grid
     std::vector<CnnImage> cnn;
     int64_t ncells = 0, max_cells = 0;   // of the batch, of the largest image
@@ -688,18 +688,39 @@ cdvs_status cdvs_pyramid_bmlog(cdvs_ctx* ctx, const uint8_t* d_images, float* d_
 
 static DetOut det_out(cdvs_ctx* ctx) { return DetOut{ctx->d_cand, ctx->d_cand_cnt, ctx->d_absp, ctx->d_flags}; }
 
-cdvs_status cdvs_alp_detect(cdvs_ctx* ctx, const float* d_pyr, const uint8_t* d_mask, cdvs_keypoint* d_kp,
-                            int32_t* d_count, void* stream) {
-    if (!ctx) return CDVS_ERR_STATE;
-    if (!d_pyr || !d_kp || !d_count) return fail(ctx, CDVS_ERR_ARG, "cdvs_alp_detect: null device pointer");
-    if (((uintptr_t)d_pyr & 255) != 0) return fail(ctx, CDVS_ERR_ARG, "cdvs_alp_detect: d_pyr not 256-byte aligned");
-    hipStream_t s = (hipStream_t)stream;
+// A detection starts from counters at zero (candidates, work, active cells),
+// where the finalisation of the one before it has left them.  A call that
+// ends in between puts them back by this itself, so that whatever runs next,
+// a graph's replay too, finds them clean; only if that fails as well does
+// counters_dirty stay set for the next call on the context to do it.
+static hipError_t clear_counters(cdvs_ctx* ctx, hipStream_t s) {
+    const hipError_t a = launch_clear(ctx->d_cand_cnt, ctx->n + kXcds, kCntStride, s);
+    const hipError_t b = launch_clear(ctx->d_active, ctx->n * kMaxOctaves, 1, s);
+    return a != hipSuccess ? a : b;
+}
+
+// Whether what is enqueued on s is recorded into a graph instead of run (true
+// when that cannot be told: the counters are then cleared once more).
+static bool recorded(hipStream_t s) {
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &c) == hipSuccess) return c != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();   // (not the next launch's)
+    return true;
+}
+
+// Clears the counters if they may not be at zero.  A recorded clear runs when
+// its graph is replayed, not now, so it leaves them dirty.
+static cdvs_status ensure_counters(cdvs_ctx* ctx, hipStream_t s) {
+    if (!ctx->counters_dirty) return CDVS_OK;
+    const bool later = recorded(s);
+    HIP_OR_FAIL(ctx, clear_counters(ctx, s));
+    ctx->counters_dirty = later;
+    return CDVS_OK;
+}
+
+static cdvs_status detect_and_finalize(cdvs_ctx* ctx, const float* d_pyr, const uint8_t* d_mask, cdvs_keypoint* d_kp,
+                                       int32_t* d_count, hipStream_t s) {
     GateParams gate{nullptr, nullptr, nullptr, 1.f};
-    if (ctx->det_unfinished) {
-        HIP_OR_FAIL(ctx, launch_clear(ctx->d_cand_cnt, ctx->n + kXcds, kCntStride, s));
-        HIP_OR_FAIL(ctx, launch_clear(ctx->d_active, ctx->n * kMaxOctaves, 1, s));
-    }
-    ctx->det_unfinished = true;
     if (d_mask) {
         Bracket b(ctx, CDVS_KERNEL_MASK_COUNT, s);
         HIP_OR_FAIL(ctx, launch_mask_count(d_mask, ctx->d_cnn, ctx->n, ctx->max_cells, ctx->d_active, s));
@@ -712,14 +733,24 @@ cdvs_status cdvs_alp_detect(cdvs_ctx* ctx, const float* d_pyr, const uint8_t* d_
         HIP_OR_FAIL(ctx, launch_detect_strips(d_pyr, ctx->d_strips, (int)ctx->strips.size(), ctx->strip_h, ctx->detect_variant,
                                               ctx->detect_grid, ctx->det, gate, ctx->d_cand_cnt + ctx->n * kCntStride, det_out(ctx), s));
     }
-    {
-        Bracket b(ctx, CDVS_KERNEL_FINALIZE, s);
-        HIP_OR_FAIL(ctx, launch_finalize(ctx->d_cand, ctx->d_absp, ctx->d_cand_cnt, ctx->d_cand_off, ctx->d_cand_capv,
-                                         d_mask ? ctx->d_active : nullptr, ctx->d_sel, ctx->d_wh, ctx->n, ctx->dedup_ratio, ctx->params.topk, ctx->kp_cap, d_kp,
-                                         d_count, ctx->d_flags, s));
-    }
-    ctx->det_unfinished = false;
+    Bracket b(ctx, CDVS_KERNEL_FINALIZE, s);
+    HIP_OR_FAIL(ctx, launch_finalize(ctx->d_cand, ctx->d_absp, ctx->d_cand_cnt, ctx->d_cand_off, ctx->d_cand_capv,
+                                     d_mask ? ctx->d_active : nullptr, ctx->d_sel, ctx->d_wh, ctx->n, ctx->dedup_ratio,
+                                     ctx->params.topk, ctx->kp_cap, d_kp, d_count, ctx->d_flags, s));
     return CDVS_OK;
+}
+
+cdvs_status cdvs_alp_detect(cdvs_ctx* ctx, const float* d_pyr, const uint8_t* d_mask, cdvs_keypoint* d_kp,
+                            int32_t* d_count, void* stream) {
+    if (!ctx) return CDVS_ERR_STATE;
+    if (!d_pyr || !d_kp || !d_count) return fail(ctx, CDVS_ERR_ARG, "cdvs_alp_detect: null device pointer");
+    if (((uintptr_t)d_pyr & 255) != 0) return fail(ctx, CDVS_ERR_ARG, "cdvs_alp_detect: d_pyr not 256-byte aligned");
+    hipStream_t s = (hipStream_t)stream;
+    cdvs_status st = ensure_counters(ctx, s);
+    if (st != CDVS_OK) return st;
+    st = detect_and_finalize(ctx, d_pyr, d_mask, d_kp, d_count, s);
+    if (st != CDVS_OK) ctx->counters_dirty = recorded(s) || clear_counters(ctx, s) != hipSuccess;
+    return st;
 }
 
 cdvs_status cdvs_orient(cdvs_ctx* ctx, const float* d_pyr, const cdvs_keypoint* d_kp_in, const int32_t* d_count_in,
@@ -1013,6 +1044,8 @@ cdvs_status cdvs_graph_capture_gated(cdvs_ctx* ctx, const uint8_t* d_images, con
 cdvs_status cdvs_graph_launch(cdvs_ctx* ctx, void* stream) {
     if (!ctx) return CDVS_ERR_STATE;
     if (!ctx->graph_exec) return fail(ctx, CDVS_ERR_STATE, "cdvs_graph_launch: no captured graph");
+    const cdvs_status st = ensure_counters(ctx, (hipStream_t)stream);
+    if (st != CDVS_OK) return st;
     HIP_OR_FAIL(ctx, hipGraphLaunch(ctx->graph_exec, (hipStream_t)stream));
     return CDVS_OK;
 }
@@ -1179,8 +1212,8 @@ cdvs_status cdvs_autotune(cdvs_ctx* ctx, const uint8_t* d_images, float* d_pyr, 
             },
             dus);
         if (st == CDVS_OK) best_dv = argmin(dus, kDetectVariants);
-        // as the finalisation would have left them
-        const hipError_t ec = launch_clear(ctx->d_cand_cnt, ctx->n + kXcds, kCntStride, s);
+        const hipError_t ec = clear_counters(ctx, s);   // as the finalisation would have left them
+        ctx->counters_dirty = ec != hipSuccess;
         if (st == CDVS_OK && ec != hipSuccess) st = fail(ctx, CDVS_ERR_HIP, "cdvs_autotune: %s", hipGetErrorString(ec));
     }
     (void)hipEventDestroy(e0);
