@@ -419,9 +419,9 @@ typedef struct {
  *     d_gv[image][i][.], bit k set when entry k is positive.
  * Shapes: d_gm, d_gv n_images x 512 x 32 floats; d_delta n_images x 512;
  * d_order n_images x 512 int32; d_bits n_images x 512 x 2 uint32.  Uses
- * 196 KB of context scratch and, in a context of at most 80 images, 75 KB
- * for each 32 descriptors of kp_capacity x n_images, at most 33 MB or one
- * image's (so calls on one context must not overlap). */
+ * 196 KB of context scratch and, in a context of few images (up to 80; 56 of
+ * kp_capacity 1000, 6 of 8192), 75 KB for each 32 descriptors of kp_capacity x
+ * n_images, at most 33 MB (so calls on one context must not overlap). */
 cdvs_status cdvs_scfv(cdvs_ctx* ctx, const cdvs_scfv_model* model, const float* d_desc, const int32_t* d_count,
                       float* d_gm, float* d_gv, float* d_delta, int32_t* d_order, uint32_t* d_bits, void* stream);
 

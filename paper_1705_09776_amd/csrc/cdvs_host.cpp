@@ -55,6 +55,7 @@ struct cdvs_ctx {
     float* d_scfv_prep = nullptr; // SCFV per-call model constants (kScfvPrepFloats)
     float* d_cnn_sums = nullptr;    // rows of sums of the CNN's backward pass (at most 19 MB)
     float* d_scfv_tiles = nullptr;  // SCFV tile blocks of a small batch
+    int32_t* d_scfv_place = nullptr;
     int scfv_tiles = 0;
     int32_t* d_wh = nullptr;      // per image: width, height
     cdvs_image_desc* d_img = nullptr;  // the image table (front-end output layout)
@@ -600,7 +601,10 @@ cdvs_status cdvs_ctx_create(const cdvs_params* params, const cdvs_image_desc* im
     ALLOC(c->d_scfv_prep, sizeof(float) * kScfvPrepFloats);
     ALLOC(c->d_cnn_sums, sizeof(float) * (size_t)cnn_sum_floats(c->ncells, c->cnn_ftiles, c->wgrad_grid));
     c->scfv_tiles = scfv_tile_blocks(n_images, kp_capacity);
-    if (c->scfv_tiles > 0) ALLOC(c->d_scfv_tiles, sizeof(float) * kScfvTileFloats * (size_t)c->scfv_tiles);
+    if (c->scfv_tiles > 0) {
+        ALLOC(c->d_scfv_tiles, sizeof(float) * kScfvTileFloats * (size_t)c->scfv_tiles);
+        ALLOC(c->d_scfv_place, sizeof(int32_t) * n);
+    }
 #undef ALLOC
     if ((e = hipMalloc(&c->d_arena, arena)) != hipSuccess) {
         fail(nullptr, CDVS_ERR_HIP, "hipMalloc(%zu): %s", arena, hipGetErrorString(e));
@@ -822,7 +826,7 @@ cdvs_status cdvs_scfv(cdvs_ctx* ctx, const cdvs_scfv_model* model, const float* 
     Bracket b(ctx, CDVS_KERNEL_SCFV, s);
     HIP_OR_FAIL(ctx, launch_scfv(d_desc, d_count, ctx->n, ctx->kp_cap, model->d_pca_mean, model->d_pca_matrix,
                                  model->d_weights, model->d_means, model->d_variances, ctx->d_scfv_prep,
-                                 ctx->d_scfv_tiles, ctx->scfv_tiles, d_gm, d_gv, d_delta, d_order, d_bits, s));
+                                 ctx->d_scfv_tiles, ctx->scfv_tiles, ctx->d_scfv_place, d_gm, d_gv, d_delta, d_order, d_bits, s));
     return CDVS_OK;
 }
 

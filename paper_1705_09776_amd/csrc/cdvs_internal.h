@@ -296,20 +296,36 @@ constexpr int kScfvPrepIsig = kScfvPrepRsw + kScfvComponents;
 constexpr int kScfvPrepFloats = kScfvPrepIsig + kScfvComponents * kScfvDim;   // 50176
 hipError_t launch_scfv(const float* desc, const int32_t* count, int n_images, int kp_cap, const float* pca_mean,
                        const float* pca_matrix, const float* weights, const float* means, const float* vars,
-                       float* prep, float* tiles, int tile_blocks, float* gm, float* gv, float* delta, int32_t* order,
-                       uint32_t* bits, hipStream_t s);
+                       float* prep, float* tiles, int tile_blocks, int32_t* place, float* gm, float* gv, float* delta,
+                       int32_t* order, uint32_t* bits, hipStream_t s);
 // Small batches form every descriptor tile's posteriors first, independently,
-// into tile blocks (32 descriptors: 512 posteriors, [x | x^2] and scale factors), as many
-// images at a time as the blocks hold, and sum over them afterwards.
+// into tile blocks (32 descriptors: 512 posteriors, [x | x^2] and scale factors),
+// and sum over them afterwards, in as many rounds as the blocks need.  Images
+// take the blocks that their descriptors fill, one after another, so only the
+// number of rounds launched follows from the capacity: with few descriptors
+// all are in the first, and a round without any costs 5 us.
 // scfv_tile_blocks: the blocks a context needs, 0 for a batch that takes one
 // workgroup per image instead.
 constexpr int kScfvTileFloats = 32 * (kScfvComponents + 2 * kScfvDim + 8);
-// Up to 80 images: a block costs about 0.14 us, while one workgroup per image
-// takes about 13 us per tile of the longest image, whatever their number
-// (700 to 1000 descriptors: 1 image 37 us, 56 images 245, 96 images 416, 128
-// images 569, against 330 to 415).
+// One workgroup per image takes 30 us and 12 per tile of the longest image,
+// whatever their number.  This form takes 25 us, 0.4 per image and 5 per round
+// whatever the descriptors, and 0.14 per tile.  The line lies where images of
+// one tile at most take about 60 us (the other form 43; 57 where it gathered its
+// operands one by one), beyond which few descriptors cost more than many save;
+// from seven rounds on the host's launches alone take longer than that.  By
+// images, capacity and descriptors, this form and the other: 56 of 1000: 32
+// descriptors 59 and 43 us, 100: 71 and 77, 300: 117 and 147, 1000: 264 and 405; 28
+// of 2000: 32: 47 and 43, 666: 107 and 276, 2000: 242 and 770; 14 of 4096: 32: 46
+// and 43, 1365: 129 and 530, 4096: 443 and 1530; beyond the line, 80 of 1000: 32:
+// 81 and 43, 300: 159 and 147, 1000: 392 and 405; 40 of 8192: 300: 222 and 147,
+// 8192: 5762 and 3054.  (With blocks given out by capacity, whatever the
+// descriptors: 56 of 1000 with 32: 118, 40 of 8192 with 300: 857.)
 constexpr int kScfvTilesMax = 448;         // 33 MB: 14 images of 1000 descriptors at a time
-constexpr int kScfvTilesMaxImages = 80;
+constexpr int kScfvTilesMaxImages = 80, kScfvRoundsMax = 6, kScfvRoundImages = 10, kScfvRoundsLine = 86;
+constexpr bool scfv_in_tiles(int n_images, int rounds) {
+    return n_images <= kScfvTilesMaxImages && rounds <= kScfvRoundsMax &&
+           n_images + kScfvRoundImages * (rounds - 1) <= kScfvRoundsLine;
+}
 int scfv_tile_blocks(int n_images, int kp_cap);
 // The allocation-free form keeps the same constants and, for small
 // batches, per-part sums S0, S1, S2 (kScfvPartialFloats each) of images

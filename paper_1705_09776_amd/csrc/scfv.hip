@@ -60,13 +60,48 @@ __device__ __forceinline__ int b_at(int j, int k) {
     return ((j >> 5) * 8 + (k >> 3)) * 256 + (32 * (k & 1) + (j & 31)) * 4 + ((k >> 1) & 3);
 }
 
+// An image's descriptors, and the tile blocks it takes (one if it has none).
+__device__ __forceinline__ int scfv_count(const int32_t* count, int img, int kp_cap) {
+    return min(max(count[img], 0), kp_cap);
+}
+__device__ __forceinline__ int scfv_blocks(int K) { return max(1, (K + TD - 1) / TD); }
+
+// place[i]: image i's first tile block, counted over rounds of `blocks` of
+// them: one image after another, each within one round.  By one wave.
+static_assert(kScfvTilesMaxImages <= 128, "two images per lane");
+__device__ __forceinline__ void place_images(const int32_t* __restrict__ count, int n, int kp_cap, int blocks,
+                                             int32_t* __restrict__ place) {
+    const int lane = threadIdx.x;
+    const int ta = lane < n ? scfv_blocks(scfv_count(count, lane, kp_cap)) : 0;
+    const int tb = lane + 64 < n ? scfv_blocks(scfv_count(count, lane + 64, kp_cap)) : 0;
+    int round0 = 0, used = 0, pa = 0, pb = 0;
+    for (int i = 0; i < n; ++i) {
+        const int t = __builtin_amdgcn_readlane(i < 64 ? ta : tb, i & 63);
+        if (used + t > blocks) {
+            round0 += blocks;
+            used = 0;
+        }
+        if (lane == i) pa = round0 + used;
+        if (lane + 64 == i) pb = round0 + used;
+        used += t;
+    }
+    if (lane < n) place[lane] = pa;
+    if (lane + 64 < n) place[lane + 64] = pb;
+}
+
 // Per-component constants of one call, derived on the device from the
 // caller's model: B[j][0..31] = M_j ./ V_j, B[j][32..63] = -1 / (2 V_j)
-// (at b_at(j, k)); c_j; 1/sqrt(w_j); 1/sigma_jk.
+// (at b_at(j, k)); c_j; 1/sqrt(w_j); 1/sigma_jk.  With `place`, a workgroup
+// more than the components need fills that.
 __global__ __launch_bounds__(256) void k_scfv_prep(const float* __restrict__ w, const float* __restrict__ means,
-                                                   const float* __restrict__ vars, float* __restrict__ prep) {
+                                                   const float* __restrict__ vars, float* __restrict__ prep,
+                                                   const int32_t* __restrict__ count, int n_images, int kp_cap, int blocks,
+                                                   int32_t* __restrict__ place) {
     const int j = blockIdx.x * 8 + (threadIdx.x >> 5), k = threadIdx.x & 31;
-    if (j >= NC) return;
+    if (j >= NC) {   // uniform
+        if (threadIdx.x < 64) place_images(count, n_images, kp_cap, blocks, place);
+        return;
+    }
     const float m = means[j * PD + k], v = vars[j * PD + k];
     float* B = prep + kScfvPrepB;
     B[b_at(j, k)] = m / v;
@@ -188,9 +223,10 @@ __device__ __forceinline__ void scfv_output(int img, int K, int wave, int lane, 
 // One workgroup of 8 waves per image (kWhole), or per part of an image: image
 // blockIdx.x / splits takes descriptor tiles [part * tiles_per_part, (part +
 // 1) * tiles_per_part) and either writes its sums S0, S1, S2 to partial block
-// blockIdx.x, which k_scfv_join adds up (kParts), or, one tile per part, the
-// tile's posteriors (before their scaling) and [X | X.*X] to tile block blockIdx.x, over which
-// k_scfv_sums then sums (kTiles; img0 is the first image).
+// blockIdx.x, which k_scfv_join adds up (kParts).  Or (kTiles) one workgroup
+// per tile: the tile that the images' places (k_scfv_prep) give to tile block
+// first + blockIdx.x, whose posteriors (before their scaling) and [X | X.*X]
+// go to block blockIdx.x, over which k_scfv_sums then sums.
 // Wave w owns components [64 w, 64 w + 64): their logits and their
 // gradient accumulators live in its registers for the whole range.
 constexpr int kWhole = 0, kParts = 1, kTiles = 2;
@@ -200,7 +236,8 @@ constexpr int kTileX = TD * NC, kTileQ = kTileX + TD * 64;
 static_assert(kScfvTileFloats == kTileQ + NW * TD, "tile block");
 template <int FORM>
 __global__ __launch_bounds__(512) void k_scfv(const float* __restrict__ desc, const int32_t* __restrict__ count,
-                                              int kp_cap, int img0, int splits, int tiles_per_part,
+                                              int kp_cap, int splits, int tiles_per_part,
+                                              const int32_t* __restrict__ place, int first, int n_images,
                                               const float* __restrict__ pca_mean,
                                               const float* __restrict__ pca_matrix, const float* __restrict__ means,
                                               const float* __restrict__ vars, const float* __restrict__ prep,
@@ -218,11 +255,30 @@ __global__ __launch_bounds__(512) void k_scfv(const float* __restrict__ desc, co
     __shared__ int sidx[NC];
 
     constexpr bool SPLIT = FORM != kWhole;
-    const int img = img0 + (SPLIT ? blockIdx.x / splits : blockIdx.x);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, h = lane >> 5, c32 = lane & 31;
-    const int K = min(max(count[img], 0), kp_cap);
+    int img, K, part = 0;
+    if constexpr (FORM == kTiles) {
+        // the image whose blocks hold this one: lane i looks at images i and i + 64
+        const int b = first + (int)blockIdx.x;
+        img = -1;
+        for (int i0 = 0; i0 < n_images && img < 0; i0 += 64) {   // uniform over the workgroup
+            const int i = min(i0 + lane, n_images - 1), k = scfv_count(count, i, kp_cap), p = place[i];
+            const uint64_t m = __ballot(i0 + lane < n_images && b >= p && b < p + scfv_blocks(k));
+            if (m) {
+                const int at = __ffsll((unsigned long long)m) - 1;
+                img = i0 + at;
+                K = __builtin_amdgcn_readlane(k, at);
+                part = b - __builtin_amdgcn_readlane(p, at);
+            }
+        }
+        if (img < 0) return;
+    } else {
+        img = SPLIT ? blockIdx.x / splits : blockIdx.x;
+        K = scfv_count(count, img, kp_cap);
+        if constexpr (SPLIT) part = blockIdx.x % splits;
+    }
     // descriptor range of this workgroup: [tbeg, tend)
-    const int tbeg = SPLIT ? min(K, (blockIdx.x % splits) * tiles_per_part * TD) : 0;
+    const int tbeg = SPLIT ? min(K, part * tiles_per_part * TD) : 0;
     const int tend = SPLIT ? min(K, tbeg + tiles_per_part * TD) : K;
     if (FORM == kTiles && tbeg >= tend) return;   // uniform over the workgroup
     const float* D = desc + (int64_t)img * kp_cap * kDescDim;
@@ -467,7 +523,7 @@ __global__ __launch_bounds__(512) void k_scfv_join(const float* __restrict__ par
     __shared__ int sidx[NC];
     const int img = blockIdx.x;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, h = lane >> 5, c32 = lane & 31;
-    const int K = min(max(count[img], 0), kp_cap);
+    const int K = scfv_count(count, img, kp_cap);
     const float* P0 = partial + (int64_t)img * splits * kScfvPartialFloats;
     s0s[tid] = P0[tid];
     f16v acc1[2], acc2[2];
@@ -484,7 +540,8 @@ __global__ __launch_bounds__(512) void k_scfv_join(const float* __restrict__ par
                 bits_out, skey, sidx);
 }
 
-// Sums and outputs of images whose tiles k_scfv<kTiles> has written: one
+// Sums and outputs of the images whose tiles k_scfv<kTiles> has written (those
+// placed in [first, first + blocks); others' workgroups end at once): one
 // workgroup per image and 16 components, wave w < 4 taking 16 of the 64
 // columns of [X | X.*X] with 16x16x4 MFMAs, the fifth wave S0.
 //
@@ -499,7 +556,8 @@ __global__ __launch_bounds__(512) void k_scfv_join(const float* __restrict__ par
 // (checked bit for bit on the device) -- so sums, order and bits are the same.
 constexpr int kSumWaves = 5;
 constexpr int kSumAhead = 4;   // tiles whose operands are on the way while one is added
-__global__ __launch_bounds__(64 * kSumWaves) void k_scfv_sums(const float* __restrict__ tiles, int img0, int tiles_per_image,
+__global__ __launch_bounds__(64 * kSumWaves) void k_scfv_sums(const float* __restrict__ tiles,
+                                                              const int32_t* __restrict__ place, int first, int blocks,
                                                               const int32_t* __restrict__ count, int kp_cap,
                                                               const float* __restrict__ means,
                                                               const float* __restrict__ vars,
@@ -507,10 +565,12 @@ __global__ __launch_bounds__(64 * kSumWaves) void k_scfv_sums(const float* __res
                                                               float* __restrict__ gv_out, float* __restrict__ delta_out,
                                                               uint32_t* __restrict__ bits_out) {
     __shared__ float S[16][64 + 1], s0s[16];
-    const int rel = blockIdx.x / (NC / 16), c0 = blockIdx.x % (NC / 16) * 16, img = img0 + rel;
+    const int img = blockIdx.x / (NC / 16), c0 = blockIdx.x % (NC / 16) * 16;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, kb = lane >> 4, li = lane & 15;
-    const int K = min(max(count[img], 0), kp_cap), nt = (K + TD - 1) / TD;
-    const float* T = tiles + (int64_t)rel * tiles_per_image * kScfvTileFloats;
+    const int at = place[img] - first;
+    const int K = scfv_count(count, img, kp_cap), nt = (K + TD - 1) / TD;
+    if (at < 0 || at >= blocks) return;   // uniform over the workgroup
+    const float* T = tiles + (int64_t)at * kScfvTileFloats;
     if (wave < 4) {
         // step j adds descriptors i = 2 j and 2 j + 1 of k_scfv's order, each
         // as the pair (h = 0, h = 1): lane group kb carries i = 2 j + kb / 2,
@@ -599,33 +659,40 @@ __global__ __launch_bounds__(256) void k_scfv_rank(const float* __restrict__ del
     if ((threadIdx.x & 3) == 0) order_out[(int64_t)img * NC + rank] = c;
 }
 
+// Rounds that hold every image, whatever its descriptors: an image has a round
+// to itself if it must, so each holds at least blocks / per images.
+int scfv_rounds(int n_images, int kp_cap, int blocks) {
+    const int images = blocks / ((kp_cap + TD - 1) / TD);
+    return (n_images + images - 1) / images;
+}
+
 }  // namespace
 
 int scfv_tile_blocks(int n_images, int kp_cap) {
-    const int64_t per = (kp_cap + TD - 1) / TD;
-    if (n_images > kScfvTilesMaxImages) return 0;
-    return (int)std::max(per, std::min<int64_t>(per * n_images, kScfvTilesMax) / per * per);
+    const int per = (kp_cap + TD - 1) / TD;   // an image's blocks at most
+    const int blocks = (int)std::max<int64_t>(per, std::min<int64_t>((int64_t)per * n_images, kScfvTilesMax));
+    return scfv_in_tiles(n_images, scfv_rounds(n_images, kp_cap, blocks)) ? blocks : 0;
 }
 
 hipError_t launch_scfv(const float* desc, const int32_t* count, int n_images, int kp_cap, const float* pca_mean,
                        const float* pca_matrix, const float* weights, const float* means, const float* vars,
-                       float* prep, float* tiles, int tile_blocks, float* gm, float* gv, float* delta, int32_t* order,
-                       uint32_t* bits, hipStream_t s) {
+                       float* prep, float* tiles, int tile_blocks, int32_t* place, float* gm, float* gv, float* delta,
+                       int32_t* order, uint32_t* bits, hipStream_t s) {
     if (n_images <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_scfv_prep, dim3(NC / 8), dim3(256), 0, s, weights, means, vars, prep);
     if (tile_blocks <= 0) {
-        hipLaunchKernelGGL(k_scfv<kWhole>, dim3(n_images), dim3(NW * 64), 0, s, desc, count, kp_cap, 0, 1, 0, pca_mean,
-                           pca_matrix, means, vars, prep, nullptr, gm, gv, delta, order, bits);
+        hipLaunchKernelGGL(k_scfv_prep, dim3(NC / 8), dim3(256), 0, s, weights, means, vars, prep, nullptr, 0, 0, 0, nullptr);
+        hipLaunchKernelGGL(k_scfv<kWhole>, dim3(n_images), dim3(NW * 64), 0, s, desc, count, kp_cap, 1, 0, nullptr, 0, 0,
+                           pca_mean, pca_matrix, means, vars, prep, nullptr, gm, gv, delta, order, bits);
         return hipGetLastError();
     }
-    // as many images at a time as the tile blocks hold
-    const int per = (kp_cap + TD - 1) / TD, round = tile_blocks / per;
-    for (int i0 = 0; i0 < n_images; i0 += round) {
-        const int m = std::min(round, n_images - i0);
-        hipLaunchKernelGGL(k_scfv<kTiles>, dim3(m * per), dim3(NW * 64), 0, s, desc, count, kp_cap, i0, per, 1, pca_mean,
-                           pca_matrix, means, vars, prep, tiles, nullptr, nullptr, nullptr, nullptr, nullptr);
-        hipLaunchKernelGGL(k_scfv_sums, dim3(m * (NC / 16)), dim3(64 * kSumWaves), 0, s, tiles, i0, per, count, kp_cap,
-                           means, vars, prep, gm, gv, delta, bits);
+    hipLaunchKernelGGL(k_scfv_prep, dim3(NC / 8 + 1), dim3(256), 0, s, weights, means, vars, prep, count, n_images, kp_cap,
+                       tile_blocks, place);
+    for (int r = 0; r < scfv_rounds(n_images, kp_cap, tile_blocks); ++r) {
+        hipLaunchKernelGGL(k_scfv<kTiles>, dim3(tile_blocks), dim3(NW * 64), 0, s, desc, count, kp_cap, 1, 1, place,
+                           r * tile_blocks, n_images, pca_mean, pca_matrix, means, vars, prep, tiles, nullptr, nullptr,
+                           nullptr, nullptr, nullptr);
+        hipLaunchKernelGGL(k_scfv_sums, dim3(n_images * (NC / 16)), dim3(64 * kSumWaves), 0, s, tiles, place,
+                           r * tile_blocks, tile_blocks, count, kp_cap, means, vars, prep, gm, gv, delta, bits);
     }
     hipLaunchKernelGGL(k_scfv_rank, dim3(n_images * (NC / 64)), dim3(256), 0, s, delta, order);
     return hipGetLastError();
@@ -672,16 +739,16 @@ hipError_t launch_scfv_static(float* scr, int splits, const float* desc, const i
                               int32_t* order, uint32_t* bits, hipStream_t s) {
     if (n_images <= 0) return hipSuccess;
     float* prep = scr;
-    hipLaunchKernelGGL(k_scfv_prep, dim3(NC / 8), dim3(256), 0, s, weights, means, vars, prep);
+    hipLaunchKernelGGL(k_scfv_prep, dim3(NC / 8), dim3(256), 0, s, weights, means, vars, prep, nullptr, 0, 0, 0, nullptr);
     if (splits <= 1) {
-        hipLaunchKernelGGL(k_scfv<kWhole>, dim3(n_images), dim3(NW * 64), 0, s, desc, count, kp_cap, 0, 1, 0, pca_mean,
-                           pca_matrix, means, vars, prep, nullptr, gm, gv, delta, order, bits);
+        hipLaunchKernelGGL(k_scfv<kWhole>, dim3(n_images), dim3(NW * 64), 0, s, desc, count, kp_cap, 1, 0, nullptr, 0, 0,
+                           pca_mean, pca_matrix, means, vars, prep, nullptr, gm, gv, delta, order, bits);
     } else {
         float* partial = scr + kScfvStaticPrepFloats;
         const int tiles = (kp_cap + TD - 1) / TD;
         const int per = (tiles + splits - 1) / splits;
-        hipLaunchKernelGGL(k_scfv<kParts>, dim3(n_images * splits), dim3(NW * 64), 0, s, desc, count, kp_cap, 0, splits,
-                           per, pca_mean, pca_matrix, means, vars, prep, partial, nullptr, nullptr, nullptr, nullptr,
+        hipLaunchKernelGGL(k_scfv<kParts>, dim3(n_images * splits), dim3(NW * 64), 0, s, desc, count, kp_cap, splits,
+                           per, nullptr, 0, 0, pca_mean, pca_matrix, means, vars, prep, partial, nullptr, nullptr, nullptr, nullptr,
                            nullptr);
         hipLaunchKernelGGL(k_scfv_reduce, dim3(n_images * (kScfvPartialFloats / 512)), dim3(256), 0, s, partial,
                            splits);
