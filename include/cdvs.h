@@ -113,9 +113,12 @@ cdvs_status cdvs_validate(const cdvs_params* params, const cdvs_image_desc* imag
 /* Create a context for one batch layout: n_images images described by the
  * host array `images` (copied).  kp_capacity is the per-image record count
  * of every keypoint buffer passed to the calls below (topk <= kp_capacity).
- * Allocates the context's device tables and scratch on the current device
- * (scratch is about 0.4 MB per image, and up to 33 MB more for the
- * aggregation of small batches, see cdvs_scfv).  On failure *out is NULL. */
+ * Allocates the context's device tables and scratch on the current device.
+ * The calls share the scratch, which is as large as the largest of them needs
+ * it: detection 48 bytes per candidate (0.4 MB per image of up to 0.5 megapixel,
+ * 0.8 bytes per pixel of larger ones), orientation 196 bytes per record, cdvs_cnn_backward
+ * 37 KB per 128 x 64 pixels (at most 19 MB), cdvs_scfv up to 33 MB for few
+ * images (see there).  On failure *out is NULL. */
 cdvs_status cdvs_ctx_create(const cdvs_params* params, const cdvs_image_desc* images, int32_t n_images,
                             int32_t kp_capacity, cdvs_ctx** out);
 void cdvs_ctx_destroy(cdvs_ctx* ctx);
@@ -419,7 +422,7 @@ typedef struct {
  *     d_gv[image][i][.], bit k set when entry k is positive.
  * Shapes: d_gm, d_gv n_images x 512 x 32 floats; d_delta n_images x 512;
  * d_order n_images x 512 int32; d_bits n_images x 512 x 2 uint32.  Uses
- * 196 KB of context scratch and, in a context of few images (up to 80; 56 of
+ * context scratch: 196 KB and, in a context of few images (up to 80; 56 of
  * kp_capacity 1000, 6 of 8192), 75 KB for each 32 descriptors of kp_capacity x
  * n_images, at most 33 MB (so calls on one context must not overlap). */
 cdvs_status cdvs_scfv(cdvs_ctx* ctx, const cdvs_scfv_model* model, const float* d_desc, const int32_t* d_count,
@@ -495,7 +498,9 @@ cdvs_status cdvs_cnn_labels(cdvs_ctx* ctx, const cdvs_keypoint* d_kp, const int3
  * octaves o, of the positive-weighted cross-entropy
  * w_o y softplus(-z) + (1 - y) softplus(z), y = label bit o, w = d_pos_weight
  * (6 fp32).  d_grad (CDVS_CNN_PARAMS fp32) and d_loss (1 fp32) are
- * overwritten.  d_work: caller scratch of 2 x cells x 16 uint16. */
+ * overwritten.  d_work: caller scratch of 2 x cells x 16 uint16; the sums of
+ * the gradients go through context scratch (37 KB per 128 x 64 pixels, at most
+ * 19 MB). */
 cdvs_status cdvs_cnn_backward(cdvs_ctx* ctx, const uint8_t* d_images, const float* d_params, const uint16_t* d_acts,
                               const float* d_logits, const uint32_t* d_labels, const float* d_pos_weight,
                               uint16_t* d_work, float* d_grad, float* d_loss, void* stream);

@@ -53,7 +53,7 @@ struct cdvs_ctx {
     int32_t* d_active = nullptr;  // [n][kMaxOctaves] active mask cells
     short* d_cnn_frag = nullptr;  // packed weight fragments of the fused inference kernel
     float* d_scfv_prep = nullptr; // SCFV per-call model constants (kScfvPrepFloats)
-    float* d_cnn_sums = nullptr;    // rows of sums of the CNN's backward pass (at most 19 MB)
+    float* d_cnn_sums = nullptr;    // rows of sums of the CNN's backward pass
     float* d_scfv_tiles = nullptr;  // SCFV tile blocks of a small batch
     int32_t* d_scfv_place = nullptr;
     int scfv_tiles = 0;
@@ -590,21 +590,36 @@ cdvs_status cdvs_ctx_create(const cdvs_params* params, const cdvs_image_desc* im
         total += c->cand_cap[i];
         cmax = std::max(cmax, c->cand_cap[i]);
     }
+    ALLOC(c->d_cnn_frag, sizeof(short) * kCnnFragShorts);
+    ALLOC(c->d_scfv_prep, sizeof(float) * kScfvPrepFloats);
+    // What a call only needs until its last launch lies in one scratch region
+    // that the calls share (two of them never run at once): detection,
+    // orientation, the CNN's backward pass, aggregation.  It is as large as the
+    // largest of them.
+    const size_t shared = arena;
+    size_t end = arena;
+    auto next_call = [&] {
+        end = std::max(end, arena);
+        arena = shared;
+    };
     ALLOC(c->d_cand, sizeof(cdvs_keypoint) * total);
     if (cmax > kCandCap) {
         ALLOC(c->d_sel, sizeof(uint32_t) * n * kCandCap);
         ALLOC(c->d_absp, sizeof(float) * total);
     }
+    next_call();
     ALLOC(c->d_ori, sizeof(cdvs_keypoint) * n * kp_capacity * kMaxOri);
     ALLOC(c->d_ori_cnt, sizeof(int32_t) * n * kp_capacity);
-    ALLOC(c->d_cnn_frag, sizeof(short) * kCnnFragShorts);
-    ALLOC(c->d_scfv_prep, sizeof(float) * kScfvPrepFloats);
+    next_call();
     ALLOC(c->d_cnn_sums, sizeof(float) * (size_t)cnn_sum_floats(c->ncells, c->cnn_ftiles, c->wgrad_grid));
+    next_call();
     c->scfv_tiles = scfv_tile_blocks(n_images, kp_capacity);
     if (c->scfv_tiles > 0) {
         ALLOC(c->d_scfv_tiles, sizeof(float) * kScfvTileFloats * (size_t)c->scfv_tiles);
         ALLOC(c->d_scfv_place, sizeof(int32_t) * n);
     }
+    next_call();
+    arena = end;
 #undef ALLOC
     if ((e = hipMalloc(&c->d_arena, arena)) != hipSuccess) {
         fail(nullptr, CDVS_ERR_HIP, "hipMalloc(%zu): %s", arena, hipGetErrorString(e));
