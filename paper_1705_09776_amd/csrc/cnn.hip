@@ -180,6 +180,9 @@ __global__ __launch_bounds__(FTHREADS, 2) void k_cnn_infer(const uint8_t* __rest
             d[FPLANE / 8] = make_uint4(w[4], w[5], w[6], w[7]);
         }
     }
+    // (ACTS: a cell of zeros, the first of the second buffer, which no layer
+    // writes: its outputs start at cell (1, 1))
+    if (ACTS && threadIdx.x < 2) *reinterpret_cast<uint4*>(&buf[1][threadIdx.x * FPLANE]) = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
 
     // The layers are unrolled, so each layer's output region is a constant.  A
@@ -188,9 +191,12 @@ __global__ __launch_bounds__(FTHREADS, 2) void k_cnn_infer(const uint8_t* __rest
     // pair m is read at one of three per-lane bases plus a constant: tap 0 of
     // the cell (the cell at (-1, -1)), shifted for the lanes that carry the
     // pair's second tap by that tap's distance from the first, which is one
-    // cell for pairs 0, 2 and 3 and FFW - 2 cells for pair 1, and not at all
-    // for pair 4, whose second tap is zero.  All ten loads of a step are
-    // issued before its MFMAs.
+    // cell for pairs 0, 2 and 3 and FFW - 2 cells for pair 1.  Pair 4's second
+    // tap is zero in the A operand: for training its lanes read the cell of
+    // zeros (an activation that has become infinite would give 0 x inf there,
+    // where the backward pass has to see what the nine taps give), for
+    // inference tap 8's cell again.  All ten loads of a step are issued before
+    // its MFMAs.
     constexpr int CB = FSTR * 2;            // bytes per cell of a plane
     constexpr int STEP = 32 * (FTHREADS / 64);
 #pragma unroll
@@ -204,6 +210,7 @@ __global__ __launch_bounds__(FTHREADS, 2) void k_cnn_infer(const uint8_t* __rest
 #pragma unroll
         for (int r = 0; r < 4; ++r) bn[r] = P[ln * LAYER_P + CONV_W + 4 * kb + r];
         const char* X = reinterpret_cast<const char*>(buf[l & 1]) + (kb & 1) * (FPLANE * 2);
+        const char* Z = reinterpret_cast<const char*>(buf[1]) + (kb & 1) * (FPLANE * 2);
         const char* XA = X + half * CB;
         const char* XB = X + half * (FFW - 2) * CB;
         char* Y = reinterpret_cast<char*>(buf[(l + 1) & 1]) + half * (FPLANE * 2) + 8 * (kb & 1) + (FFW + 1) * CB;
@@ -228,16 +235,15 @@ __global__ __launch_bounds__(FTHREADS, 2) void k_cnn_infer(const uint8_t* __rest
                 b[1][h] = *reinterpret_cast<const s8*>(XB + o + toff(2));
                 b[2][h] = *reinterpret_cast<const s8*>(XA + o + toff(4));
                 b[3][h] = *reinterpret_cast<const s8*>(XA + o + toff(6));
-                b[4][h] = *reinterpret_cast<const s8*>(X + o + toff(8));
+                b[4][h] = *reinterpret_cast<const s8*>(ACTS && half ? Z : X + o + toff(8));
             }
             f4 acc[2] = {bias, bias};
 #pragma unroll
             for (int m = 0; m < kTapPairs; ++m)
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    // (the tenth tap's lanes read tap 8's cell again: its A
-                    // fragment is zero and every activation is finite and
-                    // non-negative, so those products add exact zeros)
+                    // (the tenth tap's products add exact zeros: its A fragment
+                    // is zero and the activations are finite and non-negative)
                     acc[h] = mfma32(a[m], b[m][h], acc[h]);
                 }
             // relu, bf16, zero outside the image (selected, no branch), one
