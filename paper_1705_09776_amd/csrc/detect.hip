@@ -281,12 +281,12 @@ __device__ __forceinline__ void strip_drain(float (*q)[kQCap], int& qn, const De
 __device__ __forceinline__ void workgroup_drain(float (*q)[kQCap], int qn, const DetTile& job, const DetParams& dp,
                                                 const DetOut& out) {
     __shared__ int cnt_s[4], img_s[4], base_s[4];
-    static_assert(kQCap <= 128, "two passes");
+    static_assert(kQFlush <= 64, "one pass: a strip leaves no more than that");
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const Refined r0 = strip_refine(q, 0, qn, dp), r1 = strip_refine(q, 64, qn, dp);
-    const uint64_t m0 = __ballot(r0.keep), m1 = __ballot(r1.keep);
+    const Refined r = strip_refine(q, 0, qn, dp);
+    const uint64_t m = __ballot(r.keep);
     if (lane == 0) {
-        cnt_s[wave] = __popcll(m0) + __popcll(m1);
+        cnt_s[wave] = __popcll(m);
         img_s[wave] = job.image;
     }
     __syncthreads();
@@ -299,10 +299,7 @@ __device__ __forceinline__ void workgroup_drain(float (*q)[kQCap], int qn, const
     __syncthreads();
     int before = 0, first = wave;
     while (first > 0 && img_s[first - 1] == job.image) before += cnt_s[--first];
-    const int base = base_s[first] + before;
-    const uint64_t lower = (1ull << lane) - 1ull;
-    if (r0.keep) store_candidate(r0, base + __popcll(m0 & lower), job, out);
-    if (r1.keep) store_candidate(r1, base + __popcll(m0) + __popcll(m1 & lower), job, out);
+    if (r.keep) store_candidate(r, base_s[first] + before + __popcll(m & ((1ull << lane) - 1ull)), job, out);
 }
 
 // Centre tests of one row y from the coefficients of rows y-1, y, y+1;
@@ -688,7 +685,6 @@ __device__ __forceinline__ void strongest(const float* __restrict__ absp, int n,
     if (tid < 2) tmp[tid] = 0;
     __syncthreads();
     const int lane = tid & 63;
-#pragma unroll 2
     for (int i0 = 0; i0 < n; i0 += 4 * FIN_THREADS) {   // the same for every lane: they count together
         const int i = i0 + 4 * tid;
         uint4 k = make_uint4(0u, 0u, 0u, 0u);
