@@ -10,8 +10,8 @@
 // and the records are ordered by the complement of r's bits (r >= 0, so its
 // bits order like its value), equal ones by input index, and the first n_keep
 // are copied out.  Up to 1024 records, one per lane, are sorted by four stable
-// counting passes of 8 bits; more by a bitonic sort on (r, index) pairs in
-// LDS.  The bitonic sort's exchanges at distances below 128 stay inside one
+// counting passes of 8 bits; more, and few of them in many images, by a bitonic
+// sort on (r, index) pairs in LDS.  The bitonic sort's exchanges at distances below 128 stay inside one
 // 128-key chunk, which one wave holds in registers (two keys per lane) and
 // exchanges by lane shuffles; only the longer distances go through LDS with a
 // workgroup barrier each.  Either is a chain of exchanges in a single
@@ -25,6 +25,13 @@ namespace cdvs {
 namespace {
 
 constexpr int kRelThreads = 1024;
+// Images of at most kRelFew records in a batch of more than kRelFewImages
+// take the bitonic sort: its few stages leave most of their workgroup's waves
+// idle, which then stand in nobody's way, while every wave counts in all four
+// passes (for 64, 256 and 300 records, bitonic and counting: 256 images 8.5 and
+// 7.4, 8.4 and 7.8, 8.7 and 8.0 us; 512 images 9.0 and 13.0, 11.4 and 13.7, 15.2 and
+// 14.7; 4096 images 59 and 93, 87 and 104, 114 and 112).
+constexpr int kRelFew = 256, kRelFewImages = 256;
 
 __device__ __forceinline__ float centre_distance(float x, float y, float hx, float hy) {
 #pragma clang fp contract(off)
@@ -198,7 +205,7 @@ __global__ __launch_bounds__(kRelThreads) void k_relevance(const cdvs_keypoint* 
         for (int c = 1; c < kRelFeatures; ++c) r = r * sv[c * kRelBins + bin_of(se + c * kRelEdges, f[c])];
         return 0xFFFFFFFFu - __float_as_uint(r);
     };
-    if (n <= kRelThreads) {   // uniform
+    if (n <= kRelThreads && (n > kRelFew || gridDim.x <= kRelFewImages)) {   // uniform
         uint32_t k = tid < n ? score(tid) : 0xFFFFFFFFu;   // padding sorts last: no key is higher, and the index is
         int idx;
         radix_sort_lanes(sm.radix, k, idx);
