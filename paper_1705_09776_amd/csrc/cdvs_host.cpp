@@ -401,10 +401,11 @@ static cdvs_status build_layout(cdvs_ctx* c) {
     }
     c->strip_h = det_strip_height(tall);
     c->strips.reserve((size_t)tall * (kDetStripH / c->strip_h));   // a strip is at most so many
+    size_t next[kMaxOctaves] = {};   // an octave's jobs lie in image order
     for (int i = 0; i < c->n; ++i)
         for (int o = 0; o < kMaxOctaves; ++o)
-            for (const OctJob& j : per_oct[o]) {
-                if (j.image != i) continue;
+            for (; next[o] < per_oct[o].size() && per_oct[o][next[o]].image == i; ++next[o]) {
+                const OctJob& j = per_oct[o][next[o]];
                 const int b = c->params.border;
                 const int cw = j.w - 2 * b, ch = j.h - 2 * b;
                 if (cw <= 0 || ch <= 0) continue;
@@ -540,11 +541,20 @@ cdvs_status cdvs_ctx_create(const cdvs_params* params, const cdvs_image_desc* im
     c->cus = cus;
     hipError_t e = hipSuccess;
     const size_t n = (size_t)n_images;
-    // One allocation, cut at 256 bytes, whose first part holds the tables and
-    // the counters that start at zero and is written by one copy: each
+    // One allocation, cut at 256 bytes, whose first part holds the small tables
+    // and the counters that start at zero and is written by one copy: each
     // hipMalloc of 2 MB or more and each copy takes ten microseconds or more,
-    // and images of new sizes need a new context.
+    // and images of new sizes need a new context.  A large table is copied from
+    // where it lies (through the first part, new pages of the host's for
+    // each made that 1.4 ms for 64 images of 1600x1200).
+    constexpr size_t kLargeTable = 64 << 10;
+    struct Upload {
+        void** to;
+        const void* src;
+        size_t bytes;
+    };
     std::vector<std::pair<void*, size_t>> pieces;   // address of the pointer, offset
+    std::vector<Upload> large;
     size_t arena = 0;
 #define ALLOC(ptr, bytes)                                   \
     do {                                                    \
@@ -552,15 +562,20 @@ cdvs_status cdvs_ctx_create(const cdvs_params* params, const cdvs_image_desc* im
         arena += ((size_t)(bytes) + 255) & ~(size_t)255;    \
     } while (0)
     std::vector<char> tables;
+    tables.reserve(16 * kLargeTable);
     auto fill = [&tables, &arena](const void* src, size_t bytes) {   // the piece just cut
         const size_t at = tables.size();
         tables.resize(arena);
         if (bytes) memcpy(tables.data() + at, src, bytes);
     };
-#define TABLE(ptr, src, bytes)         \
-    do {                               \
-        ALLOC(ptr, bytes);             \
-        fill(src, bytes);              \
+#define TABLE(ptr, src, bytes)                                        \
+    do {                                                              \
+        if ((bytes) > kLargeTable) {                                  \
+            large.push_back(Upload{(void**)&(ptr), src, bytes});      \
+        } else {                                                      \
+            ALLOC(ptr, bytes);                                        \
+            fill(src, bytes);                                         \
+        }                                                             \
     } while (0)
     std::vector<int32_t> wh(2 * n);
     for (size_t i = 0; i < n; ++i) {
@@ -584,6 +599,7 @@ cdvs_status cdvs_ctx_create(const cdvs_params* params, const cdvs_image_desc* im
     ALLOC(c->d_active, sizeof(int32_t) * n * kMaxOctaves);
     ALLOC(c->d_cand_cnt, sizeof(int32_t) * (n + kXcds) * kCntStride);
     fill(nullptr, 0);
+    for (const Upload& t : large) ALLOC(*t.to, t.bytes);
     int64_t total = 0;
     int32_t cmax = 0;
     for (size_t i = 0; i < n; ++i) {
@@ -630,7 +646,10 @@ cdvs_status cdvs_ctx_create(const cdvs_params* params, const cdvs_image_desc* im
         void* at = (char*)c->d_arena + piece.second;
         memcpy(piece.first, &at, sizeof(at));
     }
-    if ((e = hipMemcpy(c->d_arena, tables.data(), tables.size(), hipMemcpyHostToDevice)) != hipSuccess) {
+    e = hipMemcpy(c->d_arena, tables.data(), tables.size(), hipMemcpyHostToDevice);
+    for (const Upload& t : large)
+        if (e == hipSuccess) e = hipMemcpy(*t.to, t.src, t.bytes, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
         fail(nullptr, CDVS_ERR_HIP, "context upload: %s", hipGetErrorString(e));
         cdvs_ctx_destroy(c);
         return CDVS_ERR_HIP;
