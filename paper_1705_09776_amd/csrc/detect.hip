@@ -1,20 +1,22 @@
 // ALP keypoint detection on gfx950 (Sec. III-A, Eqs. (2)-(3); Sec. IV-A,
 // Algorithm 1 stages A-C).
 //
-// k_detect_strip: one wave per strip of 60 x 48 centres of one (image,
-//   octave), all octaves of all images in one launch; the wave streams the
-//   five Gaussian images down its strip in registers (details at the kernel).
-//   Per centre: scale-normalised 5-point Laplacians, the four ALP
-//   coefficients, extremal scale, contrast test, strict 8-neighbour test at
-//   that scale, one quadratic refinement step; survivors go to the image's
-//   candidate list with one ballot and one atomic per pass.  With a cell
-//   mask (the learned gate) only the centres of active cells are examined
-//   and strips without any are skipped before loading anything.
+// k_detect_strip: one wave per strip of 60 columns by 6 to 48 rows of centres of
+//   one (image, octave), all octaves of all images in one launch; the wave
+//   streams the five Gaussian images down its strip in registers (details at
+//   the kernel).  Per centre: scale-normalised 5-point Laplacians, the four
+//   ALP coefficients, extremal scale, contrast test, strict 8-neighbour test
+//   at that scale, one quadratic refinement step; survivors go to the image's
+//   candidate list, those that a workgroup's strips have left at the end with
+//   one atomic for each image.  With a cell mask (the learned gate) only the
+//   centres of active cells are examined and strips without any are skipped
+//   before loading anything.
 // k_finalize: one workgroup per image.  (Images with more candidates than it
 //   holds: their strongest kCandCap by |p|.)  Stage C (cross-octave
-//   duplicates) over cells of the adjacent octaves, then a bitonic sort in LDS
-//   on the 64-bit key (|p| desc, octave, iy, ix) of what can be among the top
-//   k, and the copy-out.
+//   duplicates) over cells of the adjacent octaves, a counting sort over bins
+//   of |p| for the canonical order (|p| descending, octave, iy, ix) of what can
+//   be among the top k, and the copy-out.  It leaves the detection's counters
+//   at zero for the next one.
 #include <algorithm>
 
 #include "cdvs_internal.h"
